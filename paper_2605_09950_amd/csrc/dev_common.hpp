@@ -267,6 +267,8 @@ struct JobDev {
     uint8_t* orig;         // [p][n_pad] binned originals
     uint8_t* sha;          // [max_sha][n_pad] shadows of the current iteration
     const uint8_t** colptr;// [pw_cap] widened column -> bins
+    const uint8_t* colbase;// start of the device region: every column starts a multiple of
+                           // 256 bytes past it
     int32_t* col_src;      // [pw_cap]
     int32_t* act;          // [p] active originals, ascending
     int8_t* state;         // [p]
@@ -390,7 +392,8 @@ struct ForestDev {
     uint32_t node_cap, slot_cap, small_cap;
     uint32_t next_base;   // first node index of the next level
     uint32_t n_small_cur; // small nodes searched in this level
-    uint32_t small_ncap;  // a node takes the wave path only below this weighted count
+    uint32_t small_ncap;  // a node takes the wave path only below this weighted count (its
+                          // class counts fit 8 bits)
     int32_t kmax, parity, split_rank;
     int32_t has_cls, has_reg;  // the plan holds classification / regression jobs
     int32_t split_k;      // a plan of more than 4 class planes that also holds jobs of at

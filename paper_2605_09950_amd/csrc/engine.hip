@@ -826,6 +826,7 @@ void Engine::setup(std::vector<int>& status) {
         J.orig = at<uint8_t>(jp.orig);
         J.sha = at<uint8_t>(jp.sha);
         J.colptr = at<const uint8_t*>(jp.colptr);
+        J.colbase = (const uint8_t*)base;
         J.col_src = at<int32_t>(jp.colsrc);
         J.act = at<int32_t>(jp.act);
         J.state = at<int8_t>(jp.state);
@@ -948,9 +949,7 @@ ForestDev Engine::forest() const {
     F.has_cls = pl.has_cls ? 1 : 0;
     F.has_reg = pl.has_reg ? 1 : 0;
     F.split_k = pl.kmax > 4 && pl.has_small_k ? 1 : 0;
-    // the wave path packs class counters in 32/kmax-bit fields up to 4 classes
-    // (16-bit for 2, 10-bit for 3, 8-bit for 4), 16-bit fields beyond
-    F.small_ncap = pl.kmax == 4 ? 256u : (pl.kmax == 3 ? 1024u : 65536u);
+    F.small_ncap = 256u;  // the wave path packs class counters in 8-bit fields
     return F;
 }
 

@@ -73,6 +73,17 @@ __device__ __forceinline__ float wave_max_f_dpp(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// Minimum over the wave, as a wave-uniform value.
+__device__ __forceinline__ uint32_t wave_min_u_dpp(uint32_t v) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xa, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xc, 0xf, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 __device__ __forceinline__ float wave_max_f(float v) {
 #pragma unroll
     for (int m = 1; m < 64; m <<= 1) v = fmaxf(v, __shfl_xor(v, m));
@@ -205,6 +216,49 @@ __device__ __forceinline__ Cand wave_best_total_fp32(const Cand& c, float q32) {
         f.b = 0x7FFFFFFF;
     }
     return wave_best_total_exact(f);
+}
+
+// Packed class counters: nodes of weight N < 256 hold a side's class counts as
+// 8-bit fields, four classes to a 32-bit word.  The dot product of bytes
+// (full rate) gives the exact integers of a split: for left counts l and node
+// counts c, N_L = sum l, S_L = sum l^2 and, from sum c l, S_R = sum (c - l)^2
+// = S - 2 sum c l + S_L.  All stay below 2^16, so they are exact in FP32 too.
+struct Side8 {
+    uint32_t nl, sl, sr;
+};
+
+__device__ __forceinline__ uint32_t dot4(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_udot4(a, b, c, false);
+}
+
+template <int WORDS>
+__device__ __forceinline__ Side8 side8(const uint32_t* l, const uint32_t* c, uint32_t S) {
+    Side8 s;
+    uint32_t nl = 0, sl = 0, cl = 0;
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) {
+        nl = dot4(l[w], 0x01010101u, nl);
+        sl = dot4(l[w], l[w], sl);
+        cl = dot4(l[w], c[w], cl);
+    }
+    s.nl = nl;
+    s.sl = sl;
+    s.sr = S - 2u * cl + sl;
+    return s;
+}
+
+// FP32 ranking score (both sides non-empty): the integers convert exactly,
+// so the relative error is within 4u (reciprocal 2u, product and sum u each).
+__device__ __forceinline__ float side_q32(const Side8& s, uint32_t N) {
+    return (float)s.sl * __builtin_amdgcn_rcpf((float)s.nl) +
+           (float)s.sr * __builtin_amdgcn_rcpf((float)(N - s.nl));
+}
+
+// Q_a > Q_b exactly (numerators below 2^25, denominators below 2^14).
+__device__ __forceinline__ bool side_better(const Side8& a, const Side8& b, uint32_t N) {
+    const uint32_t na = a.sl * (N - a.nl) + a.sr * a.nl, da = a.nl * (N - a.nl);
+    const uint32_t nb = b.sl * (N - b.nl) + b.sr * b.nl, db = b.nl * (N - b.nl);
+    return (uint64_t)na * db > (uint64_t)nb * da;
 }
 
 enum : int { kLeaf = 0, kSmall = 1, kLarge = 2 };

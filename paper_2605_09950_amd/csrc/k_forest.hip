@@ -129,52 +129,47 @@ __global__ __launch_bounds__(1024) void k_boot_compact(ForestDev F0) {
 // Small nodes: one wavefront per node.  With W = the node's row count rounded
 // up to a power of two, the wave is split into 64/W segments of W lanes; a
 // segment holds the node's rows (one per lane) and evaluates one drawn
-// feature, so 64/W features are scored per pass.  The left class counts of
-// the threshold at a lane's own bin come from an all-pairs sum over the
-// segment; the bins of the next pass are gathered while this one computes.
+// feature, so 64/W features are scored per pass.  The bins of the next passes
+// are gathered while this one computes.  A node of this path weighs less than
+// 256 rows, so the class counts on the left of the threshold at a lane's own
+// bin are 8-bit fields, four classes to a word (Pk8), from
+//   * segments of up to 16 lanes: an all-pairs sum (W lane permutes a pass);
+//   * segments of 32 or 64 lanes: a histogram of the packed counters in LDS,
+//     one word per bin, summed over the bins by a wave scan and read back at
+//     the lane's bin.
+// A lane permute costs 6 cycles of the CU's one LDS pipe, so W of them pass
+// the histogram's six 16-byte accesses (8 cycles each) between W = 16 and 32.
+// Against 64-bit class sums and an exact butterfly per node (traced beside the
+// histogram kernels): 64 jobs of 2-5 classes 155 -> 47 ms over six iterations,
+// n = 10,000 x 500 of 3 classes 50 -> 35 us a launch, n = 100,000 x 2,000 of 4
+// 830 -> 730 us (there the bin gathers bound it).
 struct SmallOut {
     int kinds[2];
     uint32_t child;
     uint64_t alg;
 };
 
-// Packed per-class counters of the wave path: KMAX <= 4 classes fit one
-// 32-bit word (16-bit fields for 2 classes, 8-bit for 4; the node's weighted
-// count stays below the field range), more classes use 64-bit words of four
-// 16-bit fields.
-template <int KMAX>
-struct Pack {
-    static constexpr bool kU32 = KMAX <= 4;
-    typedef typename std::conditional<kU32, uint32_t, uint64_t>::type word;
-    static constexpr int kPer = kU32 ? KMAX : 4;         // fields per word
-    static constexpr int kBits = kU32 ? 32 / KMAX : 16;  // bits per field
-    static constexpr int kWords = kU32 ? 1 : KMAX / 4;
-    static __device__ __forceinline__ uint32_t field(word w, int k) {
-        return (uint32_t)(w >> (kBits * (k % kPer))) & ((1u << kBits) - 1u);
-    }
-};
-
 __device__ __forceinline__ uint32_t readlane_w(uint32_t v, int src) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, src);
 }
-__device__ __forceinline__ uint64_t readlane_w(uint64_t v, int src) { return readlane64(v, src); }
 
-// tab: the wave's kDrawTab-entry LDS region for the node's permutation
-// round table (as in k_draws); scnt: the wave's 64 LDS words for the rows'
-// one-word class counters
-template <int KMAX>
-__device__ void small_node(const ForestDev& F, uint32_t idx, SmallOut& out, uint16_t* tab,
-                           uint32_t* scnt) {
-    typedef Pack<KMAX> PK;
-    typedef typename PK::word word;
+// Words of LDS per wave of the small-node kernel: the permutation round table
+// (kDrawTab 16-bit entries), the rows' counters, two packed histograms.
+__host__ __device__ constexpr uint32_t small_lds_words(int words) {
+    return kDrawTab / 2 + (uint32_t)words * (64u + 512u);
+}
+
+// lds: the wave's LDS region of small_lds_words(WORDS) words
+template <int WORDS>
+__device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, const NodeDev& nd,
+                                           const TreeDev& tr, JobDev& J, SmallOut& out,
+                                           uint32_t* lds) {
+    uint16_t* tab = reinterpret_cast<uint16_t*>(lds);
+    uint32_t* scnt = lds + kDrawTab / 2;    // [WORDS][64] the rows' counter words
+    uint32_t* hist = scnt + WORDS * 64;     // [2][WORDS][256] packed histograms
     const int lane = threadIdx.x & 63;
-    out.kinds[0] = out.kinds[1] = kLeaf;
-    out.child = F.next_base + 2u * idx;
-    const uint32_t id = uniform(F.small_in[idx]);
-    const NodeDev nd = F.nodes[id];
-    const TreeDev tr = F.trees[nd.tree];
-    JobDev& J = F.jobs[tr.job];
-    const int B = J.B;
+    const int B = J.B, mtry = J.mtry;
+    const bool rowmaj = J.rowmaj != nullptr;
     const size_t tbase = (size_t)tr.tau * J.rstride + nd.seg;
     const uint64_t* rin = J.rec[F.parity] + tbase;
     uint64_t* rout = J.rec[F.parity ^ 1] + tbase;
@@ -186,20 +181,17 @@ __device__ void small_node(const ForestDev& F, uint32_t idx, SmallOut& out, uint
     const bool valid = i < len;
     const uint64_t rec = valid ? ldg(rin + i) : 0ull;
     const uint32_t row = rec_row(rec), wt = rec_w(rec), yv = rec_y(rec);
-    // class counter word of this lane's row; zero outside segment 0 so that
-    // reading lane j >= len (any segment) contributes nothing
-    word cv[PK::kWords];
+    const uint32_t inc = wt << ((yv & 3u) * 8u);  // this lane's row in its counter word
+    const uint32_t yw = yv >> 2;                  // that word
+    uint32_t cn[WORDS];  // the node's class counts, packed (each below 256)
+    uint32_t S = 0;      // their sum of squares
 #pragma unroll
-    for (int w = 0; w < PK::kWords; ++w)
-        cv[w] = (seg == 0 && valid && (int)yv / PK::kPer == w)
-                    ? ((word)wt << (PK::kBits * ((int)yv % PK::kPer)))
-                    : (word)0;
-    uint32_t cnode[KMAX];
-    uint64_t S = 0;
+    for (int w = 0; w < WORDS; ++w) {
+        cn[w] = 0;
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        cnode[k] = k < J.K ? F.cls[(size_t)id * F.kmax + k] : 0u;
-        S += (uint64_t)cnode[k] * cnode[k];
+        for (int k = 0; k < 4; ++k)
+            if (4 * w + k < J.K) cn[w] |= F.cls[(size_t)id * F.kmax + 4 * w + k] << (8 * k);
+        S = dot4(cn[w], cn[w], S);
     }
     const uint32_t N = nd.n;
     const KeyedPerm P = make_perm(J.seed_lo, J.seed_hi, kMtry, (uint32_t)J.t, (uint32_t)tr.tau,
@@ -215,117 +207,127 @@ __device__ void small_node(const ForestDev& F, uint32_t idx, SmallOut& out, uint
     }
     // Each lane keeps the best of its own candidates over the passes (they
     // arrive in increasing draw position, so an exact tie keeps the earlier
-    // one); one wave-wide reduction per node picks the winner.  With FP32
+    // one); one wave-wide selection per node picks the winner.  With FP32
     // ranking, two candidates are compared exactly only when their FP32
-    // scores are within the ranking margin of each other.
-    Cand lb;
-    lb.nl = 0;
-    lb.q = 0x7FFFFFFF;
-    lb.b = 0x7FFFFFFF;
-    lb.f = 0;
-    lb.nr = 0;
-    lb.pad = 0;
-    lb.sl = lb.sr = 0;
+    // scores are within the ranking margin of each other and their partitions
+    // are not the same one (equal or mirrored counts: an exact tie, which is
+    // what most near scores of small nodes are).
+    bool has = false;
     float lq = -1.0f;
+    int ld = 0, lb = 0;     // draw position and threshold of the lane's best
+    uint32_t la[WORDS];     // its left counts
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) la[w] = 0;
     const bool fp32 = F.split_rank != 0;
     const int abase = (lane - i) << 2;  // ds_bpermute byte address of the segment's lane 0
-    if constexpr (PK::kWords == 1) {
-        // row j's counter word at scnt[j] (lane j holds row j in segment 0;
-        // every other lane holds zero): the passes read four rows' counters
-        // per LDS broadcast instead of one lane read per row
+    const bool pairs = W <= 16;
+    if (pairs) {
+        // row j's counter words at scnt[w][j] (lane j holds row j in segment
+        // 0; every other lane holds zero): the passes read four rows'
+        // counters per LDS broadcast
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the previous node's reads
-        scnt[lane] = (uint32_t)cv[0];
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w)
+            scnt[w * 64 + lane] = seg == 0 && valid && yw == (uint32_t)w ? inc : 0u;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
-    for (int q0 = 0; q0 < J.mtry; q0 += 64) {
-        const int nq = min(64, J.mtry - q0);
+    const uint8_t* rowbase = rowmaj ? J.rowmaj + (size_t)row * J.rm_stride : J.colbase + row;
+    for (int q0 = 0; q0 < mtry; q0 += 64) {
+        const int nq = min(64, mtry - q0);
         const int myf =
             lane < nq ? (int)(use_tab ? perm_apply_tab(P, tab, (uint32_t)(q0 + lane))
                                       : perm_apply(P, (uint32_t)(q0 + lane)))
                       : 0;
-        const unsigned long long mycol =
-            lane < nq ? (unsigned long long)ldg(J.colptr + myf) : 0ull;
+        // the drawn feature's bins of a row: byte myoff of the row in the
+        // row-major copy, or 256 * myoff bytes from the row in column 0
+        uint32_t myoff = (uint32_t)myf;
+        if (!rowmaj)
+            myoff = lane < nq ? (uint32_t)((uint64_t)(ldg(J.colptr + myf) - J.colbase) >> 8) : 0u;
         const int passes = (nq + G - 1) / G;
         // The bin load is unconditional (lanes without a row read row 0, lanes
         // past the drawn features read the first one) so that blocks of loads
         // issue back to back; eval() masks what does not count.
         auto gather = [&](int pass) {
             const int qq = pass * G + seg;
-            if (J.rowmaj) {  // the row's drawn columns share cache lines
-                const int fq = __shfl(myf, qq < nq ? qq : 0);
-                return (int)ldg(J.rowmaj + (size_t)row * J.rm_stride + (uint32_t)fq);
-            }
-            const uint8_t* col = (const uint8_t*)__shfl(mycol, qq < nq ? qq : 0);
-            return (int)ldg(col + row);
+            const uint32_t off = (uint32_t)__shfl((int)myoff, qq < nq ? qq : 0);
+            return (int)ldg(rowmaj ? rowbase + off : rowbase + (uint64_t)off * 256u);
         };
         auto eval = [&](int pass, int raw) {
             const int qq = pass * G + seg;
-            const bool act = qq < nq;
-            const int b = (valid && act) ? raw : 0x7FFF;
-            // left counts of threshold b: the segment's rows j with bin <= b.
-            // Bins by lane permute, counters of row j read from lane j as
-            // scalars; rows j >= len read zero counters.
-            word acc[PK::kWords];
+            const bool act = valid && qq < nq;
+            const int b = act ? raw : 0x7FFF;
+            // acc: the segment's rows j with bin <= b
+            uint32_t acc[WORDS];
+            if (pairs) {
 #pragma unroll
-            for (int w = 0; w < PK::kWords; ++w) acc[w] = 0;
-            for (int j0 = 0; j0 < len; j0 += 8) {
-                int bj[8];
+                for (int w = 0; w < WORDS; ++w) acc[w] = 0;
+                for (int j0 = 0; j0 < len; j0 += 4) {
+                    int bj[4];
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    bj[u] = __builtin_amdgcn_ds_bpermute(abase + ((j0 + u) << 2), b);
-                if constexpr (PK::kWords == 1) {
-                    const uint4 c0 = *reinterpret_cast<const uint4*>(scnt + j0);
-                    const uint4 c1 = *reinterpret_cast<const uint4*>(scnt + j0 + 4);
-                    const uint32_t cj[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+                    for (int u = 0; u < 4; ++u)
+                        bj[u] = __builtin_amdgcn_ds_bpermute(abase + ((j0 + u) << 2), b);
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) acc[0] += bj[u] <= b ? (word)cj[u] : (word)0;
-                    continue;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const bool take = bj[u] <= b;
-#pragma unroll
-                    for (int w = 0; w < PK::kWords; ++w) {
-                        const word o = readlane_w(cv[w], j0 + u);
-                        acc[w] += take ? o : (word)0;
+                    for (int w = 0; w < WORDS; ++w) {
+                        const uint4 c = *reinterpret_cast<const uint4*>(scnt + w * 64 + j0);
+                        acc[w] += bj[0] <= b ? c.x : 0u;
+                        acc[w] += bj[1] <= b ? c.y : 0u;
+                        acc[w] += bj[2] <= b ? c.z : 0u;
+                        acc[w] += bj[3] <= b ? c.w : 0u;
                     }
                 }
-            }
-            Cand c;
-            c.q = q0 + qq;
-            c.f = __shfl(myf, act ? qq : 0);
-            c.b = b;
-            c.pad = 0;
-            uint32_t nl = 0;
-            uint64_t sl = 0, sr = 0;
+            } else {
+                uint4* h4 = reinterpret_cast<uint4*>(hist);
+                const int ng = G;  // 2 or 1 features
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the last pass's reads
 #pragma unroll
-            for (int k = 0; k < KMAX; ++k) {
-                const uint32_t l = PK::field(acc[k / PK::kPer], k);
-                const uint32_t r = cnode[k] - l;
-                nl += l;
-                sl += (uint64_t)l * l;
-                sr += (uint64_t)r * r;
+                for (int u = 0; u < 2 * WORDS; ++u)
+                    if (u < ng * WORDS) h4[u * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                if (act) atomicAdd(&hist[(uint32_t)(seg * WORDS) * 256u + yw * 256u + (uint32_t)b], inc);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+                for (int u = 0; u < 2 * WORDS; ++u) {
+                    if (u < ng * WORDS) {
+                        uint4 v = h4[u * 64 + lane];
+                        v.y += v.x;
+                        v.z += v.y;
+                        v.w += v.z;
+                        const uint32_t ex = wave_incl_sum(v.w) - v.w;
+                        h4[u * 64 + lane] = make_uint4(v.x + ex, v.y + ex, v.z + ex, v.w + ex);
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w)
+                    acc[w] = hist[(uint32_t)(seg * WORDS + w) * 256u + (act ? (uint32_t)b : 0u)];
             }
-            c.nl = nl;
-            c.nr = N - nl;
-            c.sl = sl;
-            c.sr = sr;
-            const bool ok = valid && act && b <= B - 2 && nl > 0 && nl < N;
-            const bool has = lb.nl != 0;
+            const Side8 c = side8<WORDS>(acc, cn, S);
+            const bool ok = act && b <= B - 2 && c.nl < N;  // nl >= the lane's own row
             bool better;
             float qc = -1.0f;
             if (fp32) {
-                qc = ok ? cand_q32(c) : -1.0f;
+                qc = ok ? side_q32(c, N) : -1.0f;
+                bool eq = true, mir = true;  // the same partition, the mirrored one
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w) {
+                    eq = eq && acc[w] == la[w];
+                    mir = mir && acc[w] == cn[w] - la[w];
+                }
                 const bool near = ok && has && qc >= fp32_floor(lq) && lq >= fp32_floor(qc);
                 bool exact = false;
-                if (__ballot(near)) exact = cand_better(c, lb);
+                if (__ballot(near && !eq && !mir))
+                    exact = !eq && !mir && side_better(c, side8<WORDS>(la, cn, S), N);
                 better = ok && (!has || (near ? exact : qc > lq));
             } else {
-                better = ok && (!has || cand_better(c, lb));
+                better = ok && (!has || side_better(c, side8<WORDS>(la, cn, S), N));
             }
             if (better) {
-                lb = c;
+                has = true;
                 lq = qc;
+                ld = q0 + qq;
+                lb = b;
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w) la[w] = acc[w];
             }
         };
         // bins of kPF passes are in flight while the previous kPF are scored
@@ -346,9 +348,70 @@ __device__ void small_node(const ForestDev& F, uint32_t idx, SmallOut& out, uint
             for (int u = 0; u < kPF; ++u) bq[u] = bn[u];
         }
     }
-    const Cand best = fp32 ? wave_best_total_fp32(lb, lb.nl != 0 ? lq : -1.0f)
-                           : wave_best_total_exact(lb);
-    out.alg = (uint64_t)len * (uint64_t)(J.mtry + 6);
+    out.alg = (uint64_t)len * (uint64_t)(mtry + 6);
+    // The winner: with FP32 ranking among the lanes within the margin of the
+    // wave's maximum.  When they all hold one partition (or its mirror) they
+    // tie exactly, and the earliest draw, then the smallest threshold wins;
+    // otherwise they are compared exactly one after the other.
+    bool fin = has;
+    if (fp32) {
+        const float qmax = wave_max_f_dpp(lq);
+        fin = has && lq >= fp32_floor(qmax);
+    }
+    const uint64_t fm = __ballot(fin);
+    int win = -1;
+    uint32_t ba[WORDS];
+    if (fm) {
+        win = (int)__ffsll((unsigned long long)fm) - 1;
+        bool eq = true, mir = true;
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) {
+            ba[w] = readlane_w(la[w], win);
+            eq = eq && la[w] == ba[w];
+            mir = mir && la[w] == cn[w] - ba[w];
+        }
+        if (!__ballot(fin && !eq && !mir)) {
+            const uint32_t dmin = wave_min_u_dpp(fin ? (uint32_t)ld : 0xFFFFFFFFu);
+            const uint32_t bmin =
+                wave_min_u_dpp(fin && (uint32_t)ld == dmin ? (uint32_t)lb : 0xFFFFFFFFu);
+            win = (int)__ffsll((unsigned long long)__ballot(fin && (uint32_t)ld == dmin &&
+                                                            (uint32_t)lb == bmin)) - 1;
+        } else {
+            Side8 cb = side8<WORDS>(ba, cn, S);
+            for (uint64_t m = fm & (fm - 1); m; m &= m - 1) {
+                const int l = (int)__ffsll((unsigned long long)m) - 1;
+                uint32_t a[WORDS];
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w) a[w] = readlane_w(la[w], l);
+                const Side8 c = side8<WORDS>(a, cn, S);
+                const int d0 = __builtin_amdgcn_readlane(ld, win),
+                          d1 = __builtin_amdgcn_readlane(ld, l);
+                const int b0 = __builtin_amdgcn_readlane(lb, win),
+                          b1 = __builtin_amdgcn_readlane(lb, l);
+                if (side_better(c, cb, N) ||
+                    (!side_better(cb, c, N) && (d1 < d0 || (d1 == d0 && b1 < b0)))) {
+                    win = l;
+                    cb = c;
+                }
+            }
+        }
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) ba[w] = readlane_w(la[w], win);
+    }
+    Cand best;
+    best.nl = 0;
+    if (win >= 0) {
+        const Side8 c = side8<WORDS>(ba, cn, S);
+        best.q = __builtin_amdgcn_readlane(ld, win);
+        best.b = __builtin_amdgcn_readlane(lb, win);
+        best.nl = c.nl;
+        best.nr = N - c.nl;
+        best.pad = 0;
+        best.sl = c.sl;
+        best.sr = c.sr;
+        const uint32_t q = (uint32_t)best.q;
+        best.f = (int)(use_tab ? perm_apply_tab(P, tab, q) : perm_apply(P, q));
+    }
     if (best.nl == 0 || !cand_positive(best, S, N)) {  // stays the leaf it was created as
         if (lane == 0) mark_unused_pair(F, out.child);
         return;
@@ -365,19 +428,12 @@ __device__ void small_node(const ForestDev& F, uint32_t idx, SmallOut& out, uint
                                   : nl_rows + (uint32_t)__popcll(vm & ~lm & below);
         rout[pos] = rec;
     }
-    word lc[PK::kWords];
-#pragma unroll
-    for (int w = 0; w < PK::kWords; ++w) {
-        word v = left ? cv[w] : (word)0;
-#pragma unroll
-        for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m);
-        lc[w] = v;
-    }
     if (lane == 0) {
         uint32_t cl[16], cr[16];
+#pragma unroll
         for (int k = 0; k < 16; ++k) {
-            cl[k] = k < KMAX ? PK::field(lc[k / PK::kPer], k) : 0u;
-            cr[k] = (k < KMAX ? cnode[k] : 0u) - cl[k];
+            cl[k] = k < 4 * WORDS ? ba[(k / 4) % WORDS] >> (8 * (k % 4)) & 0xFFu : 0u;
+            cr[k] = (k < 4 * WORDS ? cn[(k / 4) % WORDS] >> (8 * (k % 4)) & 0xFFu : 0u) - cl[k];
         }
         split_node(F, J, tr, id, nd, best, nl_rows, cl, cr, cand_gain_fix(best, S, N),
                    out.child, out.kinds);
@@ -387,8 +443,9 @@ __device__ void small_node(const ForestDev& F, uint32_t idx, SmallOut& out, uint
 // One wavefront per node (grid-stride over the level's small-node list).
 // The small nodes of tree level `level`: all of them (count from the level's
 // counters, grid-stride) or, with an explicit count, list entries
-// [first, first + count).
-template <int KMAX>
+// [first, first + count).  WORDS: counter words of the plan's widest job; a
+// job of fewer classes takes the narrower form.
+template <int WORDS>
 __global__ __launch_bounds__(256) void k_split_small(ForestDev F0, int level, uint32_t first,
                                                      uint32_t count) {
     const ForestDev F = level_view(F0, level);
@@ -396,16 +453,25 @@ __global__ __launch_bounds__(256) void k_split_small(ForestDev F0, int level, ui
         first = 0;
         count = level_small(F0, level);
     }
-    extern __shared__ uint16_t stab[];  // [4][kDrawTab] permutation round tables
-    __shared__ __align__(16) uint32_t s_cnt[4][64];  // per wave: the node's row counters
+    extern __shared__ uint4 lds_raw[];  // [4][small_lds_words(WORDS)]
     const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
+    uint32_t* lds = reinterpret_cast<uint32_t*>(lds_raw) + wave * small_lds_words(WORDS);
     unsigned long long alg = 0;  // statistics
     for (uint32_t li = blockIdx.x * 4u + (uint32_t)wave; li < count; li += gridDim.x * 4u) {
         SmallOut o;
         o.kinds[0] = o.kinds[1] = kLeaf;
-        o.child = 0;
+        o.child = F.next_base + 2u * (first + li);
         o.alg = 0;
-        small_node<KMAX>(F, first + li, o, stab + (size_t)wave * kDrawTab, s_cnt[wave]);
+        const uint32_t id = uniform(F.small_in[first + li]);
+        const NodeDev nd = F.nodes[id];
+        const TreeDev tr = F.trees[nd.tree];
+        JobDev& J = F.jobs[tr.job];
+        if (WORDS == 1 || J.K <= 4)
+            small_node<1>(F, id, nd, tr, J, o, lds);
+        else if (WORDS == 2 || J.K <= 8)
+            small_node<WORDS == 1 ? 1 : 2>(F, id, nd, tr, J, o, lds);
+        else
+            small_node<WORDS>(F, id, nd, tr, J, o, lds);
         // what the children need next; the next level's lists are built from these
         if (lane == 0) F.kinds[first + li] = (uint8_t)(o.kinds[0] | o.kinds[1] << 2);
         alg += o.alg;
@@ -1873,13 +1939,12 @@ void launch_split_small(const ForestDev& F, int level, uint32_t first, uint32_t 
                         uint32_t grid_wg, hipStream_t st) {
     if (!count) return;
     const dim3 grid(grid_wg);
-    const size_t lds = (size_t)4 * kDrawTab * sizeof(uint16_t);  // four waves' round tables
-    switch (F.kmax) {
+    const int words = F.kmax <= 4 ? 1 : (F.kmax <= 8 ? 2 : 4);
+    const size_t lds = (size_t)4 * small_lds_words(words) * sizeof(uint32_t);
+    switch (words) {
+        case 1: hipLaunchKernelGGL(k_split_small<1>, grid, dim3(256), lds, st, F, level, first, count); break;
         case 2: hipLaunchKernelGGL(k_split_small<2>, grid, dim3(256), lds, st, F, level, first, count); break;
-        case 3: hipLaunchKernelGGL(k_split_small<3>, grid, dim3(256), lds, st, F, level, first, count); break;
-        case 4: hipLaunchKernelGGL(k_split_small<4>, grid, dim3(256), lds, st, F, level, first, count); break;
-        case 8: hipLaunchKernelGGL(k_split_small<8>, grid, dim3(256), lds, st, F, level, first, count); break;
-        default: hipLaunchKernelGGL(k_split_small<16>, grid, dim3(256), lds, st, F, level, first, count); break;
+        default: hipLaunchKernelGGL(k_split_small<4>, grid, dim3(256), lds, st, F, level, first, count); break;
     }
 }
 
