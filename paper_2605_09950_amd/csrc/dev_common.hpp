@@ -371,8 +371,9 @@ struct ForestDev {
     NodeDev* nodes;
     uint32_t* cls;        // [node][kmax] weighted class counts
     uint64_t* ngain;      // [node] fixed-point Gini decrease of a split node
-    Cand* cand;           // [slot][npi] best candidate of each histogram item
-    uint32_t* cand_cl;    // [slot][npi][kmax] left class counts of that candidate
+    Cand* cand;           // [slot][npi] regression: best candidate of each histogram item
+    uint32_t* icand;      // [slot][npi][kmax + 2] classification: the record of each item's
+                          // best threshold (put_item)
     uint32_t* feat;       // [slot][mtry_cap] the node's drawn features, draw order
     const uint8_t** fcol; // [slot][mtry_cap] their bin columns
     SlotRec* srec;        // [slot] the large nodes of the level
@@ -396,8 +397,8 @@ struct ForestDev {
                           // class counts fit 8 bits)
     int32_t kmax, parity, split_rank;
     int32_t has_cls, has_reg;  // the plan holds classification / regression jobs
-    int32_t split_k;      // a plan of more than 4 class planes that also holds jobs of at
-                          // most 4 classes: their node-major items take the 4-plane kernel
+    int32_t hist_words;   // LDS words per bin of an item's histogram: two classes to a word
+                          // while no node weighs 65536 rows, else one per class plane
     int32_t npi;          // histogram items per large node (draw positions / fw)
     int32_t fw;           // draws per histogram item
     uint32_t small_rows;  // a node takes the wave path only up to this many distinct rows

@@ -47,7 +47,7 @@ void launch_draws(const ForestDev&, int, uint32_t, hipStream_t);
 void launch_lists(const ForestDev&, int, uint32_t, hipStream_t);
 void launch_col_sort(const ForestDev&, int, uint32_t, hipStream_t);
 size_t hist_col_lds(int, int, uint32_t);
-hipError_t prepare_hist_col(int, size_t);
+hipError_t prepare_hist_col(int, int, size_t);
 void launch_hist_col(const ForestDev&, int, uint32_t, int, uint32_t, hipStream_t);
 // k_importance.hip
 void launch_tree_totals(JobDev*, const TreeDev*, int, uint64_t*, hipStream_t);
@@ -368,7 +368,7 @@ struct JobPlan {
 
 struct Plan {
     std::vector<JobPlan> jp;
-    size_t keys, jobs, trees, tree_base, flags, nodes, cls, ngain, small0, small1, cand, cand_cl,
+    size_t keys, jobs, trees, tree_base, flags, nodes, cls, ngain, small0, small1, cand, icand,
         feat, fcol, srec, kinds, chunk_sums, slot0, slot1, ctrs, alg, tot;
     size_t fcnt = 0, fpos = 0, fitems = 0, units = 0, gcolq = 0;
     size_t seed_med = 0, seed_dec = 0;  // multi-seed aggregate [p]
@@ -380,7 +380,7 @@ struct Plan {
     // column-major histogram path: levels >= col_level (col_level >= max_D: none)
     int col_level = kColNever, col_waves = 0;
     bool has_cls = false, has_reg = false;
-    bool has_small_k = false;  // a classification job of at most 4 classes
+    int hist_words = 1;        // LDS words per bin of a histogram item
     uint32_t n_gcol = 0, unit_cap = 0, gq_max = 0;
     int64_t max_n = 0;
     uint32_t boot_chunk = 0;  // rows per workgroup of the LDS bootstrap counts (0: atomics)
@@ -481,9 +481,10 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     for (const Spec& s : specs) {
         any_reg |= s.yr != nullptr;
         pl.has_cls |= s.yr == nullptr;
-        pl.has_small_k |= s.yr == nullptr && s.K <= 4;
     }
     pl.has_reg = any_reg;
+    // a root weighs n rows: 16-bit class counts hold every node below 65536
+    pl.hist_words = pl.max_n < 65536 ? (pl.kmax + 1) / 2 : pl.kmax;
     int col_level = any_reg ? kColNever : o.col_level;
     if (col_level == 0) {
         size_t widest = 0;
@@ -491,7 +492,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         col_level = widest > kColAutoBytes ? kColLevelAuto : kColNever;
     }
     if (o.form == BORUTA_FORM_BATCHED && col_level < pl.max_D) {
-        const size_t per_wave = (size_t)pl.kmax * 256 * 4, col = (size_t)pl.gq_max * 16;
+        const size_t per_wave = (size_t)pl.hist_words * 256 * 4, col = (size_t)pl.gq_max * 16;
         if (col + 2 * per_wave <= kLdsPerWorkgroup) {
             pl.col_level = col_level;
             pl.col_waves = (int)std::min<size_t>(kColWavesMax, (kLdsPerWorkgroup - col) / per_wave);
@@ -528,8 +529,8 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     pl.ngain = r.take((size_t)pl.node_cap * 8);
     pl.small0 = r.take((size_t)pl.small_cap * 4);
     pl.small1 = r.take((size_t)pl.small_cap * 4);
-    pl.cand = r.take((size_t)pl.slot_cap * pl.npi * sizeof(Cand));
-    pl.cand_cl = r.take((size_t)pl.slot_cap * pl.npi * pl.kmax * 4);
+    pl.cand = any_reg ? r.take((size_t)pl.slot_cap * pl.npi * sizeof(Cand)) : 0;
+    pl.icand = pl.has_cls ? r.take((size_t)pl.slot_cap * pl.npi * (pl.kmax + 2) * 4) : 0;
     pl.feat = r.take((size_t)pl.slot_cap * pl.mtry_cap * 4);
     pl.fcol = r.take((size_t)pl.slot_cap * pl.mtry_cap * 8);
     pl.srec = r.take((size_t)pl.slot_cap * sizeof(SlotRec));
@@ -883,8 +884,8 @@ void Engine::setup(std::vector<int>& status) {
         int dev = 0, lds_max = 0;
         HIPC(hipGetDevice(&dev));
         HIPC(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-        const size_t lds = hist_col_lds(pl.kmax, pl.col_waves, pl.gq_max);
-        if ((size_t)lds_max < lds || prepare_hist_col(pl.kmax, lds) != hipSuccess) {
+        const size_t lds = hist_col_lds(pl.hist_words, pl.col_waves, pl.gq_max);
+        if ((size_t)lds_max < lds || prepare_hist_col(pl.kmax, pl.hist_words, lds) != hipSuccess) {
             (void)hipGetLastError();
             pl.col_level = kColNever;  // node-major at every level (same item layout)
         } else {
@@ -912,7 +913,7 @@ ForestDev Engine::forest() const {
     F.cls = at<uint32_t>(pl.cls);
     F.ngain = at<uint64_t>(pl.ngain);
     F.cand = at<Cand>(pl.cand);
-    F.cand_cl = at<uint32_t>(pl.cand_cl);
+    F.icand = at<uint32_t>(pl.icand);
     F.feat = at<uint32_t>(pl.feat);
     F.fcol = at<const uint8_t*>(pl.fcol);
     F.srec = at<SlotRec>(pl.srec);
@@ -948,7 +949,7 @@ ForestDev Engine::forest() const {
     F.split_rank = O.split_rank;
     F.has_cls = pl.has_cls ? 1 : 0;
     F.has_reg = pl.has_reg ? 1 : 0;
-    F.split_k = pl.kmax > 4 && pl.has_small_k ? 1 : 0;
+    F.hist_words = pl.hist_words;
     F.small_ncap = 256u;  // the wave path packs class counters in 8-bit fields
     return F;
 }

@@ -218,28 +218,48 @@ __device__ __forceinline__ Cand wave_best_total_fp32(const Cand& c, float q32) {
     return wave_best_total_exact(f);
 }
 
-// Packed class counters: nodes of weight N < 256 hold a side's class counts as
-// 8-bit fields, four classes to a 32-bit word.  The dot product of bytes
-// (full rate) gives the exact integers of a split: for left counts l and node
-// counts c, N_L = sum l, S_L = sum l^2 and, from sum c l, S_R = sum (c - l)^2
-// = S - 2 sum c l + S_L.  All stay below 2^16, so they are exact in FP32 too.
-struct Side8 {
+// Packed class counters: a side's class counts as fields of FB bits -- 8 for
+// nodes of weight N < 256 (four classes to a 32-bit word), 16 for N < 65536
+// (two).  The dot product of bytes or halves (full rate) gives the exact
+// integers of a split: for left counts l and node counts c, N_L = sum l,
+// S_L = sum l^2 and, from sum c l, S_R = sum (c - l)^2 = S - 2 sum c l + S_L
+// (all below 2^32; modulo 2^32 on the way).
+struct Side {
     uint32_t nl, sl, sr;
 };
 
 __device__ __forceinline__ uint32_t dot4(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_udot4(a, b, c, false);
 }
+__device__ __forceinline__ uint32_t dot2(uint32_t a, uint32_t b, uint32_t c) {
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    return __builtin_amdgcn_udot2(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b), c,
+                                  false);
+}
+template <int FB>
+__device__ __forceinline__ uint32_t dotf(uint32_t a, uint32_t b, uint32_t c) {
+    if constexpr (FB == 8)
+        return dot4(a, b, c);
+    else
+        return dot2(a, b, c);
+}
 
-template <int WORDS>
-__device__ __forceinline__ Side8 side8(const uint32_t* l, const uint32_t* c, uint32_t S) {
-    Side8 s;
+// Field k of a packed side.
+template <int FB>
+__device__ __forceinline__ uint32_t pk_field(const uint32_t* l, int k) {
+    constexpr int P = 32 / FB;
+    return l[k / P] >> (FB * (k % P)) & ((1u << FB) - 1u);
+}
+
+template <int WORDS, int FB>
+__device__ __forceinline__ Side side_of(const uint32_t* l, const uint32_t* c, uint32_t S) {
+    Side s;
     uint32_t nl = 0, sl = 0, cl = 0;
 #pragma unroll
     for (int w = 0; w < WORDS; ++w) {
-        nl = dot4(l[w], 0x01010101u, nl);
-        sl = dot4(l[w], l[w], sl);
-        cl = dot4(l[w], c[w], cl);
+        nl = dotf<FB>(l[w], FB == 8 ? 0x01010101u : 0x00010001u, nl);
+        sl = dotf<FB>(l[w], l[w], sl);
+        cl = dotf<FB>(l[w], c[w], cl);
     }
     s.nl = nl;
     s.sl = sl;
@@ -247,18 +267,106 @@ __device__ __forceinline__ Side8 side8(const uint32_t* l, const uint32_t* c, uin
     return s;
 }
 
-// FP32 ranking score (both sides non-empty): the integers convert exactly,
-// so the relative error is within 4u (reciprocal 2u, product and sum u each).
-__device__ __forceinline__ float side_q32(const Side8& s, uint32_t N) {
+// FP32 ranking score (both sides non-empty): relative error within 5u, as
+// cand_q32 (the integers convert exactly for N < 256).
+__device__ __forceinline__ float side_q32(const Side& s, uint32_t N) {
     return (float)s.sl * __builtin_amdgcn_rcpf((float)s.nl) +
            (float)s.sr * __builtin_amdgcn_rcpf((float)(N - s.nl));
 }
 
-// Q_a > Q_b exactly (numerators below 2^25, denominators below 2^14).
-__device__ __forceinline__ bool side_better(const Side8& a, const Side8& b, uint32_t N) {
-    const uint32_t na = a.sl * (N - a.nl) + a.sr * a.nl, da = a.nl * (N - a.nl);
-    const uint32_t nb = b.sl * (N - b.nl) + b.sr * b.nl, db = b.nl * (N - b.nl);
-    return (uint64_t)na * db > (uint64_t)nb * da;
+// Q as an exact fraction: numerator S_L N_R + S_R N_L (below 2^25 for N < 256,
+// 2^49 for N < 65536) over N_L N_R (below 2^14, 2^30); nd = 0: no candidate.
+struct Frac {
+    uint64_t nn;
+    uint32_t nd;
+};
+__device__ __forceinline__ Frac side_frac(const Side& s, uint32_t N) {
+    const uint32_t nr = N - s.nl;
+    return Frac{(uint64_t)s.sl * nr + (uint64_t)s.sr * s.nl, s.nl * nr};
+}
+template <int FB>
+__device__ __forceinline__ bool frac_better(const Frac& a, const Frac& b) {
+    if constexpr (FB == 8)
+        return a.nn * b.nd > b.nn * a.nd;
+    else
+        return (u128)a.nn * b.nd > (u128)b.nn * a.nd;
+}
+template <int FB>
+__device__ __forceinline__ bool side_better(const Side& a, const Side& b, uint32_t N) {
+    return frac_better<FB>(side_frac(a, N), side_frac(b, N));
+}
+
+// A histogram item's best threshold: FP32 score (negative: none) and bin.
+struct ItemBest {
+    float q;
+    int b;
+};
+
+// Best threshold over the wave's candidates of one feature, NS per lane in
+// any order (score q, threshold b, split side; ok: valid).
+// With FP32 ranking the candidates within the margin of the wave's maximum are
+// compared exactly, and not at all when they are one threshold; with exact
+// ranking all are.  Ties keep the smaller threshold.
+template <int FB, int NS>
+__device__ __forceinline__ ItemBest pick_threshold(const float* q, const int* b, const Side* sd,
+                                                   const bool* ok, uint32_t N, int split_rank) {
+    bool fin[NS];
+    ItemBest r;
+    r.q = -1.0f;
+    r.b = 0;
+    if (split_rank) {
+        float q1 = q[0];
+#pragma unroll
+        for (int u = 1; u < NS; ++u) q1 = fmaxf(q1, q[u]);
+        r.q = wave_max_f_dpp(q1);
+        if (r.q < 0.0f) return r;
+        const float fl = fp32_floor(r.q);
+        bool any = false;
+        int bf = 0;
+#pragma unroll
+        for (int u = NS - 1; u >= 0; --u) {
+            fin[u] = q[u] >= fl;
+            any |= fin[u];
+            bf = fin[u] ? b[u] : bf;
+        }
+        r.b = __builtin_amdgcn_readlane(bf, (int)__ffsll((unsigned long long)__ballot(any)) - 1);
+        bool other = false;
+#pragma unroll
+        for (int u = 0; u < NS; ++u) other |= fin[u] && b[u] != r.b;
+        if (!__ballot(other)) return r;
+    } else {
+#pragma unroll
+        for (int u = 0; u < NS; ++u) fin[u] = ok[u];
+    }
+    Frac best{0, 0};
+    int bb = 0x7FFFFFFF;
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        if (fin[u]) {
+            const Frac c = side_frac(sd[u], N);
+            if (best.nd == 0 || frac_better<FB>(c, best) ||
+                (b[u] < bb && !frac_better<FB>(best, c))) {
+                best = c;
+                bb = b[u];
+            }
+        }
+    }
+#pragma unroll 1
+    for (int m = 1; m < 64; m <<= 1) {  // seldom run with FP32 ranking: kept small
+        Frac o;
+        o.nn = __shfl_xor(best.nn, m);
+        o.nd = __shfl_xor(best.nd, m);
+        const int ob = __shfl_xor(bb, m);
+        const bool take = o.nd != 0 && (best.nd == 0 || frac_better<FB>(o, best) ||
+                                        (ob < bb && !frac_better<FB>(best, o)));
+        if (take) {
+            best = o;
+            bb = ob;
+        }
+    }
+    r.b = (int)uniform((uint32_t)bb);
+    if (!split_rank) r.q = uniform(best.nd) ? 1.0f : -1.0f;
+    return r;
 }
 
 enum : int { kLeaf = 0, kSmall = 1, kLarge = 2 };

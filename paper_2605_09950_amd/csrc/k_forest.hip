@@ -25,6 +25,7 @@
 // Q = S_L/N_L + S_R/N_R over drawn features and thresholds "bin <= b",
 // exact rational comparison, ties to the earlier draw then the smaller b;
 // split only on a strictly positive decrease Q - S/N.
+#include <algorithm>
 #include <type_traits>
 
 #include "forest_dev.hpp"
@@ -301,12 +302,13 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
                 for (int w = 0; w < WORDS; ++w)
                     acc[w] = hist[(uint32_t)(seg * WORDS + w) * 256u + (act ? (uint32_t)b : 0u)];
             }
-            const Side8 c = side8<WORDS>(acc, cn, S);
+            const Side c = side_of<WORDS, 8>(acc, cn, S);
             const bool ok = act && b <= B - 2 && c.nl < N;  // nl >= the lane's own row
             bool better;
             float qc = -1.0f;
             if (fp32) {
-                qc = ok ? side_q32(c, N) : -1.0f;
+                const float qu = side_q32(c, N);  // unconditional: a select, no branch
+                qc = ok ? qu : -1.0f;
                 bool eq = true, mir = true;  // the same partition, the mirrored one
 #pragma unroll
                 for (int w = 0; w < WORDS; ++w) {
@@ -316,10 +318,10 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
                 const bool near = ok && has && qc >= fp32_floor(lq) && lq >= fp32_floor(qc);
                 bool exact = false;
                 if (__ballot(near && !eq && !mir))
-                    exact = !eq && !mir && side_better(c, side8<WORDS>(la, cn, S), N);
+                    exact = !eq && !mir && side_better<8>(c, side_of<WORDS, 8>(la, cn, S), N);
                 better = ok && (!has || (near ? exact : qc > lq));
             } else {
-                better = ok && (!has || side_better(c, side8<WORDS>(la, cn, S), N));
+                better = ok && (!has || side_better<8>(c, side_of<WORDS, 8>(la, cn, S), N));
             }
             if (better) {
                 has = true;
@@ -377,19 +379,19 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
             win = (int)__ffsll((unsigned long long)__ballot(fin && (uint32_t)ld == dmin &&
                                                             (uint32_t)lb == bmin)) - 1;
         } else {
-            Side8 cb = side8<WORDS>(ba, cn, S);
+            Side cb = side_of<WORDS, 8>(ba, cn, S);
             for (uint64_t m = fm & (fm - 1); m; m &= m - 1) {
                 const int l = (int)__ffsll((unsigned long long)m) - 1;
                 uint32_t a[WORDS];
 #pragma unroll
                 for (int w = 0; w < WORDS; ++w) a[w] = readlane_w(la[w], l);
-                const Side8 c = side8<WORDS>(a, cn, S);
+                const Side c = side_of<WORDS, 8>(a, cn, S);
                 const int d0 = __builtin_amdgcn_readlane(ld, win),
                           d1 = __builtin_amdgcn_readlane(ld, l);
                 const int b0 = __builtin_amdgcn_readlane(lb, win),
                           b1 = __builtin_amdgcn_readlane(lb, l);
-                if (side_better(c, cb, N) ||
-                    (!side_better(cb, c, N) && (d1 < d0 || (d1 == d0 && b1 < b0)))) {
+                if (side_better<8>(c, cb, N) ||
+                    (!side_better<8>(cb, c, N) && (d1 < d0 || (d1 == d0 && b1 < b0)))) {
                     win = l;
                     cb = c;
                 }
@@ -401,7 +403,7 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
     Cand best;
     best.nl = 0;
     if (win >= 0) {
-        const Side8 c = side8<WORDS>(ba, cn, S);
+        const Side c = side_of<WORDS, 8>(ba, cn, S);
         best.q = __builtin_amdgcn_readlane(ld, win);
         best.b = __builtin_amdgcn_readlane(lb, win);
         best.nl = c.nl;
@@ -432,8 +434,8 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
         uint32_t cl[16], cr[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            cl[k] = k < 4 * WORDS ? ba[(k / 4) % WORDS] >> (8 * (k % 4)) & 0xFFu : 0u;
-            cr[k] = (k < 4 * WORDS ? cn[(k / 4) % WORDS] >> (8 * (k % 4)) & 0xFFu : 0u) - cl[k];
+            cl[k] = k < 4 * WORDS ? pk_field<8>(ba, k % (4 * WORDS)) : 0u;
+            cr[k] = (k < 4 * WORDS ? pk_field<8>(cn, k % (4 * WORDS)) : 0u) - cl[k];
         }
         split_node(F, J, tr, id, nd, best, nl_rows, cl, cr, cand_gain_fix(best, S, N),
                    out.child, out.kinds);
@@ -661,25 +663,8 @@ __device__ Cand feature_best_compact(uint32_t* h, int B, int q, int f, const uin
         hv[k][3] = v.w;
         a[k] = v.x + v.y + v.z + v.w;
     }
-    bool packed = false;
-    if constexpr (KMAX == 4) {
-        if (N < 65536u) {
-            // every prefix of a class count is below N: two classes per word,
-            // one wave scan per pair (measured faster for four classes only)
 #pragma unroll
-            for (int k = 0; k < 4; k += 2) {
-                const uint32_t pk = a[k] | (a[k + 1] << 16);
-                const uint32_t ex = wave_incl_sum(pk) - pk;
-                excl[k] = ex & 0xFFFFu;
-                excl[k + 1] = ex >> 16;
-            }
-            packed = true;
-        }
-    }
-    if (!packed) {
-#pragma unroll
-        for (int k = 0; k < KMAX; ++k) excl[k] = wave_incl_sum(a[k]) - a[k];
-    }
+    for (int k = 0; k < KMAX; ++k) excl[k] = wave_incl_sum(a[k]) - a[k];
     // the lane's thresholds worth scoring: a non-empty bin below B - 1 with
     // rows on both sides (prefix counts are rebuilt in the writing pass)
     uint32_t okm = 0, cnt = 0;
@@ -830,6 +815,246 @@ __device__ Cand feature_best_compact(uint32_t* h, int B, int q, int f, const uin
     for (int k = 0; k < KMAX; ++k)
         cl_out[k] = (uint32_t)__builtin_amdgcn_readlane((int)lcl[k], src);
     return w;
+}
+
+// ---------------------------------------------------------------------------
+// Best threshold of one feature from a packed LDS histogram h[WORDS][256]:
+// lane l owns bins 4l .. 4l+3, one 16-byte read per word, and a wave scan adds
+// up the packed prefix counts.  Two forms:
+//   * rows (nodes of at most 128 rows): the prefix counts go back to LDS and
+//     every row scores the threshold at its own bin (rows lane and lane + 64,
+//     bins b0 and b1): one or two scores per lane, however the rows spread
+//     over bins;
+//   * bins: every lane scores its four bins where they hold rows.
+// The scan is what an item of a small node costs (an unpacked one of four
+// classes takes four prefix scans and two passes over the bins): against one
+// word per class k_hist_tile went from 82 to 62 us a launch at n = 10,000, 3
+// classes, and from 353 to 225 us at 2,000 x 20,000, 2 classes.  l receives the
+// packed left counts of the best threshold.
+template <int WORDS, int FB, int NS>
+__device__ __forceinline__ ItemBest scan_rows(uint32_t* h, uint32_t len, int b0, int b1, int B,
+                                              const uint32_t* cn, uint32_t S, uint32_t N,
+                                              int split_rank, uint32_t* l) {
+    const int lane = threadIdx.x & 63;
+    int rb[NS];
+    rb[0] = b0;
+    if constexpr (NS > 1) rb[1] = b1;
+    uint4* h4 = reinterpret_cast<uint4*>(h);
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) {
+        uint4 v = h4[w * 64 + lane];
+        v.y += v.x;
+        v.z += v.y;
+        v.w += v.z;
+        const uint32_t ex = wave_incl_sum(v.w) - v.w;
+        h4[w * 64 + lane] = make_uint4(v.x + ex, v.y + ex, v.z + ex, v.w + ex);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    float q[NS];
+    Side sd[NS];
+    bool ok[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        uint32_t a[WORDS];
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) a[w] = h[w * 256 + rb[u]];
+        sd[u] = side_of<WORDS, FB>(a, cn, S);
+        // nl >= the row's own weight
+        ok[u] = (uint32_t)(lane + 64 * u) < len && rb[u] <= B - 2 && sd[u].nl < N;
+        const float qu = side_q32(sd[u], N);  // unconditional: a select, no branch
+        q[u] = ok[u] ? qu : -1.0f;
+    }
+    const ItemBest r = pick_threshold<FB, NS>(q, rb, sd, ok, N, split_rank);
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) l[w] = uniform(h[w * 256 + r.b]);
+    return r;
+}
+
+template <int WORDS, int FB>
+__device__ __forceinline__ ItemBest scan_bins(const uint32_t* h, int B, const uint32_t* cn,
+                                              uint32_t S, uint32_t N, int split_rank,
+                                              uint32_t* l) {
+    const int lane = threadIdx.x & 63;
+    const uint4* h4 = reinterpret_cast<const uint4*>(h);
+    uint32_t p[4][WORDS];
+    uint32_t own[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) {
+        const uint4 v = h4[w * 64 + lane];
+        own[0] |= v.x;
+        own[1] |= v.y;
+        own[2] |= v.z;
+        own[3] |= v.w;
+        p[0][w] = v.x;
+        p[1][w] = p[0][w] + v.y;
+        p[2][w] = p[1][w] + v.z;
+        p[3][w] = p[2][w] + v.w;
+        const uint32_t ex = wave_incl_sum(p[3][w]) - p[3][w];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) p[u][w] += ex;
+    }
+    float q[4];
+    int b[4];
+    Side sd[4];
+    bool ok[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        b[u] = lane * 4 + u;
+        sd[u] = side_of<WORDS, FB>(p[u], cn, S);
+        // an empty bin repeats the previous threshold's partition
+        ok[u] = own[u] != 0 && b[u] <= B - 2 && sd[u].nl < N;
+        const float qu = side_q32(sd[u], N);  // unconditional: a select, no branch
+        q[u] = ok[u] ? qu : -1.0f;
+    }
+    const ItemBest r = pick_threshold<FB, 4>(q, b, sd, ok, N, split_rank);
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) {
+        uint32_t v = p[0][w];
+#pragma unroll
+        for (int u = 1; u < 4; ++u) v = b[u] == r.b ? p[u][w] : v;
+        l[w] = readlane_w(v, r.b >> 2);
+    }
+    return r;
+}
+
+// How the histogram items of a node hold their class counts: 8-bit fields
+// below a weight of 256, 16-bit fields below 65536, else one word per class.
+// Two-class nodes take 16-bit fields (one word either way).  A row of class y
+// and weight w adds w << (y & fm) * fb to word y >> fs of its bin; words: what
+// the scan of K classes reads.
+struct CountForm {
+    uint32_t fb, fs, fm, words;
+};
+template <int KMAX>
+__device__ __forceinline__ CountForm count_form(uint32_t N, uint32_t K) {
+    if (KMAX > 2 && N < 256u) return CountForm{8u, 2u, 3u, K <= 4u ? 1u : (K <= 8u ? 2u : 4u)};
+    if (N < 65536u)
+        return CountForm{16u, 1u, 1u, KMAX == 2 ? 1u : (K <= 4u ? 2u : (K <= 8u ? 4u : 8u))};
+    return CountForm{0u, 0u, 0u, (uint32_t)KMAX};
+}
+__device__ __forceinline__ void count_row(uint32_t* h, const CountForm& cf, uint32_t y,
+                                          uint32_t b, uint32_t w) {
+    atomicAdd(&h[(y >> cf.fs) * 256u + b], w << ((y & cf.fm) * cf.fb));
+}
+
+// Node counts packed in WORDS words of FB-bit fields, and S = sum c^2.
+template <int KMAX, int WORDS, int FB>
+__device__ __forceinline__ uint32_t pack_counts(const uint32_t* c, uint32_t* cn) {
+    constexpr int P = 32 / FB;
+    uint32_t S = 0;
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) {
+        cn[w] = 0;
+#pragma unroll
+        for (int k = 0; k < P; ++k)
+            if (w * P + k < KMAX) cn[w] |= c[w * P + k] << (FB * k);
+        S = dotf<FB>(cn[w], cn[w], S);
+    }
+    return S;
+}
+
+// One feature's best threshold from its histogram in form cf: through the
+// packed scans, or one word per class above a weight of 65535.  cnode: the
+// node's class counts [KMAX] (zero past K); cl: the best threshold's left
+// class counts [KMAX].  b0, b1: the bins of rows lane and lane + 64 (nodes of
+// at most 128 rows; those of 16-bit counts are larger but for odd weights).
+template <int KMAX, int WORDS, int FB>
+__device__ __forceinline__ ItemBest scan_packed(uint32_t* h, uint32_t len, int b0, int b1, int B,
+                                                const uint32_t* cnode, uint32_t N,
+                                                int split_rank, uint32_t* cl) {
+    uint32_t cn[WORDS], l[WORDS];
+    const uint32_t S = pack_counts<KMAX, WORDS, FB>(cnode, cn);
+    ItemBest r;
+    if ((FB == 8 || KMAX == 2) && len <= 64u)
+        r = scan_rows<WORDS, FB, 1>(h, len, b0, b1, B, cn, S, N, split_rank, l);
+    else if ((FB == 8 || KMAX == 2) && len <= 128u)
+        r = scan_rows<WORDS, FB, 2>(h, len, b0, b1, B, cn, S, N, split_rank, l);
+    else
+        r = scan_bins<WORDS, FB>(h, B, cn, S, N, split_rank, l);
+    constexpr int P = 32 / FB;
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) cl[k] = k < P * WORDS ? pk_field<FB>(l, k % (P * WORDS)) : 0u;
+    return r;
+}
+
+// BIG: the plan may hold nodes of weight 65536 and more.
+template <int KMAX, bool BIG>
+__device__ __forceinline__ ItemBest scan_item(uint32_t* h, const CountForm& cf, uint32_t K,
+                                              uint32_t len, int b0, int b1, int B,
+                                              const uint32_t* cnode, uint32_t N, int split_rank,
+                                              uint32_t* cl) {
+    if (KMAX > 2 && cf.fb == 8u) {
+        if (KMAX <= 4 || K <= 4u)
+            return scan_packed<KMAX, 1, 8>(h, len, b0, b1, B, cnode, N, split_rank, cl);
+        if (KMAX <= 8 || K <= 8u)
+            return scan_packed<KMAX, 2, 8>(h, len, b0, b1, B, cnode, N, split_rank, cl);
+        return scan_packed<KMAX, 4, 8>(h, len, b0, b1, B, cnode, N, split_rank, cl);
+    }
+    if (!BIG || cf.fb == 16u) {
+        if (KMAX <= 2)
+            return scan_packed<KMAX, 1, 16>(h, len, b0, b1, B, cnode, N, split_rank, cl);
+        if (KMAX <= 4 || K <= 4u)
+            return scan_packed<KMAX, 2, 16>(h, len, b0, b1, B, cnode, N, split_rank, cl);
+        if (KMAX <= 8 || K <= 8u)
+            return scan_packed<KMAX, 4, 16>(h, len, b0, b1, B, cnode, N, split_rank, cl);
+        return scan_packed<KMAX, 8, 16>(h, len, b0, b1, B, cnode, N, split_rank, cl);
+    }
+    ItemBest r;
+    Cand c;
+    if constexpr (KMAX <= 4) {
+        c = feature_best_compact<KMAX>(h, B, 0, 0, cnode, N, split_rank, cl);
+    } else {
+        const int lane = threadIdx.x & 63;
+        c = feature_best<KMAX>(h, B, 0, 0, cnode, N, split_rank);
+        const int bt = c.nl != 0 ? c.b : -1;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            const uint4 v4 = *reinterpret_cast<const uint4*>(h + k * 256 + lane * 4);
+            const int bl = lane * 4;
+            const uint32_t a = (bl <= bt ? v4.x : 0u) + (bl + 1 <= bt ? v4.y : 0u) +
+                               (bl + 2 <= bt ? v4.z : 0u) + (bl + 3 <= bt ? v4.w : 0u);
+            cl[k] = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(a), 63);
+        }
+    }
+    r.q = c.nl != 0 ? cand_q32(c) : -1.0f;
+    r.b = c.b;
+    return r;
+}
+
+// Record of a classification item in F.icand, kmax + 2 words: the FP32 score
+// of its best threshold (negative: none), the threshold bin | the draw's
+// place in the item << 8, and the left class counts.
+template <int KMAX>
+__device__ __forceinline__ void put_item(const ForestDev& F, uint32_t item, const ItemBest& r,
+                                         uint32_t draw, const uint32_t* cl) {
+    const int lane = threadIdx.x & 63;
+    uint32_t v = lane == 0 ? __float_as_uint(r.q) : (uint32_t)r.b | draw << 8;
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) v = lane == k + 2 ? cl[k] : v;
+    if (lane < KMAX + 2) F.icand[(size_t)item * (KMAX + 2) + lane] = v;
+}
+
+// Exact form of an item record: the split of its left counts.
+template <int KMAX>
+__device__ __forceinline__ Cand cand_of(const uint32_t* rec, const uint32_t* cnode, uint32_t N) {
+    Cand c;
+    c.q = c.f = 0;
+    c.pad = 0;
+    c.b = (int)(rec[1] & 0xFFu);
+    uint32_t nl = 0;
+    uint64_t sl = 0, sr = 0;
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) {
+        const uint32_t l = rec[2 + k], r = cnode[k] - l;
+        nl += l;
+        sl += (uint64_t)l * l;
+        sr += (uint64_t)r * r;
+    }
+    c.nl = nl;
+    c.nr = N - nl;
+    c.sl = sl;
+    c.sr = sr;
+    return c;
 }
 
 // ---------------------------------------------------------------------------
@@ -1151,7 +1376,7 @@ struct ItemWalk {
 
 // Regression nodes of the node-major levels: one wavefront per (node, F.fw
 // consecutive draws) item, the histograms and scan of reg_item in the wave's
-// LDS region (F.fw * F.kmax * 256 words, at least 768).  Items of
+// LDS region (F.fw * F.hist_words * 256 words, at least 768).  Items of
 // classification nodes are left to k_hist_tile, which in turn skips these:
 // the regression item's registers and code stay out of the classification
 // kernel.
@@ -1161,7 +1386,8 @@ __global__ __launch_bounds__(256) void k_hist_reg(ForestDev F, int level, uint32
     extern __shared__ uint4 lds_raw[];
     const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
     const int fw = F.fw;
-    uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw) + (size_t)wave * fw * F.kmax * 256;
+    uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw) +
+                     (size_t)wave * max(fw * F.hist_words * 256, 768);
     const ItemWalk wk(F, level, first, count, (uint32_t)wave);
     unsigned long long alg = 0;
     for (uint32_t cur = wk.r; cur < wk.m_end; cur += wk.R) {
@@ -1192,15 +1418,15 @@ __global__ __launch_bounds__(256) void k_hist_reg(ForestDev F, int level, uint32
                   alg);
 }
 
-template <int KMAX, int FW, int RB>
+template <int KMAX, int FW, int RB, bool BIG>
 __global__ __launch_bounds__(256) void k_hist_tile(ForestDev F, int level, uint32_t first,
                                                    uint32_t count) {
     // RB rows per lane per batch: RB record loads and RB * FW bin gathers in
     // flight (a launch tuning choice; every RB gives the same histograms)
-    constexpr int WORDS = FW * KMAX * 256;
     extern __shared__ uint4 lds_raw[];
     const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw) + wave * WORDS;
+    const uint32_t hw = (uint32_t)F.hist_words;  // LDS words per bin and feature
+    uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw) + (size_t)wave * FW * hw * 256u;
     const ItemWalk wk(F, level, first, count, (uint32_t)wave);
     const uint32_t npi = wk.npi;
     unsigned long long alg = 0;
@@ -1209,106 +1435,104 @@ __global__ __launch_bounds__(256) void k_hist_tile(ForestDev F, int level, uint3
         const uint32_t slot = item / npi, j = item % npi;
         const SlotRec& sr = F.srec[slot];
         if (sr.reg) continue;  // a regression node: k_hist_reg
-        // with split_k, jobs of at most 4 classes take the 4-plane instance
-        if (F.split_k && ((sr.K <= 4u) != (KMAX <= 4))) continue;
         const int q0 = (int)j * FW;
         const int mtry = (int)sr.mtry;
         if (q0 >= mtry) continue;  // the job draws fewer features this iteration
         const int nf = min(FW, mtry - q0);
-        const uint32_t* drawn = F.feat + (size_t)slot * F.mtry_cap + q0;
         const uint8_t* const* dcol = F.fcol + (size_t)slot * F.mtry_cap + q0;
-        int fq[FW];
         const uint8_t* col[FW];
 #pragma unroll
-        for (int u = 0; u < FW; ++u) {
-            fq[u] = (int)drawn[u < nf ? u : 0];
-            col[u] = dcol[u < nf ? u : 0];
-        }
+        for (int u = 0; u < FW; ++u) col[u] = dcol[u < nf ? u : 0];
+        const uint32_t N = sr.n, K = sr.K;
+        const CountForm cf = count_form<KMAX>(N, K);
 #pragma unroll
-        for (int i = 0; i < WORDS / 256; ++i)
-            reinterpret_cast<uint4*>(hist)[i * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
+        for (int v = 0; v < FW; ++v)
+            for (uint32_t i = 0; i < cf.words; ++i)
+                reinterpret_cast<uint4*>(hist + v * hw * 256u)[i * 64u + lane] =
+                    make_uint4(0u, 0u, 0u, 0u);
         const uint64_t* recs = sr.recs;
         const uint32_t len = sr.len;
-        // (loading the next batch's records ahead of this batch's gathers was
-        // measured slower here: the other waves of the SIMD hide the latency)
-        for (uint32_t i0 = 0; i0 < len; i0 += 64 * RB) {
-            uint64_t r[RB];
+        int b0[FW], b1[FW];  // bins of rows lane and lane + 64 (nodes of at most 128 rows)
+        // One batch of NB rows per lane: all record loads, then all bin
+        // gathers, then the counts.  (Loading the next batch's records ahead
+        // of this batch's gathers was measured slower here: the other waves
+        // of the SIMD hide the latency.)
+        auto batch = [&](uint32_t i0, auto nb) {
+            constexpr int NB = decltype(nb)::value;
+            uint64_t r[NB];
 #pragma unroll
-            for (int u = 0; u < RB; ++u) {
-                const uint32_t i = i0 + u * 64 + lane;
-                r[u] = i < len ? ldg(recs + i) : 0ull;
-            }
-            uint32_t b[RB][FW];
+            for (int u = 0; u < NB; ++u) r[u] = rec_raw(recs, i0 + u * 64 + lane, len);
+            uint32_t b[NB][FW];
 #pragma unroll
-            for (int u = 0; u < RB; ++u)
+            for (int u = 0; u < NB; ++u)
 #pragma unroll
                 for (int v = 0; v < FW; ++v) b[u][v] = ldg(col[v] + rec_row(r[u]));
 #pragma unroll
-            for (int u = 0; u < RB; ++u) {
-                const uint32_t w = rec_w(r[u]), y = rec_y(r[u]);  // padding rows: w = 0
+            for (int u = 0; u < NB; ++u) {
+                if (i0 + u * 64 + lane >= len) continue;
+                const uint32_t w = rec_w(r[u]), y = rec_y(r[u]);
 #pragma unroll
                 for (int v = 0; v < FW; ++v)
-                    if (v < nf && w) atomicAdd(&hist[(v * KMAX + y) * 256 + b[u][v]], w);
+                    if (v < nf) count_row(hist + v * hw * 256u, cf, y, b[u][v], w);
             }
-        }
+#pragma unroll
+            for (int v = 0; v < FW; ++v) {
+                b0[v] = (int)b[0][v];
+                b1[v] = (int)b[1][v];
+            }
+        };
+        if (len <= 128u)
+            batch(0u, std::integral_constant<int, 2>{});
+        else
+            for (uint32_t i0 = 0; i0 < len; i0 += 64 * RB)
+                batch(i0, std::integral_constant<int, RB>{});
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         uint32_t cnode[KMAX];
 #pragma unroll
         for (int c = 0; c < KMAX; ++c) cnode[c] = sr.cnode[c];
-        const uint32_t N = sr.n;
         const int B = (int)sr.B;
-        Cand best;
-        best.nl = 0;
-        int bi = 0;
+        ItemBest best;
+        best.q = -1.0f;
+        best.b = 0;
+        uint32_t bi = 0;
         uint32_t best_cl[KMAX];
 #pragma unroll
         for (int c = 0; c < KMAX; ++c) best_cl[c] = 0;
 #pragma unroll
         for (int v = 0; v < FW; ++v) {
             if (v >= nf) break;
-            Cand fb;
             uint32_t fcl[KMAX];
-            if constexpr (KMAX <= 4)
-                fb = feature_best_compact<KMAX>(hist + v * KMAX * 256, B, q0 + v, fq[v], cnode,
-                                                N, F.split_rank, fcl);
-            else
-                fb = feature_best<KMAX>(hist + v * KMAX * 256, B, q0 + v, fq[v], cnode, N,
-                                        F.split_rank);
+            const ItemBest fb =
+                scan_item<KMAX, BIG>(hist + v * hw * 256u, cf, K, len, b0[v], b1[v],
+                                     B, cnode, N, F.split_rank, fcl);
+            if (fb.q < 0.0f) continue;
             // draws in order: a strictly better score replaces
-            if (fb.nl != 0 && (best.nl == 0 || cand_better(fb, best))) {
-                best = fb;
-                bi = v;
-                if constexpr (KMAX <= 4) {
+            bool better = best.q < 0.0f;
+            if (FW > 1 && !better) {
+                if (F.split_rank && (fb.q < fp32_floor(best.q) || best.q < fp32_floor(fb.q))) {
+                    better = fb.q > best.q;
+                } else {
+                    Cand x, y;
+                    uint32_t rx[KMAX + 2], ry[KMAX + 2];
+                    rx[1] = ry[1] = 0;
 #pragma unroll
-                    for (int c = 0; c < KMAX; ++c) best_cl[c] = fcl[c];
+                    for (int c = 0; c < KMAX; ++c) {
+                        rx[2 + c] = fcl[c];
+                        ry[2 + c] = best_cl[c];
+                    }
+                    x = cand_of<KMAX>(rx, cnode, N);
+                    y = cand_of<KMAX>(ry, cnode, N);
+                    better = cand_better(x, y);
                 }
             }
-        }
-        // left class counts of the item's best, for the partition step
-        uint32_t* out = F.cand_cl + (size_t)item * F.kmax;
-        if constexpr (KMAX <= 4) {
-            if (lane < KMAX) {
+            if (better) {
+                best = fb;
+                bi = (uint32_t)v;
 #pragma unroll
-                for (int c = 0; c < KMAX; ++c)
-                    if (lane == c) out[c] = best.nl != 0 ? best_cl[c] : 0u;
-            } else if (lane < F.kmax) {
-                out[lane] = 0u;  // the plan's class planes past this instance's
-            }
-        } else {
-            const int bt = best.nl != 0 ? best.b : -1;
-#pragma unroll
-            for (int c = 0; c < KMAX; ++c) {
-                const uint4 v4 =
-                    *reinterpret_cast<const uint4*>(hist + (bi * KMAX + c) * 256 + lane * 4);
-                const int bl = lane * 4;
-                const uint32_t a = (bl <= bt ? v4.x : 0u) + (bl + 1 <= bt ? v4.y : 0u) +
-                                   (bl + 2 <= bt ? v4.z : 0u) + (bl + 3 <= bt ? v4.w : 0u);
-                const uint32_t tot =
-                    (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(a), 63);
-                if (lane == c) out[c] = tot;
+                for (int c = 0; c < KMAX; ++c) best_cl[c] = fcl[c];
             }
         }
-        if (lane == 0) F.cand[item] = best;
+        put_item<KMAX>(F, item, best, bi, best_cl);
         alg += (unsigned long long)len * (unsigned long long)(nf + (j == 0 ? 6 : 0));
         // the histogram is rewritten by the wave's next item
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -1442,18 +1666,18 @@ __global__ __launch_bounds__(256) void k_col_scatter(ForestDev F, int level) {
 
 // k_hist_col: grid-stride over units.  The workgroup copies the unit's bin
 // column into LDS (16-byte loads, the whole column once), then each wave
-// takes the unit's items in turn: an LDS class-count histogram [KMAX][256]
-// from the node's row records and the staged bins, the prefix scan, and the
-// item's candidate and left class counts (item = slot * mtry_cap + draw).
-template <int KMAX>
+// takes the unit's items in turn: an LDS class-count histogram from the node's
+// row records and the staged bins, the threshold scan, and the item's record
+// (item = slot * mtry_cap + draw).
+template <int KMAX, bool BIG>
 __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level) {
-    constexpr int WORDS = KMAX * 256;
     constexpr int RB = 8;
     extern __shared__ uint4 lds_raw[];
     const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
     const uint32_t nw = blockDim.x >> 6;
-    uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw) + wave * WORDS;
-    uint4* colq = lds_raw + nw * (WORDS / 4);
+    const uint32_t hw = (uint32_t)F.hist_words;
+    uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw) + (size_t)wave * hw * 256u;
+    uint4* colq = lds_raw + nw * hw * 64u;
     const uint8_t* colb = reinterpret_cast<const uint8_t*>(colq);
     const LevelCtr& lc = F.ctrs[level];
     const uint32_t n_units = lc.overflow ? 0u : min(lc.n_units, F.unit_cap);
@@ -1461,7 +1685,10 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level) {
     unsigned long long alg = 0;
     for (uint32_t u = blockIdx.x; u < n_units; u += gridDim.x) {
         const ColUnit cu = F.units[u];
-        const uint4* src = reinterpret_cast<const uint4*>(F.fcol[F.fitems[cu.begin]]);
+        const uint32_t item0 = F.fitems[cu.begin];
+        const uint4* src = reinterpret_cast<const uint4*>(F.fcol[item0]);
+        const uint32_t K = F.srec[item0 / mc].K;  // a column's items are of one job
+        const int B = (int)F.srec[item0 / mc].B;
         for (uint32_t i = threadIdx.x; i < cu.gq; i += blockDim.x) colq[i] = src[i];
         __syncthreads();
         // The wave's items are k0 + t * nw; their node records are loaded
@@ -1473,7 +1700,6 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level) {
             const SlotRec* msr = F.srec + my_item / mc;
             const uint64_t my_recs = have ? reinterpret_cast<uint64_t>(msr->recs) : 0ull;
             const uint32_t my_len = have ? msr->len : 0u, my_n = have ? msr->n : 0u;
-            const uint32_t my_B = have ? msr->B : 0u, my_f = have ? F.feat[my_item] : 0u;
             uint32_t my_cn[KMAX];
 #pragma unroll
             for (int c = 0; c < KMAX; ++c) my_cn[c] = have ? msr->cnode[c] : 0u;
@@ -1481,88 +1707,77 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level) {
             // Record batches stream one ahead: while a batch is counted, the
             // next one is in flight -- the item's next batch, or after its
             // last batch the first batch of the wave's next item (hidden
-            // behind that item's scan).
+            // behind that item's scan).  An item of at most 128 rows takes
+            // the batch's first two records per lane only.
             uint64_t rn[RB];
-            {
-                const uint64_t* recs = reinterpret_cast<const uint64_t*>(readlane64(my_recs, 0));
-                const uint32_t len = readlane_w(my_len, 0);
+            auto fetch = [&](const uint64_t* recs, uint32_t i0, uint32_t len) {
 #pragma unroll
-                for (int v = 0; v < RB; ++v) {
-                    const uint32_t i = v * 64 + lane;
-                    rn[v] = rec_raw(recs, i, len);
+                for (int v = 0; v < 2; ++v) rn[v] = rec_raw(recs, i0 + v * 64 + lane, len);
+                if (len > 128u) {
+#pragma unroll
+                    for (int v = 2; v < RB; ++v) rn[v] = rec_raw(recs, i0 + v * 64 + lane, len);
                 }
-            }
+            };
+            fetch(reinterpret_cast<const uint64_t*>(readlane64(my_recs, 0)), 0u,
+                  readlane_w(my_len, 0));
             for (uint32_t t = 0; t < n_here; ++t) {
                 const uint32_t item = readlane_w(my_item, (int)t);
-                const uint32_t q = item - (item / mc) * mc;
-                const uint64_t* recs = reinterpret_cast<const uint64_t*>(readlane64(my_recs, (int)t));
-                const uint32_t len = readlane_w(my_len, (int)t);
+                const uint32_t len = readlane_w(my_len, (int)t), N = readlane_w(my_n, (int)t);
+                const CountForm cf = count_form<KMAX>(N, K);
+                for (uint32_t i = 0; i < cf.words; ++i)
+                    reinterpret_cast<uint4*>(hist)[i * 64u + lane] = make_uint4(0u, 0u, 0u, 0u);
+                int b0 = 0, b1 = 0;
+                auto fetch_next = [&]() {
+                    if (t + 1 < n_here)
+                        fetch(reinterpret_cast<const uint64_t*>(readlane64(my_recs, (int)t + 1)),
+                              0u, readlane_w(my_len, (int)t + 1));
+                };
+                if (len <= 128u) {
+                    const uint64_t r0 = rn[0], r1 = rn[1];
+                    b0 = colb[rec_row(r0)];
+                    b1 = colb[rec_row(r1)];
+                    fetch_next();
+                    if ((uint32_t)lane < len)
+                        count_row(hist, cf, rec_y(r0), (uint32_t)b0, rec_w(r0));
+                    if ((uint32_t)lane + 64u < len)
+                        count_row(hist, cf, rec_y(r1), (uint32_t)b1, rec_w(r1));
+                } else {
+                    const uint64_t* recs =
+                        reinterpret_cast<const uint64_t*>(readlane64(my_recs, (int)t));
+                    for (uint32_t i0 = 0;;) {
+                        uint64_t r[RB];
 #pragma unroll
-                for (int i = 0; i < WORDS / 256; ++i)
-                    reinterpret_cast<uint4*>(hist)[i * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
-                for (uint32_t i0 = 0;;) {
-                    uint64_t r[RB];
+                        for (int v = 0; v < RB; ++v) r[v] = rn[v];
+                        // all bins of the batch first (records past the node's
+                        // end repeat its last record and are masked below),
+                        // then the atomics: one LDS round trip for the batch,
+                        // not one per row
+                        uint32_t bb[RB];
 #pragma unroll
-                    for (int v = 0; v < RB; ++v) r[v] = rn[v];
-                    // all bins of the batch first (records past the node's end
-                    // repeat its last record and are masked below), then the
-                    // atomics: one LDS round trip for the batch, not one per row
-                    uint32_t bb[RB];
+                        for (int v = 0; v < RB; ++v) bb[v] = colb[rec_row(r[v])];
+                        const uint32_t i1 = i0 + 64 * RB;
+                        if (i1 < len)
+                            fetch(recs, i1, len);
+                        else
+                            fetch_next();
 #pragma unroll
-                    for (int v = 0; v < RB; ++v) bb[v] = colb[rec_row(r[v])];
-                    const uint32_t i1 = i0 + 64 * RB;
-                    if (i1 < len) {
-#pragma unroll
-                        for (int v = 0; v < RB; ++v) rn[v] = rec_raw(recs, i1 + v * 64 + lane, len);
-                    } else if (t + 1 < n_here) {
-                        const uint64_t* nrecs =
-                            reinterpret_cast<const uint64_t*>(readlane64(my_recs, (int)t + 1));
-                        const uint32_t nlen = readlane_w(my_len, (int)t + 1);
-#pragma unroll
-                        for (int v = 0; v < RB; ++v) rn[v] = rec_raw(nrecs, v * 64 + lane, nlen);
+                        for (int v = 0; v < RB; ++v) {
+                            if (i0 + (uint32_t)(v * 64 + lane) < len)
+                                count_row(hist, cf, rec_y(r[v]), bb[v], rec_w(r[v]));
+                        }
+                        if (i1 >= len) break;
+                        i0 = i1;
                     }
-#pragma unroll
-                    for (int v = 0; v < RB; ++v) {
-                        if (i0 + (uint32_t)(v * 64 + lane) < len)
-                            atomicAdd(&hist[rec_y(r[v]) * 256 + bb[v]], rec_w(r[v]));
-                    }
-                    if (i1 >= len) break;
-                    i0 = i1;
                 }
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                uint32_t cnode[KMAX];
+                uint32_t cnode[KMAX], cl[KMAX];
 #pragma unroll
                 for (int c = 0; c < KMAX; ++c) cnode[c] = readlane_w(my_cn[c], (int)t);
-                const int B = (int)readlane_w(my_B, (int)t), fq = (int)readlane_w(my_f, (int)t);
-                const uint32_t N = readlane_w(my_n, (int)t);
-                Cand best;
-                uint32_t* out = F.cand_cl + (size_t)item * F.kmax;
-                if constexpr (KMAX <= 4) {
-                    uint32_t cl[KMAX];
-                    best = feature_best_compact<KMAX>(hist, B, (int)q, fq, cnode, N, F.split_rank,
-                                                      cl);
-                    if (lane < KMAX) {
-#pragma unroll
-                        for (int c = 0; c < KMAX; ++c)
-                            if (lane == c) out[c] = best.nl != 0 ? cl[c] : 0u;
-                    }
-                } else {
-                    best = feature_best<KMAX>(hist, B, (int)q, fq, cnode, N, F.split_rank);
-                    const int bt = best.nl != 0 ? best.b : -1;
-#pragma unroll
-                    for (int c = 0; c < KMAX; ++c) {
-                        const uint4 v4 =
-                            *reinterpret_cast<const uint4*>(hist + c * 256 + lane * 4);
-                        const int bl = lane * 4;
-                        const uint32_t a = (bl <= bt ? v4.x : 0u) + (bl + 1 <= bt ? v4.y : 0u) +
-                                           (bl + 2 <= bt ? v4.z : 0u) + (bl + 3 <= bt ? v4.w : 0u);
-                        const uint32_t tot =
-                            (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(a), 63);
-                        if (lane == c) out[c] = tot;
-                    }
-                }
-                if (lane == 0) F.cand[item] = best;
-                alg += (unsigned long long)len * (unsigned long long)(1u + (q == 0 ? 6u : 0u));
+                const ItemBest best = scan_item<KMAX, BIG>(hist, cf, K, len, b0, b1, B, cnode, N,
+                                                           F.split_rank, cl);
+                put_item<KMAX>(F, item, best, 0u, cl);
+                if (F.alg_bytes)
+                    alg += (unsigned long long)len * (item % mc == 0u ? 7ull : 1ull);
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             }
         }
@@ -1765,31 +1980,35 @@ __global__ __launch_bounds__(256) void k_split_finalize(ForestDev F0, int level,
             S += (uint64_t)cnode[c] * cnode[c];
         }
         const uint32_t N = sr.n;
-        // rank the items' candidates: each lane keeps the best of its items
+        // The items' records, lanes over items: with FP32 ranking those within
+        // the margin of the maximum, else all, are compared exactly in draw
+        // order, a strictly better one replacing (so ties keep the earlier
+        // draw); one finalist alone is taken as it is.
         const int ni = ((int)sr.mtry + F.fw - 1) / F.fw;
-        Cand c;
-        c.nl = 0;
-        c.q = 0x7FFFFFFF;
-        c.b = 0x7FFFFFFF;
-        c.f = 0;
-        c.nr = 0;
-        c.pad = 0;
-        c.sl = c.sr = 0;
-        int ci = -1;
-        for (int t = lane; t < ni; t += 64) {
-            const Cand d = F.cand[(size_t)slot * F.npi + t];
-            if (d.nl != 0 && (c.nl == 0 || cand_wins_total(d, c))) {
-                c = d;
-                ci = t;
+        const uint32_t* items = F.icand + (size_t)slot * F.npi * (KMAX + 2);
+        float fl = 0.0f;
+        if (F.split_rank) {
+            float q1 = -1.0f;
+            for (int t = lane; t < ni; t += 64)
+                q1 = fmaxf(q1, __uint_as_float(items[(size_t)t * (KMAX + 2)]));
+            const float qmax = wave_max_f_dpp(q1);
+            fl = qmax < 0.0f ? 2.0f * (float)N : fp32_floor(qmax);  // Q <= N
+        }
+        Cand best;
+        best.nl = 0;
+        int bt = -1;
+        for (int t0 = 0; t0 < ni; t0 += 64) {
+            const float q =
+                t0 + lane < ni ? __uint_as_float(items[(size_t)(t0 + lane) * (KMAX + 2)]) : -1.0f;
+            for (uint64_t m = __ballot(q >= fl); m; m &= m - 1) {
+                const int t = t0 + (int)__ffsll((unsigned long long)m) - 1;
+                const Cand d = cand_of<KMAX>(items + (size_t)t * (KMAX + 2), cnode, N);
+                if (best.nl == 0 || cand_better(d, best)) {
+                    best = d;
+                    bt = t;
+                }
             }
         }
-        // FP32 ranking with the exact recheck of the finalists (as in the
-        // histogram scans), or exact throughout
-        const Cand best = F.split_rank ? wave_best_total_fp32(c, c.nl != 0 ? cand_q32(c) : -1.0f)
-                                       : wave_best_total_exact(c);
-        const unsigned long long hit =
-            __ballot(best.nl != 0 && c.nl != 0 && c.q == best.q && c.b == best.b);
-        const int bt = hit ? __shfl(ci, (int)__ffsll(hit) - 1) : -1;
         const uint32_t child = F.next_base + 2u * (F.n_small_cur + slot);
         const bool split = bt >= 0 && cand_positive(best, S, N);
         if (!split) {  // stays the leaf it was created as
@@ -1799,7 +2018,10 @@ __global__ __launch_bounds__(256) void k_split_finalize(ForestDev F0, int level,
             }
             continue;
         }
-        const uint32_t* clt = F.cand_cl + ((size_t)slot * F.npi + bt) * F.kmax;
+        const uint32_t* rec = items + (size_t)bt * (KMAX + 2);
+        const uint32_t* clt = rec + 2;
+        best.q = bt * F.fw + (int)(rec[1] >> 8);
+        best.f = (int)F.feat[(size_t)slot * F.mtry_cap + best.q];
         uint32_t cl[16], cr[16];
         int nzl = 0, nzr = 0;
 #pragma unroll
@@ -1961,11 +2183,21 @@ void launch_draws(const ForestDev& F, int level, uint32_t grid_wg, hipStream_t s
 template <int KMAX, int FW>
 static void launch_tile_rb(const ForestDev& F, int level, uint32_t first, uint32_t count,
                            dim3 grid, size_t lds, int rb, hipStream_t st) {
+    // plans that may hold nodes of weight 65536 and more: one class per word
+    const bool big = F.hist_words == F.kmax;
+#define BORUTA_TILE(RB)                                                                          \
+    if (big)                                                                                     \
+        hipLaunchKernelGGL((k_hist_tile<KMAX, FW, RB, true>), grid, dim3(256), lds, st, F, level, \
+                           first, count);                                                        \
+    else                                                                                         \
+        hipLaunchKernelGGL((k_hist_tile<KMAX, FW, RB, false>), grid, dim3(256), lds, st, F,      \
+                           level, first, count);
     switch (rb) {
-        case 4: hipLaunchKernelGGL((k_hist_tile<KMAX, FW, 4>), grid, dim3(256), lds, st, F, level, first, count); break;
-        case 16: hipLaunchKernelGGL((k_hist_tile<KMAX, FW, 16>), grid, dim3(256), lds, st, F, level, first, count); break;
-        default: hipLaunchKernelGGL((k_hist_tile<KMAX, FW, 8>), grid, dim3(256), lds, st, F, level, first, count); break;
+        case 4: BORUTA_TILE(4) break;
+        case 16: BORUTA_TILE(16) break;
+        default: BORUTA_TILE(8) break;
     }
+#undef BORUTA_TILE
 }
 
 // rb: rows per lane per batch (4, 8 or 16); F.fw draws per item with
@@ -1975,22 +2207,18 @@ static void launch_tile_rb(const ForestDev& F, int level, uint32_t first, uint32
 void launch_hist_tile(const ForestDev& F, int level, uint32_t first, uint32_t count,
                       uint32_t grid_wg, int rb, hipStream_t st) {
     if (!count) return;
-    // four waves of fw * KMAX * 256 words
-    const size_t lds = (size_t)4 * F.fw * F.kmax * 256 * sizeof(uint32_t);
+    // four waves of fw histograms of hist_words words per bin
+    const size_t lds = (size_t)4 * F.fw * F.hist_words * 256 * sizeof(uint32_t);
     const dim3 grid(grid_wg);
     if (F.has_reg) {
+        const size_t rl = std::max(lds, (size_t)4 * 768 * sizeof(uint32_t));
         switch (rb) {
-            case 4: hipLaunchKernelGGL((k_hist_reg<4>), grid, dim3(256), lds, st, F, level, first, count); break;
-            case 16: hipLaunchKernelGGL((k_hist_reg<16>), grid, dim3(256), lds, st, F, level, first, count); break;
-            default: hipLaunchKernelGGL((k_hist_reg<8>), grid, dim3(256), lds, st, F, level, first, count); break;
+            case 4: hipLaunchKernelGGL((k_hist_reg<4>), grid, dim3(256), rl, st, F, level, first, count); break;
+            case 16: hipLaunchKernelGGL((k_hist_reg<16>), grid, dim3(256), rl, st, F, level, first, count); break;
+            default: hipLaunchKernelGGL((k_hist_reg<8>), grid, dim3(256), rl, st, F, level, first, count); break;
         }
     }
     if (!F.has_cls) return;
-    if (F.split_k) {  // the items of jobs of at most 4 classes (FW = 1 for these plans)
-        const size_t lds4 = (size_t)4 * F.fw * 4 * 256 * sizeof(uint32_t);
-        if (F.fw == 1) launch_tile_rb<4, 1>(F, level, first, count, grid, lds4, rb, st);
-        else launch_tile_rb<4, 2>(F, level, first, count, grid, lds4, rb, st);
-    }
     switch (F.kmax * 8 + F.fw) {
         case 2 * 8 + 4: launch_tile_rb<2, 4>(F, level, first, count, grid, lds, rb, st); break;
         case 2 * 8 + 2: launch_tile_rb<2, 2>(F, level, first, count, grid, lds, rb, st); break;
@@ -2004,8 +2232,8 @@ void launch_hist_tile(const ForestDev& F, int level, uint32_t first, uint32_t co
     }
 }
 
-size_t hist_col_lds(int kmax, int waves, uint32_t gq_max) {
-    return (size_t)waves * kmax * 256 * sizeof(uint32_t) + (size_t)gq_max * 16;
+size_t hist_col_lds(int hist_words, int waves, uint32_t gq_max) {
+    return (size_t)waves * hist_words * 256 * sizeof(uint32_t) + (size_t)gq_max * 16;
 }
 
 // F.col_count == 2: the places are counted by k_col_count (n_gcol <= kColCountLds)
@@ -2019,29 +2247,34 @@ void launch_col_sort(const ForestDev& F, int level, uint32_t grid_wg, hipStream_
 
 // Allows the column path's dynamic LDS (above the default per-launch limit)
 // for the instantiation of kmax classes.
-hipError_t prepare_hist_col(int kmax, size_t lds) {
-    const void* fn;
-    switch (kmax) {
-        case 2: fn = reinterpret_cast<const void*>(&k_hist_col<2>); break;
-        case 3: fn = reinterpret_cast<const void*>(&k_hist_col<3>); break;
-        case 4: fn = reinterpret_cast<const void*>(&k_hist_col<4>); break;
-        case 8: fn = reinterpret_cast<const void*>(&k_hist_col<8>); break;
-        default: fn = reinterpret_cast<const void*>(&k_hist_col<16>); break;
+static const void* hist_col_fn(int kmax, bool big) {
+    switch (kmax * 2 + (big ? 1 : 0)) {
+        case 4: return reinterpret_cast<const void*>(&k_hist_col<2, false>);
+        case 5: return reinterpret_cast<const void*>(&k_hist_col<2, true>);
+        case 6: return reinterpret_cast<const void*>(&k_hist_col<3, false>);
+        case 7: return reinterpret_cast<const void*>(&k_hist_col<3, true>);
+        case 8: return reinterpret_cast<const void*>(&k_hist_col<4, false>);
+        case 9: return reinterpret_cast<const void*>(&k_hist_col<4, true>);
+        case 16: return reinterpret_cast<const void*>(&k_hist_col<8, false>);
+        case 17: return reinterpret_cast<const void*>(&k_hist_col<8, true>);
+        case 32: return reinterpret_cast<const void*>(&k_hist_col<16, false>);
+        default: return reinterpret_cast<const void*>(&k_hist_col<16, true>);
     }
-    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+hipError_t prepare_hist_col(int kmax, int hist_words, size_t lds) {
+    return hipFuncSetAttribute(hist_col_fn(kmax, hist_words == kmax),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
 void launch_hist_col(const ForestDev& F, int level, uint32_t grid_wg, int waves, uint32_t gq_max,
                      hipStream_t st) {
-    const size_t lds = hist_col_lds(F.kmax, waves, gq_max);
-    const dim3 grid(grid_wg), block(64 * waves);
-    switch (F.kmax) {
-        case 2: hipLaunchKernelGGL(k_hist_col<2>, grid, block, lds, st, F, level); break;
-        case 3: hipLaunchKernelGGL(k_hist_col<3>, grid, block, lds, st, F, level); break;
-        case 4: hipLaunchKernelGGL(k_hist_col<4>, grid, block, lds, st, F, level); break;
-        case 8: hipLaunchKernelGGL(k_hist_col<8>, grid, block, lds, st, F, level); break;
-        default: hipLaunchKernelGGL(k_hist_col<16>, grid, block, lds, st, F, level); break;
-    }
+    const size_t lds = hist_col_lds(F.hist_words, waves, gq_max);
+    ForestDev f = F;
+    void* args[] = {&f, &level};
+    // a refused launch is reported by the caller's hipGetLastError
+    (void)hipLaunchKernel(hist_col_fn(F.kmax, F.hist_words == F.kmax), dim3(grid_wg),
+                          dim3(64 * waves), args, lds, st);
 }
 
 void launch_split_finalize(const ForestDev& F, int level, uint32_t first, uint32_t count,
