@@ -133,18 +133,14 @@ __device__ __forceinline__ T ldg(const T* p) {
     return *(const __attribute__((address_space(1))) T*)p;
 }
 
-// Row record i of a node's len >= 1 records, 0 (weight 0) past the end: the
-// load itself is unconditional (clamped to the last record), so a batch of
-// them issues back to back instead of one branch per load.
-__device__ __forceinline__ uint64_t rec_at(const uint64_t* recs, uint32_t i, uint32_t len) {
-    const uint64_t v = ldg(recs + (i < len ? i : len - 1u));
-    return i < len ? v : 0ull;
-}
-// The same load without the mask, for records loaded ahead of their use (a
-// prefetch): the caller masks past-the-end records when it uses them, so the
-// load need not complete at the point of the call.
-__device__ __forceinline__ uint64_t rec_raw(const uint64_t* recs, uint32_t i, uint32_t len) {
-    return ldg(recs + (i < len ? i : len - 1u));
+// Row record i of a node's len >= 1 records, its last one past the end: the
+// load is unconditional (so a batch of them issues back to back instead of one
+// branch per load, and may run ahead of its use); the caller masks past-the-end
+// records.  The byte offset is 32-bit (a node has at most 2^24 records): one
+// scalar base and a vector offset.
+__device__ __forceinline__ uint32_t rec_raw(const uint32_t* recs, uint32_t i, uint32_t len) {
+    const uint32_t off = (i < len ? i : len - 1u) * 4u;
+    return ldg(reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(recs) + off));
 }
 
 // Wave-uniform values: the compiler cannot see that e.g. threadIdx.x / 64 is
@@ -280,7 +276,7 @@ struct JobDev {
     uint64_t* G;           // [T][pw_cap] per-tree fixed-point Gini decreases
     int64_t* imp;          // [pw_cap] integer importance of the iteration
     uint32_t* wbuf;        // [T][n] bootstrap multiplicities
-    uint64_t* rec[2];      // [T][rstride] row records, ping-pong by level parity
+    uint32_t* rec[2];      // [T][rstride] row records, ping-pong by level parity
     uint32_t* oob;         // [T][n] out-of-bag rows, ascending
     int32_t* tstat;        // [T][4] distinct in-bag, OOB rows, OOB correct, spare
     uint8_t* rowmaj;       // [n_pad][rm_stride] the widened bins row-major, rebuilt every
@@ -300,7 +296,7 @@ struct NodeDev {
     uint32_t tree;   // global tree index of the iteration
     uint32_t heap;   // heap id: root 1, children 2h, 2h+1
     uint32_t seg;    // first row record (within the tree's record block)
-    uint32_t len;    // distinct rows
+    uint32_t len;    // row records (distinct rows, but for rows drawn over 15 times)
     uint32_t n;      // weighted rows
     int32_t feat;    // widened column, -1 for a leaf
     uint32_t left;   // index of the left child; the right one is left + 1
@@ -312,15 +308,16 @@ struct NodeDev {
 // What a histogram item needs of its large node, gathered once per node and
 // level so that an item's first loads do not depend on each other.
 struct SlotRec {
-    const uint64_t* recs;  // the node's row records (this level's parity)
+    const uint32_t* recs;  // the node's row records (this level's parity)
     const int64_t* yfix;   // regression job: its fixed-point targets (else null)
     uint32_t id;           // node index
-    uint32_t len, n;       // distinct rows, weighted rows
+    uint32_t len, n;       // row records, weighted rows
     uint32_t mtry;         // features drawn this iteration
     uint32_t B, reg;       // bins; 1 for a regression job
     uint32_t K, pad;       // the job's classes
     uint32_t cnode[16];    // weighted class counts (zero past K); regression: the
                            // weighted target sum T in words 0 (low) and 1 (high)
+    uint32_t pk[8];        // the class counts packed as count_bits says
 };
 
 // Per-level counters: the lists of tree level d (small nodes, large-node
@@ -334,13 +331,25 @@ struct LevelCtr {
     uint32_t pad[2];
 };
 
-// Row record: row | weight << 32 | label << 48.
-__device__ __forceinline__ uint64_t rec_pack(uint32_t row, uint32_t w, uint32_t y) {
-    return (uint64_t)row | ((uint64_t)w << 32) | ((uint64_t)y << 48);
+// Row record: row | weight << 24 | label << 28 (n <= 2^24, at most 16 classes).
+// A row drawn more than 15 times is several records of weight at most 15: a
+// node's counts and target sums are the same, and a tree has at most n records.
+constexpr uint32_t kRecWeight = 15;
+__device__ __forceinline__ uint32_t rec_pack(uint32_t row, uint32_t w, uint32_t y) {
+    return row | (w << 24) | (y << 28);
 }
-__device__ __forceinline__ uint32_t rec_row(uint64_t r) { return (uint32_t)r; }
-__device__ __forceinline__ uint32_t rec_w(uint64_t r) { return (uint32_t)(r >> 32) & 0xFFFFu; }
-__device__ __forceinline__ uint32_t rec_y(uint64_t r) { return (uint32_t)(r >> 48) & 0xFFu; }
+__device__ __forceinline__ uint32_t rec_row(uint32_t r) { return r & 0xFFFFFFu; }
+__device__ __forceinline__ uint32_t rec_w(uint32_t r) { return r >> 24 & 15u; }
+__device__ __forceinline__ uint32_t rec_y(uint32_t r) { return r >> 28; }
+
+// How the histogram items of a node hold their class counts: 8-bit fields
+// below a weight of 256 (two-class plans need none of these: one word either
+// way), 16-bit fields below 65536, else (0) one word per class.
+__host__ __device__ __forceinline__ uint32_t count_bits(int kmax, uint32_t N) {
+    return kmax > 2 && N < 256u ? 8u : (N < 65536u ? 16u : 0u);
+}
+// Words of a node's packed class counts: two classes to a word.
+__host__ __device__ constexpr int pk_words(int kmax) { return (kmax + 1) / 2; }
 
 // k_col_count: columns counted in LDS (64 KB) and its workgroups
 constexpr uint32_t kColCountLds = 16384;
@@ -372,8 +381,8 @@ struct ForestDev {
     uint32_t* cls;        // [node][kmax] weighted class counts
     uint64_t* ngain;      // [node] fixed-point Gini decrease of a split node
     Cand* cand;           // [slot][npi] regression: best candidate of each histogram item
-    uint32_t* icand;      // [slot][npi][kmax + 2] classification: the record of each item's
-                          // best threshold (put_item)
+    uint32_t* icand;      // [slot][npi][item_words] classification: the record of each
+                          // item's best threshold (put_item)
     uint32_t* feat;       // [slot][mtry_cap] the node's drawn features, draw order
     const uint8_t** fcol; // [slot][mtry_cap] their bin columns
     SlotRec* srec;        // [slot] the large nodes of the level
@@ -399,6 +408,7 @@ struct ForestDev {
     int32_t has_cls, has_reg;  // the plan holds classification / regression jobs
     int32_t hist_words;   // LDS words per bin of an item's histogram: two classes to a word
                           // while no node weighs 65536 rows, else one per class plane
+    int32_t item_words;   // words of an item record: 2 + hist_words
     int32_t npi;          // histogram items per large node (draw positions / fw)
     int32_t fw;           // draws per histogram item
     uint32_t small_rows;  // a node takes the wave path only up to this many distinct rows

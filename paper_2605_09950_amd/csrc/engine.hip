@@ -430,8 +430,8 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         j.G = s.mode == 0 ? r.take(T * j.pw_cap * 8) : 0;
         j.imp = r.take((size_t)j.pw_cap * 8);
         j.wbuf = r.take(T * n * 4);
-        j.rec0 = r.take(T * n * 8);
-        j.rec1 = r.take(T * n * 8);
+        j.rec0 = r.take(T * n * 4);
+        j.rec1 = r.take(T * n * 4);
         if (s.yr) {
             j.yfix = sh ? sh->yfix : r.take(n * 8);
             j.yrange = sh ? sh->yrange : r.take(8);
@@ -484,7 +484,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     }
     pl.has_reg = any_reg;
     // a root weighs n rows: 16-bit class counts hold every node below 65536
-    pl.hist_words = pl.max_n < 65536 ? (pl.kmax + 1) / 2 : pl.kmax;
+    pl.hist_words = pl.max_n < 65536 ? pk_words(pl.kmax) : pl.kmax;
     int col_level = any_reg ? kColNever : o.col_level;
     if (col_level == 0) {
         size_t widest = 0;
@@ -530,7 +530,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     pl.small0 = r.take((size_t)pl.small_cap * 4);
     pl.small1 = r.take((size_t)pl.small_cap * 4);
     pl.cand = any_reg ? r.take((size_t)pl.slot_cap * pl.npi * sizeof(Cand)) : 0;
-    pl.icand = pl.has_cls ? r.take((size_t)pl.slot_cap * pl.npi * (pl.kmax + 2) * 4) : 0;
+    pl.icand = pl.has_cls ? r.take((size_t)pl.slot_cap * pl.npi * (pl.hist_words + 2) * 4) : 0;
     pl.feat = r.take((size_t)pl.slot_cap * pl.mtry_cap * 4);
     pl.fcol = r.take((size_t)pl.slot_cap * pl.mtry_cap * 8);
     pl.srec = r.take((size_t)pl.slot_cap * sizeof(SlotRec));
@@ -839,8 +839,8 @@ void Engine::setup(std::vector<int>& status) {
         J.G = s.mode == 0 ? at<uint64_t>(jp.G) : nullptr;
         J.imp = at<int64_t>(jp.imp);
         J.wbuf = at<uint32_t>(jp.wbuf);
-        J.rec[0] = at<uint64_t>(jp.rec0);
-        J.rec[1] = at<uint64_t>(jp.rec1);
+        J.rec[0] = at<uint32_t>(jp.rec0);
+        J.rec[1] = at<uint32_t>(jp.rec1);
         J.oob = at<uint32_t>(jp.oob);
         J.tstat = at<int32_t>(jp.tstat);
         J.rowmaj = jp.rm_stride ? at<uint8_t>(jp.rowmaj) : nullptr;
@@ -950,6 +950,7 @@ ForestDev Engine::forest() const {
     F.has_cls = pl.has_cls ? 1 : 0;
     F.has_reg = pl.has_reg ? 1 : 0;
     F.hist_words = pl.hist_words;
+    F.item_words = pl.hist_words + 2;
     F.small_ncap = 256u;  // the wave path packs class counters in 8-bit fields
     return F;
 }

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(1024) void k_boot_compact(ForestDev F0) {
     const uint32_t n = (uint32_t)J.n;
     const bool reg = J.reg != 0;
     uint32_t* w = J.wbuf + (size_t)tr.tau * n;
-    uint64_t* recs = J.rec[0] + (size_t)tr.tau * J.rstride;
+    uint32_t* recs = J.rec[0] + (size_t)tr.tau * J.rstride;
     uint32_t* oob = J.oob + (size_t)tr.tau * n;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid < 16) s_cls[tid] = 0;
@@ -73,8 +73,16 @@ __global__ __launch_bounds__(1024) void k_boot_compact(ForestDev F0) {
         const bool inb = i < n && wi > 0, isoob = i < n && wi == 0;
         const uint32_t yi = inb && !reg ? (uint32_t)J.y[i] : 0u;
         const uint64_t mi = __ballot(inb), mo = __ballot(isoob);
+        // records of the row; more than one only for rows drawn over 15 times
+        const uint32_t nr = inb ? (wi + kRecWeight - 1u) / kRecWeight : 0u;
+        uint32_t wpre = (uint32_t)__popcll(mi & below), wrec = (uint32_t)__popcll(mi);
+        if (__ballot(nr > 1u)) {
+            const uint32_t incl = wave_incl_sum(nr);
+            wpre = incl - nr;
+            wrec = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
         if (lane == 0) {
-            s_win[wave] = __popcll(mi);
+            s_win[wave] = wrec;
             s_wout[wave] = __popcll(mo);
             s_rin[wave] = __popcll(mi);
         }
@@ -85,8 +93,11 @@ __global__ __launch_bounds__(1024) void k_boot_compact(ForestDev F0) {
             pout += s_wout[v];
         }
         if (inb) {
-            if (wi > 0xFFFFu) atomicOr(&F.ctr->overflow, 8u);
-            recs[pin + __popcll(mi & below)] = rec_pack(i, wi, yi);
+            uint32_t left = wi;
+            for (uint32_t k = 0; k < nr; ++k) {
+                recs[pin + wpre + k] = rec_pack(i, min(left, kRecWeight), yi);
+                left -= min(left, kRecWeight);
+            }
             atomicAdd(&s_cls[yi], wi);
         }
         if (reg) {  // the root's weighted target sum: one LDS atomic per wave
@@ -172,15 +183,15 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
     const int B = J.B, mtry = J.mtry;
     const bool rowmaj = J.rowmaj != nullptr;
     const size_t tbase = (size_t)tr.tau * J.rstride + nd.seg;
-    const uint64_t* rin = J.rec[F.parity] + tbase;
-    uint64_t* rout = J.rec[F.parity ^ 1] + tbase;
+    const uint32_t* rin = J.rec[F.parity] + tbase;
+    uint32_t* rout = J.rec[F.parity ^ 1] + tbase;
     const int len = (int)uniform(nd.len);
     int W = 2;
     while (W < len) W <<= 1;
     const int G = 64 / W;                // features per pass
     const int seg = lane / W, i = lane & (W - 1);
     const bool valid = i < len;
-    const uint64_t rec = valid ? ldg(rin + i) : 0ull;
+    const uint32_t rec = valid ? ldg(rin + i) : 0u;
     const uint32_t row = rec_row(rec), wt = rec_w(rec), yv = rec_y(rec);
     const uint32_t inc = wt << ((yv & 3u) * 8u);  // this lane's row in its counter word
     const uint32_t yw = yv >> 2;                  // that word
@@ -917,137 +928,153 @@ __device__ __forceinline__ ItemBest scan_bins(const uint32_t* h, int B, const ui
     return r;
 }
 
-// How the histogram items of a node hold their class counts: 8-bit fields
-// below a weight of 256, 16-bit fields below 65536, else one word per class.
-// Two-class nodes take 16-bit fields (one word either way).  A row of class y
-// and weight w adds w << (y & fm) * fb to word y >> fs of its bin; words: what
-// the scan of K classes reads.
+// Form of an item's histogram (count_bits): a row of class y and weight w adds
+// w << (y & fm) * fb to word y >> fs of its bin; words: what the scan of K
+// classes reads.
 struct CountForm {
     uint32_t fb, fs, fm, words;
 };
 template <int KMAX>
 __device__ __forceinline__ CountForm count_form(uint32_t N, uint32_t K) {
-    if (KMAX > 2 && N < 256u) return CountForm{8u, 2u, 3u, K <= 4u ? 1u : (K <= 8u ? 2u : 4u)};
-    if (N < 65536u)
+    const uint32_t fb = count_bits(KMAX, N);
+    if (fb == 8u) return CountForm{8u, 2u, 3u, K <= 4u ? 1u : (K <= 8u ? 2u : 4u)};
+    if (fb == 16u)
         return CountForm{16u, 1u, 1u, KMAX == 2 ? 1u : (K <= 4u ? 2u : (K <= 8u ? 4u : 8u))};
     return CountForm{0u, 0u, 0u, (uint32_t)KMAX};
 }
-__device__ __forceinline__ void count_row(uint32_t* h, const CountForm& cf, uint32_t y,
-                                          uint32_t b, uint32_t w) {
-    atomicAdd(&h[(y >> cf.fs) * 256u + b], w << ((y & cf.fm) * cf.fb));
+template <int KMAX>
+__device__ __forceinline__ void count_row(uint32_t* h, const CountForm& cf, uint32_t rec,
+                                          uint32_t b) {
+    const uint32_t y = rec_y(rec), w = rec_w(rec);
+    if (KMAX <= 4 && cf.words == 1u)  // uniform
+        atomicAdd(&h[b], w << (y * cf.fb));
+    else
+        atomicAdd(&h[(y >> cf.fs) * 256u + b], w << ((y & cf.fm) * cf.fb));
 }
 
-// Node counts packed in WORDS words of FB-bit fields, and S = sum c^2.
+// Words of a histogram and of an item's left counts.
+template <int KMAX, bool BIG>
+__host__ __device__ constexpr int item_counts() {
+    return BIG ? KMAX : pk_words(KMAX);
+}
+
+// Field k of left counts l in fb-bit form.
+template <int KMAX, bool BIG>
+__device__ __forceinline__ uint32_t left_count(const uint32_t* l, uint32_t fb, int k) {
+    const uint32_t v16 = pk_field<16>(l, k);
+    const uint32_t v8 = KMAX > 2 ? pk_field<8>(l, k) : v16;
+    const uint32_t v = fb == 8u ? v8 : v16;
+    return BIG && fb == 0u ? l[k] : v;
+}
+
 template <int KMAX, int WORDS, int FB>
-__device__ __forceinline__ uint32_t pack_counts(const uint32_t* c, uint32_t* cn) {
-    constexpr int P = 32 / FB;
+__device__ __forceinline__ ItemBest scan_packed(uint32_t* h, uint32_t len, int b0, int b1, int B,
+                                                const uint32_t* cn, uint32_t N, int split_rank,
+                                                uint32_t* l) {
     uint32_t S = 0;
 #pragma unroll
-    for (int w = 0; w < WORDS; ++w) {
-        cn[w] = 0;
-#pragma unroll
-        for (int k = 0; k < P; ++k)
-            if (w * P + k < KMAX) cn[w] |= c[w * P + k] << (FB * k);
-        S = dotf<FB>(cn[w], cn[w], S);
-    }
-    return S;
+    for (int w = 0; w < WORDS; ++w) S = dotf<FB>(cn[w], cn[w], S);
+    if ((FB == 8 || KMAX == 2) && len <= 64u)
+        return scan_rows<WORDS, FB, 1>(h, len, b0, b1, B, cn, S, N, split_rank, l);
+    if ((FB == 8 || KMAX == 2) && len <= 128u)
+        return scan_rows<WORDS, FB, 2>(h, len, b0, b1, B, cn, S, N, split_rank, l);
+    return scan_bins<WORDS, FB>(h, B, cn, S, N, split_rank, l);
 }
 
 // One feature's best threshold from its histogram in form cf: through the
-// packed scans, or one word per class above a weight of 65535.  cnode: the
-// node's class counts [KMAX] (zero past K); cl: the best threshold's left
-// class counts [KMAX].  b0, b1: the bins of rows lane and lane + 64 (nodes of
-// at most 128 rows; those of 16-bit counts are larger but for odd weights).
-template <int KMAX, int WORDS, int FB>
-__device__ __forceinline__ ItemBest scan_packed(uint32_t* h, uint32_t len, int b0, int b1, int B,
-                                                const uint32_t* cnode, uint32_t N,
-                                                int split_rank, uint32_t* cl) {
-    uint32_t cn[WORDS], l[WORDS];
-    const uint32_t S = pack_counts<KMAX, WORDS, FB>(cnode, cn);
-    ItemBest r;
-    if ((FB == 8 || KMAX == 2) && len <= 64u)
-        r = scan_rows<WORDS, FB, 1>(h, len, b0, b1, B, cn, S, N, split_rank, l);
-    else if ((FB == 8 || KMAX == 2) && len <= 128u)
-        r = scan_rows<WORDS, FB, 2>(h, len, b0, b1, B, cn, S, N, split_rank, l);
-    else
-        r = scan_bins<WORDS, FB>(h, B, cn, S, N, split_rank, l);
-    constexpr int P = 32 / FB;
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) cl[k] = k < P * WORDS ? pk_field<FB>(l, k % (P * WORDS)) : 0u;
-    return r;
-}
-
-// BIG: the plan may hold nodes of weight 65536 and more.
+// packed scans, or one word per class above a weight of 65535 (BIG: the plan
+// may hold such nodes).  pk: the node's packed class counts, cnode: its plain
+// ones; l: the best threshold's left class counts in the node's form.  b0, b1:
+// the bins of rows lane and lane + 64 (nodes of at most 128 rows; those of
+// 16-bit counts are larger but for odd weights).
 template <int KMAX, bool BIG>
 __device__ __forceinline__ ItemBest scan_item(uint32_t* h, const CountForm& cf, uint32_t K,
                                               uint32_t len, int b0, int b1, int B,
-                                              const uint32_t* cnode, uint32_t N, int split_rank,
-                                              uint32_t* cl) {
+                                              const uint32_t* pk, const uint32_t* cnode,
+                                              uint32_t N, int split_rank, uint32_t* l) {
     if (KMAX > 2 && cf.fb == 8u) {
-        if (KMAX <= 4 || K <= 4u)
-            return scan_packed<KMAX, 1, 8>(h, len, b0, b1, B, cnode, N, split_rank, cl);
-        if (KMAX <= 8 || K <= 8u)
-            return scan_packed<KMAX, 2, 8>(h, len, b0, b1, B, cnode, N, split_rank, cl);
-        return scan_packed<KMAX, 4, 8>(h, len, b0, b1, B, cnode, N, split_rank, cl);
+        if constexpr (KMAX > 2) {
+            if (KMAX <= 4 || K <= 4u)
+                return scan_packed<KMAX, 1, 8>(h, len, b0, b1, B, pk, N, split_rank, l);
+        }
+        if constexpr (KMAX > 4) {
+            if (KMAX <= 8 || K <= 8u)
+                return scan_packed<KMAX, 2, 8>(h, len, b0, b1, B, pk, N, split_rank, l);
+        }
+        if constexpr (KMAX > 8)
+            return scan_packed<KMAX, 4, 8>(h, len, b0, b1, B, pk, N, split_rank, l);
     }
     if (!BIG || cf.fb == 16u) {
-        if (KMAX <= 2)
-            return scan_packed<KMAX, 1, 16>(h, len, b0, b1, B, cnode, N, split_rank, cl);
-        if (KMAX <= 4 || K <= 4u)
-            return scan_packed<KMAX, 2, 16>(h, len, b0, b1, B, cnode, N, split_rank, cl);
-        if (KMAX <= 8 || K <= 8u)
-            return scan_packed<KMAX, 4, 16>(h, len, b0, b1, B, cnode, N, split_rank, cl);
-        return scan_packed<KMAX, 8, 16>(h, len, b0, b1, B, cnode, N, split_rank, cl);
-    }
-    ItemBest r;
-    Cand c;
-    if constexpr (KMAX <= 4) {
-        c = feature_best_compact<KMAX>(h, B, 0, 0, cnode, N, split_rank, cl);
-    } else {
-        const int lane = threadIdx.x & 63;
-        c = feature_best<KMAX>(h, B, 0, 0, cnode, N, split_rank);
-        const int bt = c.nl != 0 ? c.b : -1;
-#pragma unroll
-        for (int k = 0; k < KMAX; ++k) {
-            const uint4 v4 = *reinterpret_cast<const uint4*>(h + k * 256 + lane * 4);
-            const int bl = lane * 4;
-            const uint32_t a = (bl <= bt ? v4.x : 0u) + (bl + 1 <= bt ? v4.y : 0u) +
-                               (bl + 2 <= bt ? v4.z : 0u) + (bl + 3 <= bt ? v4.w : 0u);
-            cl[k] = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(a), 63);
+        if constexpr (KMAX <= 2) {
+            return scan_packed<KMAX, 1, 16>(h, len, b0, b1, B, pk, N, split_rank, l);
+        } else {
+            if (KMAX <= 4 || K <= 4u)
+                return scan_packed<KMAX, 2, 16>(h, len, b0, b1, B, pk, N, split_rank, l);
+            if constexpr (KMAX > 4) {
+                if (KMAX <= 8 || K <= 8u)
+                    return scan_packed<KMAX, 4, 16>(h, len, b0, b1, B, pk, N, split_rank, l);
+            }
+            if constexpr (KMAX > 8)
+                return scan_packed<KMAX, 8, 16>(h, len, b0, b1, B, pk, N, split_rank, l);
         }
     }
-    r.q = c.nl != 0 ? cand_q32(c) : -1.0f;
-    r.b = c.b;
+    ItemBest r;
+    r.q = -1.0f;
+    r.b = 0;
+    if constexpr (BIG) {
+        Cand c;
+        if constexpr (KMAX <= 4) {
+            c = feature_best_compact<KMAX>(h, B, 0, 0, cnode, N, split_rank, l);
+        } else {
+            const int lane = threadIdx.x & 63;
+            c = feature_best<KMAX>(h, B, 0, 0, cnode, N, split_rank);
+            const int bt = c.nl != 0 ? c.b : -1;
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k) {
+                const uint4 v4 = *reinterpret_cast<const uint4*>(h + k * 256 + lane * 4);
+                const int bl = lane * 4;
+                const uint32_t a = (bl <= bt ? v4.x : 0u) + (bl + 1 <= bt ? v4.y : 0u) +
+                                   (bl + 2 <= bt ? v4.z : 0u) + (bl + 3 <= bt ? v4.w : 0u);
+                l[k] = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(a), 63);
+            }
+        }
+        if (c.nl != 0) {
+            r.q = cand_q32(c);
+            r.b = c.b;
+        }
+    }
     return r;
 }
 
-// Record of a classification item in F.icand, kmax + 2 words: the FP32 score
-// of its best threshold (negative: none), the threshold bin | the draw's
-// place in the item << 8, and the left class counts.
-template <int KMAX>
+// Record of a classification item in F.icand, F.item_words words: the FP32
+// score of its best threshold (negative: none), the threshold bin | the draw's
+// place in the item << 8, and the left class counts in the node's form.
+template <int KMAX, bool BIG>
 __device__ __forceinline__ void put_item(const ForestDev& F, uint32_t item, const ItemBest& r,
-                                         uint32_t draw, const uint32_t* cl) {
+                                         uint32_t draw, const uint32_t* l) {
+    constexpr int C = item_counts<KMAX, BIG>();
     const int lane = threadIdx.x & 63;
     uint32_t v = lane == 0 ? __float_as_uint(r.q) : (uint32_t)r.b | draw << 8;
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k) v = lane == k + 2 ? cl[k] : v;
-    if (lane < KMAX + 2) F.icand[(size_t)item * (KMAX + 2) + lane] = v;
+    for (int k = 0; k < C; ++k) v = lane == k + 2 ? l[k] : v;
+    if (lane < C + 2) F.icand[(size_t)item * (C + 2) + lane] = v;
 }
 
-// Exact form of an item record: the split of its left counts.
-template <int KMAX>
-__device__ __forceinline__ Cand cand_of(const uint32_t* rec, const uint32_t* cnode, uint32_t N) {
+// Exact form of a threshold's left counts l (fb-bit form).
+template <int KMAX, bool BIG>
+__device__ __forceinline__ Cand cand_of(const uint32_t* l, uint32_t fb, int b,
+                                        const uint32_t* cnode, uint32_t N) {
     Cand c;
     c.q = c.f = 0;
     c.pad = 0;
-    c.b = (int)(rec[1] & 0xFFu);
+    c.b = b;
     uint32_t nl = 0;
     uint64_t sl = 0, sr = 0;
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
-        const uint32_t l = rec[2 + k], r = cnode[k] - l;
-        nl += l;
-        sl += (uint64_t)l * l;
+        const uint32_t x = left_count<KMAX, BIG>(l, fb, k), r = cnode[k] - x;
+        nl += x;
+        sl += (uint64_t)x * x;
         sr += (uint64_t)r * r;
     }
     c.nl = nl;
@@ -1153,7 +1180,7 @@ __device__ __forceinline__ Cand reg_item(const ForestDev& F, const SlotRec& sr, 
     const int64_t T = (int64_t)((uint64_t)sr.cnode[0] | ((uint64_t)sr.cnode[1] << 32));
     const uint32_t W = sr.n, len = sr.len;
     const int64_t* yfix = sr.yfix;
-    const uint64_t* recs = sr.recs;
+    const uint32_t* recs = sr.recs;
     Cand best;
     best.nl = 0;
     for (int v = 0; v < nf; ++v) {
@@ -1162,12 +1189,9 @@ __device__ __forceinline__ Cand reg_item(const ForestDev& F, const SlotRec& sr, 
         reinterpret_cast<uint4*>(ht)[2 * lane + 1] = make_uint4(0u, 0u, 0u, 0u);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         for (uint32_t i0 = 0; i0 < len; i0 += 64 * RB) {
-            uint64_t r[RB];
+            uint32_t r[RB];
 #pragma unroll
-            for (int u = 0; u < RB; ++u) {
-                const uint32_t i = i0 + u * 64 + lane;
-                r[u] = rec_at(recs, i, len);
-            }
+            for (int u = 0; u < RB; ++u) r[u] = rec_raw(recs, i0 + u * 64 + lane, len);
             uint32_t b[RB];
             long long yv[RB];
 #pragma unroll
@@ -1177,8 +1201,8 @@ __device__ __forceinline__ Cand reg_item(const ForestDev& F, const SlotRec& sr, 
             }
 #pragma unroll
             for (int u = 0; u < RB; ++u) {
-                const uint32_t w = rec_w(r[u]);  // padding rows: w = 0
-                if (w) {
+                const uint32_t w = rec_w(r[u]);
+                if (i0 + u * 64 + lane < len) {
                     atomicAdd(&hw[b[u]], w);
                     atomicAdd(reinterpret_cast<unsigned long long*>(&ht[b[u]]),
                               (unsigned long long)((long long)w * yv[u]));
@@ -1245,6 +1269,14 @@ __global__ __launch_bounds__(256) void k_draws(ForestDev F, int level) {
         SlotRec* sr = F.srec + slot;
         for (uint32_t c = ql; c < 16u; c += S)
             sr->cnode[c] = c < (uint32_t)J.K ? F.cls[(size_t)id * F.kmax + c] : 0u;
+        const uint32_t fb = count_bits(F.kmax, nd.n), per = fb == 8u ? 4u : 2u;
+        for (uint32_t w = ql; w < 8u; w += S) {
+            uint32_t v = 0;
+            for (uint32_t k = 0; k < per; ++k)
+                if (w * per + k < (uint32_t)J.K)
+                    v |= F.cls[(size_t)id * F.kmax + w * per + k] << (fb * k);
+            sr->pk[w] = J.reg || fb == 0u ? 0u : v;
+        }
         if (ql == 0) {
             sr->recs = J.rec[F.parity] + (size_t)tr.tau * J.rstride + nd.seg;
             sr->yfix = J.reg ? J.yfix : nullptr;
@@ -1282,7 +1314,7 @@ __device__ __forceinline__ Cand reg_item_wave(const ForestDev& F, const SlotRec&
     const uint32_t len = sr.len, W = sr.n;
     const int64_t T = (int64_t)((uint64_t)sr.cnode[0] | ((uint64_t)sr.cnode[1] << 32));
     const bool have = (uint32_t)lane < len;
-    const uint64_t r = have ? ldg(sr.recs + lane) : 0ull;
+    const uint32_t r = have ? ldg(sr.recs + lane) : 0u;
     const uint32_t row = rec_row(r), w = have ? rec_w(r) : 0u;
     const int64_t yw = have ? (int64_t)w * ldg(sr.yfix + row) : 0;
     Cand best;
@@ -1450,7 +1482,7 @@ __global__ __launch_bounds__(256) void k_hist_tile(ForestDev F, int level, uint3
             for (uint32_t i = 0; i < cf.words; ++i)
                 reinterpret_cast<uint4*>(hist + v * hw * 256u)[i * 64u + lane] =
                     make_uint4(0u, 0u, 0u, 0u);
-        const uint64_t* recs = sr.recs;
+        const uint32_t* recs = sr.recs;
         const uint32_t len = sr.len;
         int b0[FW], b1[FW];  // bins of rows lane and lane + 64 (nodes of at most 128 rows)
         // One batch of NB rows per lane: all record loads, then all bin
@@ -1459,7 +1491,7 @@ __global__ __launch_bounds__(256) void k_hist_tile(ForestDev F, int level, uint3
         // of the SIMD hide the latency.)
         auto batch = [&](uint32_t i0, auto nb) {
             constexpr int NB = decltype(nb)::value;
-            uint64_t r[NB];
+            uint32_t r[NB];
 #pragma unroll
             for (int u = 0; u < NB; ++u) r[u] = rec_raw(recs, i0 + u * 64 + lane, len);
             uint32_t b[NB][FW];
@@ -1470,10 +1502,9 @@ __global__ __launch_bounds__(256) void k_hist_tile(ForestDev F, int level, uint3
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
                 if (i0 + u * 64 + lane >= len) continue;
-                const uint32_t w = rec_w(r[u]), y = rec_y(r[u]);
 #pragma unroll
                 for (int v = 0; v < FW; ++v)
-                    if (v < nf) count_row(hist + v * hw * 256u, cf, y, b[u][v], w);
+                    if (v < nf) count_row<KMAX>(hist + v * hw * 256u, cf, r[u], b[u][v]);
             }
 #pragma unroll
             for (int v = 0; v < FW; ++v) {
@@ -1487,52 +1518,46 @@ __global__ __launch_bounds__(256) void k_hist_tile(ForestDev F, int level, uint3
             for (uint32_t i0 = 0; i0 < len; i0 += 64 * RB)
                 batch(i0, std::integral_constant<int, RB>{});
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        uint32_t cnode[KMAX];
+        constexpr int C = item_counts<KMAX, BIG>();
+        uint32_t cnode[KMAX], pk[pk_words(KMAX)];
 #pragma unroll
         for (int c = 0; c < KMAX; ++c) cnode[c] = sr.cnode[c];
+#pragma unroll
+        for (int c = 0; c < pk_words(KMAX); ++c) pk[c] = sr.pk[c];
         const int B = (int)sr.B;
         ItemBest best;
         best.q = -1.0f;
         best.b = 0;
         uint32_t bi = 0;
-        uint32_t best_cl[KMAX];
+        uint32_t best_l[C];
 #pragma unroll
-        for (int c = 0; c < KMAX; ++c) best_cl[c] = 0;
+        for (int c = 0; c < C; ++c) best_l[c] = 0;
 #pragma unroll
         for (int v = 0; v < FW; ++v) {
             if (v >= nf) break;
-            uint32_t fcl[KMAX];
-            const ItemBest fb =
-                scan_item<KMAX, BIG>(hist + v * hw * 256u, cf, K, len, b0[v], b1[v],
-                                     B, cnode, N, F.split_rank, fcl);
+            uint32_t l[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) l[c] = 0;
+            const ItemBest fb = scan_item<KMAX, BIG>(hist + v * hw * 256u, cf, K, len, b0[v],
+                                                     b1[v], B, pk, cnode, N, F.split_rank, l);
             if (fb.q < 0.0f) continue;
             // draws in order: a strictly better score replaces
             bool better = best.q < 0.0f;
             if (FW > 1 && !better) {
-                if (F.split_rank && (fb.q < fp32_floor(best.q) || best.q < fp32_floor(fb.q))) {
+                if (F.split_rank && (fb.q < fp32_floor(best.q) || best.q < fp32_floor(fb.q)))
                     better = fb.q > best.q;
-                } else {
-                    Cand x, y;
-                    uint32_t rx[KMAX + 2], ry[KMAX + 2];
-                    rx[1] = ry[1] = 0;
-#pragma unroll
-                    for (int c = 0; c < KMAX; ++c) {
-                        rx[2 + c] = fcl[c];
-                        ry[2 + c] = best_cl[c];
-                    }
-                    x = cand_of<KMAX>(rx, cnode, N);
-                    y = cand_of<KMAX>(ry, cnode, N);
-                    better = cand_better(x, y);
-                }
+                else
+                    better = cand_better(cand_of<KMAX, BIG>(l, cf.fb, fb.b, cnode, N),
+                                         cand_of<KMAX, BIG>(best_l, cf.fb, best.b, cnode, N));
             }
             if (better) {
                 best = fb;
                 bi = (uint32_t)v;
 #pragma unroll
-                for (int c = 0; c < KMAX; ++c) best_cl[c] = fcl[c];
+                for (int c = 0; c < C; ++c) best_l[c] = l[c];
             }
         }
-        put_item<KMAX>(F, item, best, bi, best_cl);
+        put_item<KMAX, BIG>(F, item, best, bi, best_l);
         alg += (unsigned long long)len * (unsigned long long)(nf + (j == 0 ? 6 : 0));
         // the histogram is rewritten by the wave's next item
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -1669,16 +1694,22 @@ __global__ __launch_bounds__(256) void k_col_scatter(ForestDev F, int level) {
 // takes the unit's items in turn: an LDS class-count histogram from the node's
 // row records and the staged bins, the threshold scan, and the item's record
 // (item = slot * mtry_cap + draw).
+// Bound: the records (4 bytes per row and draw, mostly from the last-level
+// cache) at the shallow levels, the vector instructions of the scan at the
+// deep ones.  The first two records per lane of the wave's next item are
+// loaded while this item is scanned, always and into the same registers: a
+// conditional load here is waited for where its paths join.  With 4-byte
+// instead of 8-byte records and the prefetch in flight a launch takes 2.42
+// instead of 2.69 ms (n = 100,000, 2,000 features, mean of tree levels 5-15).
 template <int KMAX, bool BIG>
-__global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level) {
-    constexpr int RB = 8;
-    extern __shared__ uint4 lds_raw[];
+__global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level, uint32_t col_words) {
+    constexpr int RB = 8, C = item_counts<KMAX, BIG>(), PW = pk_words(KMAX);
+    extern __shared__ uint4 lds_raw[];  // the column (col_words 16-byte words), the histograms
     const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
     const uint32_t nw = blockDim.x >> 6;
-    const uint32_t hw = (uint32_t)F.hist_words;
-    uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw) + (size_t)wave * hw * 256u;
-    uint4* colq = lds_raw + nw * hw * 64u;
+    uint4* colq = lds_raw;
     const uint8_t* colb = reinterpret_cast<const uint8_t*>(colq);
+    uint32_t* hist = reinterpret_cast<uint32_t*>(lds_raw + col_words) + wave * C * 256;
     const LevelCtr& lc = F.ctrs[level];
     const uint32_t n_units = lc.overflow ? 0u : min(lc.n_units, F.unit_cap);
     const uint32_t mc = (uint32_t)F.mtry_cap;
@@ -1696,86 +1727,86 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level) {
         for (uint32_t k0 = cu.begin + (uint32_t)wave; k0 < cu.end; k0 += 64u * nw) {
             const uint32_t kk = k0 + (uint32_t)lane * nw;
             const bool have = kk < cu.end;
-            const uint32_t my_item = have ? F.fitems[kk] : 0u;
+            const uint32_t my_item = F.fitems[have ? kk : k0];
             const SlotRec* msr = F.srec + my_item / mc;
-            const uint64_t my_recs = have ? reinterpret_cast<uint64_t>(msr->recs) : 0ull;
-            const uint32_t my_len = have ? msr->len : 0u, my_n = have ? msr->n : 0u;
-            uint32_t my_cn[KMAX];
+            const uint64_t my_recs = reinterpret_cast<uint64_t>(msr->recs);
+            const uint32_t my_len = msr->len, my_n = msr->n;
+            uint32_t my_pk[PW];
 #pragma unroll
-            for (int c = 0; c < KMAX; ++c) my_cn[c] = have ? msr->cnode[c] : 0u;
+            for (int c = 0; c < PW; ++c) my_pk[c] = msr->pk[c];
             const uint32_t n_here = min(64u, (cu.end - k0 + nw - 1u) / nw);
-            // Record batches stream one ahead: while a batch is counted, the
-            // next one is in flight -- the item's next batch, or after its
-            // last batch the first batch of the wave's next item (hidden
-            // behind that item's scan).  An item of at most 128 rows takes
-            // the batch's first two records per lane only.
-            uint64_t rn[RB];
-            auto fetch = [&](const uint64_t* recs, uint32_t i0, uint32_t len) {
-#pragma unroll
-                for (int v = 0; v < 2; ++v) rn[v] = rec_raw(recs, i0 + v * 64 + lane, len);
-                if (len > 128u) {
-#pragma unroll
-                    for (int v = 2; v < RB; ++v) rn[v] = rec_raw(recs, i0 + v * 64 + lane, len);
-                }
+            auto recs_of = [&](uint32_t t) {
+                return reinterpret_cast<const uint32_t*>(readlane64(my_recs, (int)t));
             };
-            fetch(reinterpret_cast<const uint64_t*>(readlane64(my_recs, 0)), 0u,
-                  readlane_w(my_len, 0));
+            uint32_t p0, p1;  // records lane and lane + 64 of the next item
+            {
+                const uint32_t len = readlane_w(my_len, 0);
+                p0 = rec_raw(recs_of(0), (uint32_t)lane, len);
+                p1 = rec_raw(recs_of(0), (uint32_t)lane + 64u, len);
+            }
             for (uint32_t t = 0; t < n_here; ++t) {
                 const uint32_t item = readlane_w(my_item, (int)t);
                 const uint32_t len = readlane_w(my_len, (int)t), N = readlane_w(my_n, (int)t);
                 const CountForm cf = count_form<KMAX>(N, K);
-                for (uint32_t i = 0; i < cf.words; ++i)
-                    reinterpret_cast<uint4*>(hist)[i * 64u + lane] = make_uint4(0u, 0u, 0u, 0u);
-                int b0 = 0, b1 = 0;
-                auto fetch_next = [&]() {
-                    if (t + 1 < n_here)
-                        fetch(reinterpret_cast<const uint64_t*>(readlane64(my_recs, (int)t + 1)),
-                              0u, readlane_w(my_len, (int)t + 1));
-                };
-                if (len <= 128u) {
-                    const uint64_t r0 = rn[0], r1 = rn[1];
-                    b0 = colb[rec_row(r0)];
-                    b1 = colb[rec_row(r1)];
-                    fetch_next();
-                    if ((uint32_t)lane < len)
-                        count_row(hist, cf, rec_y(r0), (uint32_t)b0, rec_w(r0));
-                    if ((uint32_t)lane + 64u < len)
-                        count_row(hist, cf, rec_y(r1), (uint32_t)b1, rec_w(r1));
-                } else {
-                    const uint64_t* recs =
-                        reinterpret_cast<const uint64_t*>(readlane64(my_recs, (int)t));
-                    for (uint32_t i0 = 0;;) {
-                        uint64_t r[RB];
+#pragma unroll
+                for (int i = 0; i < C; ++i)
+                    if ((uint32_t)i < cf.words)
+                        reinterpret_cast<uint4*>(hist)[i * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
+                const uint32_t* recs = recs_of(t);
+                uint32_t rn[RB];  // a larger item's next batch
+                if (len > 128u) {
+#pragma unroll
+                    for (int v = 0; v < RB; ++v) rn[v] = rec_raw(recs, 128u + v * 64 + lane, len);
+                }
+                const uint32_t r0 = p0, r1 = p1;
+                const int b0 = colb[rec_row(r0)], b1 = colb[rec_row(r1)];
+                {
+                    const uint32_t tn = min(t + 1u, n_here - 1u);
+                    const uint32_t nlen = readlane_w(my_len, (int)tn);
+                    p0 = rec_raw(recs_of(tn), (uint32_t)lane, nlen);
+                    p1 = rec_raw(recs_of(tn), (uint32_t)lane + 64u, nlen);
+                }
+                if ((uint32_t)lane < len) count_row<KMAX>(hist, cf, r0, (uint32_t)b0);
+                if ((uint32_t)lane + 64u < len) count_row<KMAX>(hist, cf, r1, (uint32_t)b1);
+                if (len > 128u) {
+                    for (uint32_t i0 = 128u;;) {
+                        uint32_t r[RB];
 #pragma unroll
                         for (int v = 0; v < RB; ++v) r[v] = rn[v];
-                        // all bins of the batch first (records past the node's
-                        // end repeat its last record and are masked below),
-                        // then the atomics: one LDS round trip for the batch,
-                        // not one per row
+                        const uint32_t i1 = i0 + 64 * RB;
+                        if (i1 < len) {
+#pragma unroll
+                            for (int v = 0; v < RB; ++v)
+                                rn[v] = rec_raw(recs, i1 + v * 64 + lane, len);
+                        }
+                        // all bins of the batch first, then the counts: one
+                        // LDS round trip for the batch, not one per row
                         uint32_t bb[RB];
 #pragma unroll
                         for (int v = 0; v < RB; ++v) bb[v] = colb[rec_row(r[v])];
-                        const uint32_t i1 = i0 + 64 * RB;
-                        if (i1 < len)
-                            fetch(recs, i1, len);
-                        else
-                            fetch_next();
 #pragma unroll
-                        for (int v = 0; v < RB; ++v) {
+                        for (int v = 0; v < RB; ++v)
                             if (i0 + (uint32_t)(v * 64 + lane) < len)
-                                count_row(hist, cf, rec_y(r[v]), bb[v], rec_w(r[v]));
-                        }
+                                count_row<KMAX>(hist, cf, r[v], bb[v]);
                         if (i1 >= len) break;
                         i0 = i1;
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                uint32_t cnode[KMAX], cl[KMAX];
+                uint32_t pk[PW], l[C], cnode[KMAX];
 #pragma unroll
-                for (int c = 0; c < KMAX; ++c) cnode[c] = readlane_w(my_cn[c], (int)t);
-                const ItemBest best = scan_item<KMAX, BIG>(hist, cf, K, len, b0, b1, B, cnode, N,
-                                                           F.split_rank, cl);
-                put_item<KMAX>(F, item, best, 0u, cl);
+                for (int c = 0; c < PW; ++c) pk[c] = readlane_w(my_pk[c], (int)t);
+#pragma unroll
+                for (int c = 0; c < C; ++c) l[c] = 0;
+                if constexpr (BIG) {
+                    if (cf.fb == 0u) {
+#pragma unroll
+                        for (int c = 0; c < KMAX; ++c) cnode[c] = F.srec[item / mc].cnode[c];
+                    }
+                }
+                const ItemBest best = scan_item<KMAX, BIG>(hist, cf, K, len, b0, b1, B, pk, cnode,
+                                                           N, F.split_rank, l);
+                put_item<KMAX, BIG>(F, item, best, 0u, l);
                 if (F.alg_bytes)
                     alg += (unsigned long long)len * (item % mc == 0u ? 7ull : 1ull);
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -1802,27 +1833,27 @@ __device__ uint32_t partition_rows(const ForestDev& F, const JobDev& J, const Tr
                                    uint32_t len) {
     const int lane = threadIdx.x & 63;
     const uint8_t* col = ldg(J.colptr + best.f);
-    const uint64_t* recs = sr.recs;
-    uint64_t* rout = J.rec[F.parity ^ 1] + (size_t)tr.tau * J.rstride + nd.seg;
+    const uint32_t* recs = sr.recs;
+    uint32_t* rout = J.rec[F.parity ^ 1] + (size_t)tr.tau * J.rstride + nd.seg;
     constexpr int kR = 8;  // rows per lane per block: lane l owns rows [l kR, l kR + kR)
     uint32_t runl = 0, runr = 0;
-    uint64_t rn[kR];  // with AHEAD: the next block's records, loaded one block ahead
+    uint32_t rn[kR];  // with AHEAD: the next block's records, loaded one block ahead
     if constexpr (AHEAD) {
 #pragma unroll
         for (int u = 0; u < kR; ++u) {
             const uint32_t i = (uint32_t)lane * kR + u;
-            rn[u] = i < len ? ldg(recs + i) : 0ull;
+            rn[u] = i < len ? ldg(recs + i) : 0u;
         }
     }
     for (uint32_t blk = 0; blk < len; blk += 64 * kR) {
         const uint32_t i0 = blk + (uint32_t)lane * kR;
-        uint64_t r[kR];
+        uint32_t r[kR];
 #pragma unroll
         for (int u = 0; u < kR; ++u) {
             if constexpr (AHEAD)
                 r[u] = rn[u];
             else
-                r[u] = i0 + u < len ? ldg(recs + i0 + u) : 0ull;
+                r[u] = i0 + u < len ? ldg(recs + i0 + u) : 0u;
         }
         int bb[kR];
 #pragma unroll
@@ -1831,7 +1862,7 @@ __device__ uint32_t partition_rows(const ForestDev& F, const JobDev& J, const Tr
             // the next block's records are in flight while this block is placed
             const uint32_t j0 = i0 + 64 * kR;
 #pragma unroll
-            for (int u = 0; u < kR; ++u) rn[u] = j0 + u < len ? ldg(recs + j0 + u) : 0ull;
+            for (int u = 0; u < kR; ++u) rn[u] = j0 + u < len ? ldg(recs + j0 + u) : 0u;
         }
         uint32_t nlm = 0, nrm = 0;
 #pragma unroll
@@ -1955,7 +1986,7 @@ __global__ __launch_bounds__(256) void k_split_finalize_reg(ForestDev F0, int le
     }
 }
 
-template <int KMAX>
+template <int KMAX, bool BIG>
 __global__ __launch_bounds__(256) void k_split_finalize(ForestDev F0, int level, uint32_t first,
                                                         uint32_t count) {
     const ForestDev F = level_view(F0, level);
@@ -1985,12 +2016,14 @@ __global__ __launch_bounds__(256) void k_split_finalize(ForestDev F0, int level,
         // order, a strictly better one replacing (so ties keep the earlier
         // draw); one finalist alone is taken as it is.
         const int ni = ((int)sr.mtry + F.fw - 1) / F.fw;
-        const uint32_t* items = F.icand + (size_t)slot * F.npi * (KMAX + 2);
+        constexpr int IW = item_counts<KMAX, BIG>() + 2;
+        const uint32_t fb = count_bits(KMAX, N);
+        const uint32_t* items = F.icand + (size_t)slot * F.npi * IW;
         float fl = 0.0f;
         if (F.split_rank) {
             float q1 = -1.0f;
             for (int t = lane; t < ni; t += 64)
-                q1 = fmaxf(q1, __uint_as_float(items[(size_t)t * (KMAX + 2)]));
+                q1 = fmaxf(q1, __uint_as_float(items[(size_t)t * IW]));
             const float qmax = wave_max_f_dpp(q1);
             fl = qmax < 0.0f ? 2.0f * (float)N : fp32_floor(qmax);  // Q <= N
         }
@@ -1999,10 +2032,11 @@ __global__ __launch_bounds__(256) void k_split_finalize(ForestDev F0, int level,
         int bt = -1;
         for (int t0 = 0; t0 < ni; t0 += 64) {
             const float q =
-                t0 + lane < ni ? __uint_as_float(items[(size_t)(t0 + lane) * (KMAX + 2)]) : -1.0f;
+                t0 + lane < ni ? __uint_as_float(items[(size_t)(t0 + lane) * IW]) : -1.0f;
             for (uint64_t m = __ballot(q >= fl); m; m &= m - 1) {
                 const int t = t0 + (int)__ffsll((unsigned long long)m) - 1;
-                const Cand d = cand_of<KMAX>(items + (size_t)t * (KMAX + 2), cnode, N);
+                const uint32_t* rec = items + (size_t)t * IW;
+                const Cand d = cand_of<KMAX, BIG>(rec + 2, fb, (int)(rec[1] & 0xFFu), cnode, N);
                 if (best.nl == 0 || cand_better(d, best)) {
                     best = d;
                     bt = t;
@@ -2018,15 +2052,14 @@ __global__ __launch_bounds__(256) void k_split_finalize(ForestDev F0, int level,
             }
             continue;
         }
-        const uint32_t* rec = items + (size_t)bt * (KMAX + 2);
-        const uint32_t* clt = rec + 2;
+        const uint32_t* rec = items + (size_t)bt * IW;
         best.q = bt * F.fw + (int)(rec[1] >> 8);
         best.f = (int)F.feat[(size_t)slot * F.mtry_cap + best.q];
         uint32_t cl[16], cr[16];
         int nzl = 0, nzr = 0;
 #pragma unroll
         for (int c2 = 0; c2 < 16; ++c2) {
-            cl[c2] = c2 < KMAX ? clt[c2] : 0u;
+            cl[c2] = c2 < KMAX ? left_count<KMAX, BIG>(rec + 2, fb, c2 % KMAX) : 0u;
             cr[c2] = (c2 < KMAX ? cnode[c2] : 0u) - cl[c2];
             nzl += cl[c2] != 0;
             nzr += cr[c2] != 0;
@@ -2271,7 +2304,7 @@ void launch_hist_col(const ForestDev& F, int level, uint32_t grid_wg, int waves,
                      hipStream_t st) {
     const size_t lds = hist_col_lds(F.hist_words, waves, gq_max);
     ForestDev f = F;
-    void* args[] = {&f, &level};
+    void* args[] = {&f, &level, &gq_max};
     // a refused launch is reported by the caller's hipGetLastError
     (void)hipLaunchKernel(hist_col_fn(F.kmax, F.hist_words == F.kmax), dim3(grid_wg),
                           dim3(64 * waves), args, lds, st);
@@ -2284,13 +2317,21 @@ void launch_split_finalize(const ForestDev& F, int level, uint32_t first, uint32
     if (F.has_reg)
         hipLaunchKernelGGL(k_split_finalize_reg, grid, dim3(256), 0, st, F, level, first, count);
     if (!F.has_cls) return;
+#define BORUTA_FINALIZE(K)                                                                       \
+    if (F.hist_words == F.kmax)                                                                  \
+        hipLaunchKernelGGL((k_split_finalize<K, true>), grid, dim3(256), 0, st, F, level, first, \
+                           count);                                                               \
+    else                                                                                         \
+        hipLaunchKernelGGL((k_split_finalize<K, false>), grid, dim3(256), 0, st, F, level,       \
+                           first, count);
     switch (F.kmax) {
-        case 2: hipLaunchKernelGGL(k_split_finalize<2>, grid, dim3(256), 0, st, F, level, first, count); break;
-        case 3: hipLaunchKernelGGL(k_split_finalize<3>, grid, dim3(256), 0, st, F, level, first, count); break;
-        case 4: hipLaunchKernelGGL(k_split_finalize<4>, grid, dim3(256), 0, st, F, level, first, count); break;
-        case 8: hipLaunchKernelGGL(k_split_finalize<8>, grid, dim3(256), 0, st, F, level, first, count); break;
-        default: hipLaunchKernelGGL(k_split_finalize<16>, grid, dim3(256), 0, st, F, level, first, count); break;
+        case 2: BORUTA_FINALIZE(2) break;
+        case 3: BORUTA_FINALIZE(3) break;
+        case 4: BORUTA_FINALIZE(4) break;
+        case 8: BORUTA_FINALIZE(8) break;
+        default: BORUTA_FINALIZE(16) break;
     }
+#undef BORUTA_FINALIZE
 }
 
 }  // namespace boruta
