@@ -260,9 +260,8 @@ int boruta_fit_ex(const float* X, const int32_t* y, int64_t n, int64_t p, int32_
  * 2 bits(R + 1) - 63) and s_kl = max(0, bits(n) + 2 bits(R + 1) - 63) keep
  * every sum within 64 bits.  Arguments and outputs otherwise as boruta_fit_ex;
  * in a trace a node's weighted count is W, a leaf's class column holds its
- * prediction floor(T / W), and the OOB-correct count is 0.  Regression nodes
- * always take the histogram path (small_rows does not apply), and a batch
- * with a regression job keeps every tree level node-major (col_level does not
+ * prediction floor(T / W), and the OOB-correct count is 0.  A batch with a
+ * regression job keeps every tree level node-major (col_level does not
  * apply). */
 int boruta_fit_regression(const float* X, const float* y, int64_t n, int64_t p, int32_t n_trees,
                           int32_t max_depth, int32_t mtry, int32_t importance_mode,

@@ -459,10 +459,8 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         // every searched node reserves a pair of child slots (a leaf leaves its
         // pair unused), so the pool holds up to twice the nodes of the trees
         node_cap += T + 2 * T * per_tree_nodes;
-        // a regression node of two or more distinct rows always takes the
-        // histogram path
-        const uint64_t large_per_tree = s.yr ? (uint64_t)(s.n + 1) / 2
-                                             : (uint64_t)(s.n + o.small_rows) / (o.small_rows + 1);
+        const uint64_t large_per_tree =
+            (uint64_t)(s.n + o.small_rows) / (uint64_t)(o.small_rows + 1);
         slot_cap += T * large_per_tree;
         small_cap += T * (uint64_t)((s.n + 1) / 2);
         pl.max_sha = std::max(pl.max_sha, j.max_sha);
@@ -1044,21 +1042,16 @@ void Engine::enqueue_iteration() {
         // nodes, child pairs, row segments and kinds entries: without kernel
         // statistics the small-node launch runs on a second stream, beside
         // the large-node kernels, and rejoins before the lists are built.
-        // Regression nodes all take the histogram path: a plan of regression
-        // jobs alone has no small-node work.
-        const bool fork = !stats && side != nullptr && pl.has_cls;
+        const bool fork = !stats && side != nullptr;
         hipStream_t ss = st;
         if (fork) {
             HIPC(hipEventRecord(ev_fork, st));
             HIPC(hipStreamWaitEvent(side, ev_fork, 0));
             ss = side;
         }
-        size_t h = 0;
-        if (pl.has_cls) {
-            h = clock.begin(stats ? &stats->hist_small : nullptr, ss);
-            launch_split_small(F, d, 0, kAll, g_small, ss);
-            clock.end(h, ss);
-        }
+        size_t h = clock.begin(stats ? &stats->hist_small : nullptr, ss);
+        launch_split_small(F, d, 0, kAll, g_small, ss);
+        clock.end(h, ss);
         if (fork) HIPC(hipEventRecord(ev_join, side));
         const bool col = d >= pl.col_level;
         if (col) {

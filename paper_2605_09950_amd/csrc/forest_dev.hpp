@@ -74,6 +74,32 @@ __device__ __forceinline__ float wave_max_f_dpp(float f) {
     return __int_as_float(__builtin_amdgcn_readlane(v, 63));
 }
 
+// The same for FP64 scores that are -1 or not negative.
+__device__ __forceinline__ double dpp_f64(double v, int sel) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
+    switch (sel) {
+#define BORUTA_DPP(S, CTRL, ROWS)                                              \
+    case S:                                                                    \
+        lo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);      \
+        hi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);      \
+        break;
+        BORUTA_DPP(0, 0x111, 0xf)
+        BORUTA_DPP(1, 0x112, 0xf)
+        BORUTA_DPP(2, 0x114, 0xf)
+        BORUTA_DPP(3, 0x118, 0xf)
+        BORUTA_DPP(4, 0x142, 0xa)
+        BORUTA_DPP(5, 0x143, 0xc)
+#undef BORUTA_DPP
+    }
+    return __builtin_bit_cast(double, (uint64_t)(uint32_t)lo | (uint64_t)(uint32_t)hi << 32);
+}
+__device__ __forceinline__ double wave_max_f64_dpp(double v) {
+#pragma unroll
+    for (int s = 0; s < 6; ++s) v = fmax(v, dpp_f64(v, s));
+    return __builtin_bit_cast(double, readlane64(__builtin_bit_cast(uint64_t, v), 63));
+}
+
 // Minimum over the wave, as a wave-uniform value.
 __device__ __forceinline__ uint32_t wave_min_u_dpp(uint32_t v) {
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false));
@@ -403,8 +429,8 @@ __device__ __forceinline__ ForestDev level_view(const ForestDev& F, int level) {
 
 // Write a new node record -- a leaf until a split search turns it into a
 // split -- and return what it needs next: nothing (final leaf: maximum depth,
-// fewer than two distinct rows or a single class), the wave path (<= 64
-// distinct rows) or the tiled histogram path.
+// fewer than two row records or a single class), the wave path (up to
+// small_rows records) or the histogram path.
 __device__ inline int write_node(const ForestDev& F, const JobDev& J, uint32_t idx, uint32_t tree,
                                  uint32_t heap, uint32_t seg, uint32_t len, uint32_t n,
                                  uint32_t depth, const uint32_t* counts) {
@@ -433,9 +459,9 @@ __device__ inline int write_node(const ForestDev& F, const JobDev& J, uint32_t i
 
 // Regression node: weight W and weighted target sum T (kept in the node's
 // first two class words); it is a final leaf at the maximum depth or with
-// fewer than two distinct rows, else it takes the histogram path (its split
-// search ranks exact weighted target sums, which the wave path does not keep).
-// A leaf's prediction floor(T / W) is read from these fields.
+// fewer than two row records, else it takes the wave path (up to small_rows
+// records) or the histogram path.  A leaf's prediction floor(T / W) is read
+// from these fields.
 __device__ inline int write_node_reg(const ForestDev& F, const JobDev& J, uint32_t idx,
                                      uint32_t tree, uint32_t heap, uint32_t seg, uint32_t len,
                                      uint32_t W, int64_t T, uint32_t depth) {
@@ -455,7 +481,7 @@ __device__ inline int write_node_reg(const ForestDev& F, const JobDev& J, uint32
     F.nodes[idx] = nd;
     F.ngain[idx] = 0;
     if ((int)depth >= J.D || len < 2) return kLeaf;
-    return kLarge;
+    return len <= F.small_rows ? kSmall : kLarge;
 }
 
 // Weighted target sum of a regression node from its class words.

@@ -479,6 +479,7 @@ __global__ __launch_bounds__(256) void k_split_small(ForestDev F0, int level, ui
         const NodeDev nd = F.nodes[id];
         const TreeDev tr = F.trees[nd.tree];
         JobDev& J = F.jobs[tr.job];
+        if (F.has_reg && J.reg) continue;  // k_split_small_reg
         if (WORDS == 1 || J.K <= 4)
             small_node<1>(F, id, nd, tr, J, o, lds);
         else if (WORDS == 2 || J.K <= 8)
@@ -490,6 +491,228 @@ __global__ __launch_bounds__(256) void k_split_small(ForestDev F0, int level, ui
         alg += o.alg;
     }
     // one atomic per wave for the statistics
+    if (F.alg_bytes && lane == 0 && alg)
+        atomicAdd((unsigned long long*)&F.alg_bytes[kAlgWords + ((blockIdx.x * 4u + wave) &
+                                                                 (kAlgWords - 1))], alg);
+}
+
+// Small regression nodes, as small_node: a segment's lanes hold the rows'
+// weights and weighted targets as FP64 integers (at most 64 records of weight
+// 15 and |y_fix| < 2^38: sums below 2^49, exact), and the left sums of the
+// threshold at a lane's own bin come from an all-pairs sum over the segment,
+// two fused multiply-adds per row.  Thresholds are ranked by reg_score and
+// compared exactly (reg_small_better) within the FP64 margin, except those
+// that leave the same or the mirrored sums: an exact tie.
+// These nodes took one wavefront and one 256-bin, 64-bit histogram scan per
+// drawn feature: of the 3.75 ms of an iteration at n = 10,000, 50 features, 200
+// trees of depth 12, the histogram, partition and draw kernels spent 2.7 ms on
+// the levels whose nodes have a few dozen rows (at the deepest level 662 us of
+// histograms, 165 of partitions and 66 of draws became 221, 15 and 99 beside 182
+// for the nodes that stay).
+constexpr uint32_t kSmallRegLds = kDrawTab / 2 + 64 * 4;  // words per wave
+
+__device__ __forceinline__ void small_node_reg(const ForestDev& F, uint32_t id, const NodeDev& nd,
+                                               const TreeDev& tr, JobDev& J, SmallOut& out,
+                                               uint32_t* lds) {
+    uint16_t* tab = reinterpret_cast<uint16_t*>(lds);
+    double2* rows = reinterpret_cast<double2*>(lds + kDrawTab / 2);  // [64] (w, w y)
+    const int lane = threadIdx.x & 63;
+    const int B = J.B, mtry = J.mtry;
+    const size_t tbase = (size_t)tr.tau * J.rstride + nd.seg;
+    const uint32_t* rin = J.rec[F.parity] + tbase;
+    uint32_t* rout = J.rec[F.parity ^ 1] + tbase;
+    const int len = (int)uniform(nd.len);
+    int W = 2;
+    while (W < len) W <<= 1;
+    const int G = 64 / W;
+    const int seg = lane / W, i = lane & (W - 1);
+    const bool valid = i < len;
+    const uint32_t rec = valid ? ldg(rin + i) : 0u;
+    const uint32_t row = rec_row(rec), wt = rec_w(rec);
+    const int64_t Ti = node_tsum(F.cls, F.kmax, id);
+    const uint32_t Wi = nd.n;
+    const double T = (double)Ti, Wn = (double)Wi;
+    const KeyedPerm P = make_perm(J.seed_lo, J.seed_hi, kMtry, (uint32_t)J.t, (uint32_t)tr.tau,
+                                  nd.heap, 0u, (uint64_t)J.p_w);
+    const bool use_tab = (P.rounds << P.half) <= kDrawTab;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the previous node's reads
+    if (use_tab) {
+        for (uint32_t e = (uint32_t)lane; e < (P.rounds << P.half); e += 64u)
+            tab[e] = (uint16_t)perm_round(P, e >> P.half, e & P.mask);
+    }
+    {
+        const bool mine = seg == 0 && valid;
+        const int64_t yw = mine ? (int64_t)wt * ldg(J.yfix + row) : 0;
+        rows[lane] = double2{mine ? (double)wt : 0.0, (double)yw};
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    bool has = false;
+    double lq = -1.0, lt = 0.0, lw = 0.0;  // the lane's best: score, left sums
+    int ld = 0, lb = 0;                    // its draw position and threshold
+    const bool rank = F.split_rank != 0;
+    const int abase = (lane - i) << 2;
+    for (int q0 = 0; q0 < mtry; q0 += 64) {
+        const int nq = min(64, mtry - q0);
+        const int myf =
+            lane < nq ? (int)(use_tab ? perm_apply_tab(P, tab, (uint32_t)(q0 + lane))
+                                      : perm_apply(P, (uint32_t)(q0 + lane)))
+                      : 0;
+        const uint32_t myoff =
+            lane < nq ? (uint32_t)((uint64_t)(ldg(J.colptr + myf) - J.colbase) >> 8) : 0u;
+        const int passes = (nq + G - 1) / G;
+        auto gather = [&](int pass) {
+            const int qq = pass * G + seg;
+            const uint32_t off = (uint32_t)__shfl((int)myoff, qq < nq ? qq : 0);
+            return (int)ldg(J.colbase + row + (uint64_t)off * 256u);
+        };
+        int nb = gather(0);
+        for (int pass = 0; pass < passes; ++pass) {
+            const int qq = pass * G + seg;
+            const bool act = valid && qq < nq;
+            const int b = act ? nb : 0x7FFF;
+            nb = gather(pass + 1 < passes ? pass + 1 : pass);
+            double wl = 0.0, tl = 0.0;
+            for (int j0 = 0; j0 < len; j0 += 4) {
+                int bj[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    bj[u] = __builtin_amdgcn_ds_bpermute(abase + ((j0 + u) << 2), b);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double2 r = rows[j0 + u];  // zero past the node's rows
+                    const double m = bj[u] <= b ? 1.0 : 0.0;
+                    wl = __builtin_fma(m, r.x, wl);
+                    tl = __builtin_fma(m, r.y, tl);
+                }
+            }
+            const bool ok = act && b <= B - 2 && wl < Wn;  // wl holds the lane's own row
+            const double qu = reg_score(tl, wl, T, Wn);
+            const double qc = ok ? qu : -1.0;
+            const bool tie = (tl == lt && wl == lw) || (tl == T - lt && wl == Wn - lw);
+            const bool near =
+                ok && has && !tie &&
+                (!rank || (qc >= fp64_floor(lq) && lq >= fp64_floor(qc)));
+            bool better = ok && (!has || (!tie && qc > lq));
+            if (__ballot(near)) {
+                const bool ex = reg_small_better((int64_t)tl, (uint32_t)wl, (int64_t)lt,
+                                                 (uint32_t)lw, Ti, Wi);
+                better = near ? ex : better;
+            }
+            if (better) {
+                has = true;
+                lq = qc;
+                lt = tl;
+                lw = wl;
+                ld = q0 + qq;
+                lb = b;
+            }
+        }
+    }
+    out.alg = (uint64_t)len * (uint64_t)(mtry + 6);
+    // the winner, as in small_node
+    bool fin = has;
+    if (rank) {
+        const double qmax = wave_max_f64_dpp(lq);
+        fin = has && lq >= fp64_floor(qmax);
+    }
+    const uint64_t fm = __ballot(fin);
+    int win = -1;
+    if (fm) {
+        win = (int)__ffsll((unsigned long long)fm) - 1;
+        auto lane_f64 = [&](double v, int l) {
+            return __builtin_bit_cast(double, readlane64(__builtin_bit_cast(uint64_t, v), l));
+        };
+        double bt = lane_f64(lt, win), bw = lane_f64(lw, win);
+        const bool tie = (lt == bt && lw == bw) || (lt == T - bt && lw == Wn - bw);
+        if (!__ballot(fin && !tie)) {
+            const uint32_t dmin = wave_min_u_dpp(fin ? (uint32_t)ld : 0xFFFFFFFFu);
+            const uint32_t bmin =
+                wave_min_u_dpp(fin && (uint32_t)ld == dmin ? (uint32_t)lb : 0xFFFFFFFFu);
+            win = (int)__ffsll((unsigned long long)__ballot(fin && (uint32_t)ld == dmin &&
+                                                            (uint32_t)lb == bmin)) - 1;
+        } else {
+            for (uint64_t m = fm & (fm - 1); m; m &= m - 1) {
+                const int l = (int)__ffsll((unsigned long long)m) - 1;
+                const double ct = lane_f64(lt, l), cw = lane_f64(lw, l);
+                const int d0 = __builtin_amdgcn_readlane(ld, win),
+                          d1 = __builtin_amdgcn_readlane(ld, l);
+                const int b0 = __builtin_amdgcn_readlane(lb, win),
+                          b1 = __builtin_amdgcn_readlane(lb, l);
+                const bool up = reg_small_better((int64_t)ct, (uint32_t)cw, (int64_t)bt,
+                                                 (uint32_t)bw, Ti, Wi);
+                const bool down = reg_small_better((int64_t)bt, (uint32_t)bw, (int64_t)ct,
+                                                   (uint32_t)cw, Ti, Wi);
+                if (up || (!down && (d1 < d0 || (d1 == d0 && b1 < b0)))) {
+                    win = l;
+                    bt = ct;
+                    bw = cw;
+                }
+            }
+        }
+    }
+    Cand best;
+    best.nl = 0;
+    if (win >= 0) {
+        const int64_t tl =
+            (int64_t)__builtin_bit_cast(double, readlane64(__builtin_bit_cast(uint64_t, lt), win));
+        best.nl = (uint32_t)__builtin_bit_cast(
+            double, readlane64(__builtin_bit_cast(uint64_t, lw), win));
+        best.nr = Wi - best.nl;
+        best.q = __builtin_amdgcn_readlane(ld, win);
+        best.b = __builtin_amdgcn_readlane(lb, win);
+        best.pad = 0;
+        best.sl = (uint64_t)tl;
+        best.sr = (uint64_t)(Ti - tl);
+        best.f = (int)(use_tab ? perm_apply_tab(P, tab, (uint32_t)best.q)
+                               : perm_apply(P, (uint32_t)best.q));
+    }
+    if (best.nl == 0 || reg_gap(best) == 0) {  // no decrease: stays the leaf it was created as
+        if (lane == 0) mark_unused_pair(F, out.child);
+        return;
+    }
+    const bool mine = seg == 0 && valid;
+    const uint8_t* col = ldg(J.colptr + best.f);
+    const bool left = mine && (int)ldg(col + row) <= best.b;
+    const uint64_t lm = __ballot(left), vm = __ballot(mine);
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const uint32_t nl_rows = (uint32_t)__popcll(lm);
+    if (mine) {
+        const uint32_t pos = left ? (uint32_t)__popcll(lm & below)
+                                  : nl_rows + (uint32_t)__popcll(vm & ~lm & below);
+        rout[pos] = rec;
+    }
+    if (lane == 0)
+        split_node_reg(F, J, tr, id, nd, best, nl_rows, reg_gain_fix(best, J.s_gain), out.child,
+                       out.kinds);
+}
+
+// The regression nodes of a level's small-node list (k_split_small takes the
+// others).
+__global__ __launch_bounds__(256) void k_split_small_reg(ForestDev F0, int level, uint32_t first,
+                                                         uint32_t count) {
+    const ForestDev F = level_view(F0, level);
+    if (count == 0xFFFFFFFFu) {
+        first = 0;
+        count = level_small(F0, level);
+    }
+    extern __shared__ uint4 lds_raw[];  // [4][kSmallRegLds]
+    const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
+    uint32_t* lds = reinterpret_cast<uint32_t*>(lds_raw) + wave * kSmallRegLds;
+    unsigned long long alg = 0;
+    for (uint32_t li = blockIdx.x * 4u + (uint32_t)wave; li < count; li += gridDim.x * 4u) {
+        SmallOut o;
+        o.kinds[0] = o.kinds[1] = kLeaf;
+        o.child = F.next_base + 2u * (first + li);
+        o.alg = 0;
+        const uint32_t id = uniform(F.small_in[first + li]);
+        const NodeDev nd = F.nodes[id];
+        const TreeDev tr = F.trees[nd.tree];
+        JobDev& J = F.jobs[tr.job];
+        if (!J.reg) continue;
+        small_node_reg(F, id, nd, tr, J, o, lds);
+        if (lane == 0) F.kinds[first + li] = (uint8_t)(o.kinds[0] | o.kinds[1] << 2);
+        alg += o.alg;
+    }
     if (F.alg_bytes && lane == 0 && alg)
         atomicAdd((unsigned long long*)&F.alg_bytes[kAlgWords + ((blockIdx.x * 4u + wave) &
                                                                  (kAlgWords - 1))], alg);
@@ -1298,81 +1521,6 @@ __global__ __launch_bounds__(256) void k_draws(ForestDev F, int level) {
 // spread a wave's atomics over the banks by bin), scans each feature and
 // writes the item's best candidate and its left class counts.  No barriers:
 // the four waves of a workgroup are independent.
-// Regression item of a node with at most kRegWaveRows distinct rows: lane i
-// holds row i (its weight w_i and w_i y_fix_i), and for each drawn feature
-// the left sums of the threshold at lane i's bin, (W_L, T_L) = the sums of
-// (w_j, w_j y_fix_j) over the rows j with bin <= b_i, come from one pass over
-// the rows with their values broadcast -- no histogram to clear and scan.
-// The thresholds scored are the occupied bins, as in reg_feature_best, and
-// ranking, margin and tie-breaks are the same, so both give one candidate.
-constexpr uint32_t kRegWaveRows = 24;
-
-__device__ __forceinline__ Cand reg_item_wave(const ForestDev& F, const SlotRec& sr, int q0,
-                                              int nf, const int* fq,
-                                              const uint8_t* const* col) {
-    const int lane = threadIdx.x & 63;
-    const uint32_t len = sr.len, W = sr.n;
-    const int64_t T = (int64_t)((uint64_t)sr.cnode[0] | ((uint64_t)sr.cnode[1] << 32));
-    const bool have = (uint32_t)lane < len;
-    const uint32_t r = have ? ldg(sr.recs + lane) : 0u;
-    const uint32_t row = rec_row(r), w = have ? rec_w(r) : 0u;
-    const int64_t yw = have ? (int64_t)w * ldg(sr.yfix + row) : 0;
-    Cand best;
-    best.nl = 0;
-    for (int v = 0; v < nf; ++v) {
-        const int b = have ? (int)ldg(col[v] + row) : 0x7FFF;
-        uint32_t wl = 0;
-        int64_t tl = 0;
-        for (uint32_t j = 0; j < len; ++j) {
-            const int bj = __builtin_amdgcn_readlane(b, (int)j);
-            const uint32_t wj = readlane_w(w, (int)j);
-            const int64_t tj = (int64_t)readlane64((uint64_t)yw, (int)j);
-            if (bj <= b) {
-                wl += wj;
-                tl += tj;
-            }
-        }
-        Cand c;
-        c.q = q0 + v;
-        c.f = fq[v];
-        c.b = b;
-        c.pad = 0;
-        const bool ok = have && b <= (int)sr.B - 2 && wl != W;  // wl >= w_i > 0
-        c.nl = ok ? wl : 0u;
-        c.nr = W - wl;
-        c.sl = (uint64_t)tl;
-        c.sr = (uint64_t)(T - tl);
-        const double qc = ok ? reg_q64(c) : -1.0;
-        double qmax = qc;
-#pragma unroll
-        for (int m = 1; m < 64; m <<= 1) {
-            const double o = __shfl_xor(qmax, m);
-            qmax = o > qmax ? o : qmax;
-        }
-        if (qmax < 0.0) continue;
-        const double floor64 = F.split_rank ? fp64_floor(qmax) : 0.0;
-        if (!(ok && qc >= floor64)) {
-            c.nl = 0;
-            c.b = 0x7FFFFFFF;
-        }
-        const unsigned long long finm = __ballot(c.nl != 0);
-        Cand fb;
-        if (__popcll(finm) == 1) {
-            fb = shfl_cand(c, (int)__ffsll(finm) - 1);
-        } else {
-#pragma unroll
-            for (int m = 1; m < 64; m <<= 1) {
-                const Cand o = shfl_xor_cand(c, m);
-                if (reg_wins_same_feature(o, c)) c = o;
-            }
-            fb = c;
-        }
-        // draws in order: a strictly better score replaces
-        if (fb.nl != 0 && (best.nl == 0 || reg_better(fb, best))) best = fb;
-    }
-    return best;
-}
-
 // Work of a level for the node-major histogram kernels: node slots [0, n)
 // with npi items each.  Workgroup b takes the slots congruent to b mod 8 (the
 // grid is a multiple of 8), and its waves walk those slots' items in order,
@@ -1440,8 +1588,7 @@ __global__ __launch_bounds__(256) void k_hist_reg(ForestDev F, int level, uint32
             fq[u] = (int)drawn[u < nf ? u : 0];
             col[u] = dcol[u < nf ? u : 0];
         }
-        const Cand best = sr.len <= kRegWaveRows ? reg_item_wave(F, sr, q0, nf, fq, col)
-                                                 : reg_item<RB>(F, sr, q0, nf, fq, col, hist);
+        const Cand best = reg_item<RB>(F, sr, q0, nf, fq, col, hist);
         if (lane == 0) F.cand[item] = best;
         alg += (unsigned long long)sr.len * (unsigned long long)(nf + (j == 0 ? 6 : 0));
     }
@@ -2194,6 +2341,11 @@ void launch_split_small(const ForestDev& F, int level, uint32_t first, uint32_t 
                         uint32_t grid_wg, hipStream_t st) {
     if (!count) return;
     const dim3 grid(grid_wg);
+    if (F.has_reg)
+        hipLaunchKernelGGL(k_split_small_reg, grid, dim3(256),
+                           (size_t)4 * kSmallRegLds * sizeof(uint32_t), st, F, level, first,
+                           count);
+    if (!F.has_cls) return;
     const int words = F.kmax <= 4 ? 1 : (F.kmax <= 8 ? 2 : 4);
     const size_t lds = (size_t)4 * small_lds_words(words) * sizeof(uint32_t);
     switch (words) {

@@ -169,10 +169,39 @@ __device__ inline uint64_t udiv256_128_est(const U256& num, u128 den) {
     return udiv256_128(num, den);
 }
 
+// floor(num / den) for num < 2^126, 0 < den < 2^63 and a quotient below 2^63:
+// an FP64 estimate, one FP64 correction from the exact remainder, then exact
+// +-1 steps (the correction leaves at most a few units).
+__device__ __forceinline__ uint64_t udiv128_63(u128 num, uint64_t den) {
+    const double dd = (double)den;
+    double qd = u128_to_double(num) / dd;
+    qd = qd < 9.2e18 ? qd : 9.2e18;
+    uint64_t q = (uint64_t)qd;
+    u128 prod = (u128)q * den;
+    const bool over = prod > num;
+    const uint64_t c = (uint64_t)(u128_to_double(over ? prod - num : num - prod) / dd);
+    q = over ? q - c : q + c;
+    prod = (u128)q * den;
+    while (prod > num) {
+        --q;
+        prod -= den;
+    }
+    while (num - prod >= den) {
+        ++q;
+        prod += den;
+    }
+    return q;
+}
+
 // floor(D / 2^s) = floor(g^2 / (W_L W_R W 2^s)); W_L W_R W 2^s < 2^128 and the
-// quotient < 2^63 for the shifts the engine chooses.
+// quotient < 2^63 for the shifts the engine chooses.  In 128 bits where the
+// gap and the denominator are below 2^63 (nodes of few rows), else in 256.
 __device__ inline uint64_t reg_gain_fix(const Cand& c, int s) {
     const u128 g = reg_gap(c);
+    const u128 d3 = (u128)((uint64_t)c.nl * c.nr) * (c.nl + c.nr);
+    if ((uint64_t)(g >> 63) == 0 && s < 63 && (uint64_t)(d3 >> (63 - s)) == 0 &&
+        (uint64_t)(d3 >> 64) == 0)
+        return udiv128_63(g * g, (uint64_t)d3 << s);
     const u128 den = ((u128)((uint64_t)c.nl * c.nr) * (c.nl + c.nr)) << s;
     return udiv256_128_est(mul128_full(g, g), den);
 }
@@ -181,6 +210,39 @@ __device__ inline uint64_t reg_gain_fix(const Cand& c, int s) {
 __device__ __forceinline__ int64_t reg_pred(int64_t T, uint32_t W) {
     const int64_t q = T / (int64_t)W;
     return (q * (int64_t)W != T && T < 0) ? q - 1 : q;
+}
+
+// FP64 score of a threshold of a node whose target sums are integers below
+// 2^53 in FP64 (T, left sum TL; weights W, WL): g^2 / (W_L W_R), g = T_L W -
+// T W_L.  The products' rounding errors are carried along (two-product), so g
+// is within 2^-52 relatively even where they cancel: the first fused
+// difference is exact below 2^53, and far above the second term otherwise.  The
+// reciprocal (hardware estimate, two Newton steps) is within a few units:
+// within 2^-48 of the exact score in all.
+__device__ __forceinline__ double reg_score(double TL, double WL, double T, double W) {
+    const double ph = T * WL;
+    const double pl = __builtin_fma(T, WL, -ph);
+    const double g = __builtin_fma(TL, W, -ph) - pl;
+    const double d = WL * (W - WL);
+    double r = __builtin_amdgcn_rcp(d);
+    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    return g * g * r;
+}
+
+// D_a > D_b exactly for thresholds of a node of weight W < 2^11 and |T| < 2^49:
+// gaps below 2^61, g^2 W_L W_R in 192 bits.
+__device__ __forceinline__ bool reg_small_better(int64_t TLa, uint32_t WLa, int64_t TLb,
+                                                 uint32_t WLb, int64_t T, uint32_t W) {
+    const int64_t ga = TLa * (int64_t)W - T * (int64_t)WLa;
+    const int64_t gb = TLb * (int64_t)W - T * (int64_t)WLb;
+    const uint64_t xa = (uint64_t)(ga < 0 ? -ga : ga), xb = (uint64_t)(gb < 0 ? -gb : gb);
+    const u128 sa = (u128)xa * xa, sb = (u128)xb * xb;
+    const uint32_t da = WLa * (W - WLa), db = WLb * (W - WLb);
+    const u128 la = (u128)(uint64_t)sa * db, lb = (u128)(uint64_t)sb * da;
+    const u128 ha = (u128)(uint64_t)(sa >> 64) * db + (la >> 64);
+    const u128 hb = (u128)(uint64_t)(sb >> 64) * da + (lb >> 64);
+    return ha != hb ? ha > hb : (uint64_t)la > (uint64_t)lb;
 }
 
 // Order of one feature's candidates: larger D, then the smaller threshold;

@@ -51,3 +51,22 @@ def test_weights_around_the_eight_bit_limit(K, col):
 @pytest.mark.parametrize("n", [65535, 65536])
 def test_weights_around_the_sixteen_bit_limit(n, K):
     same(K, n, 2, 3, 1, dict(col_level=1 if K in (4, 12) else 64), B.RANK_FP32, levels=60, p=3)
+
+
+@pytest.mark.parametrize("rank", [B.RANK_FP32, B.RANK_EXACT], ids=["fp64", "exact"])
+@pytest.mark.parametrize("rows", [2, 7, 16, 32, 64])
+@pytest.mark.parametrize("kind", ["ties", "wide"])
+def test_regression_nodes_of_the_wave_path(kind, rows, rank):
+    # target sums as FP64 integers in nodes of up to 64 rows: tied thresholds
+    # (few targets and bin values), targets over many binades, both rankings
+    rng = np.random.default_rng(640 + rows)
+    X = rng.integers(0, 12, (400, 9)).astype(np.float32)
+    y = np.round(X[:, 0] - X[:, 1] + rng.standard_normal(400))
+    if kind == "wide":
+        y = (y - 3) * np.exp(rng.uniform(-30, 0, 400))
+    kw = dict(max_iter=3, seed=9 + rows, n_bins=64)
+    print(f"regression wave path rows={rows} kind={kind} rank={rank}", flush=True)
+    g = B.boruta_fit_regression(X, y.astype(np.float32), 30, 12, trace=True, split_rank=rank,
+                                tune=dict(small_rows=rows), **kw)
+    o = O.boruta_fit_reg(X, y.astype(np.float32), 30, 12, trace=True, **kw)
+    assert_same_run(g, o)
