@@ -277,6 +277,7 @@ struct JobDev {
     int64_t* imp;          // [pw_cap] integer importance of the iteration
     uint32_t* wbuf;        // [T][n] bootstrap multiplicities
     uint32_t* rec[2];      // [T][rstride] row records, ping-pong by level parity
+    int64_t* wy[2];        // [T][rstride] regression: weight * y_fix of each record
     uint32_t* oob;         // [T][n] out-of-bag rows, ascending
     int32_t* tstat;        // [T][4] distinct in-bag, OOB rows, OOB correct, spare
     uint8_t* rowmaj;       // [n_pad][rm_stride] the widened bins row-major, rebuilt every
@@ -309,7 +310,7 @@ struct NodeDev {
 // level so that an item's first loads do not depend on each other.
 struct SlotRec {
     const uint32_t* recs;  // the node's row records (this level's parity)
-    const int64_t* yfix;   // regression job: its fixed-point targets (else null)
+    const int64_t* wy;     // regression job: the records' weighted targets (else null)
     uint32_t id;           // node index
     uint32_t len, n;       // row records, weighted rows
     uint32_t mtry;         // features drawn this iteration
@@ -406,6 +407,7 @@ struct ForestDev {
                           // class counts fit 8 bits)
     int32_t kmax, parity, split_rank;
     int32_t has_cls, has_reg;  // the plan holds classification / regression jobs
+    int32_t wide_reg;     // ... and regression nodes may weigh more than kRegF64Weight
     int32_t hist_words;   // LDS words per bin of an item's histogram: two classes to a word
                           // while no node weighs 65536 rows, else one per class plane
     int32_t item_words;   // words of an item record: 2 + hist_words

@@ -364,6 +364,7 @@ struct JobPlan {
     size_t X, y32, y8, orig, sha, colptr, colsrc, act, state, hits, hist, smax, hconf, hrej, G,
         imp, wbuf, rec0, rec1, oob, tstat;
     size_t yfix = 0, yrange = 0;  // regression: fixed-point targets, target minimum/maximum
+    size_t wy0 = 0, wy1 = 0;      // regression: the records' weighted targets
 };
 
 struct Plan {
@@ -435,6 +436,8 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         if (s.yr) {
             j.yfix = sh ? sh->yfix : r.take(n * 8);
             j.yrange = sh ? sh->yrange : r.take(8);
+            j.wy0 = r.take(T * n * 8);
+            j.wy1 = r.take(T * n * 8);
         }
         j.oob = r.take(T * n * 4);
         j.tstat = r.take(T * 16);
@@ -839,6 +842,8 @@ void Engine::setup(std::vector<int>& status) {
         J.wbuf = at<uint32_t>(jp.wbuf);
         J.rec[0] = at<uint32_t>(jp.rec0);
         J.rec[1] = at<uint32_t>(jp.rec1);
+        J.wy[0] = s.yr ? at<int64_t>(jp.wy0) : nullptr;
+        J.wy[1] = s.yr ? at<int64_t>(jp.wy1) : nullptr;
         J.oob = at<uint32_t>(jp.oob);
         J.tstat = at<int32_t>(jp.tstat);
         J.rowmaj = jp.rm_stride ? at<uint8_t>(jp.rowmaj) : nullptr;
@@ -947,6 +952,7 @@ ForestDev Engine::forest() const {
     F.split_rank = O.split_rank;
     F.has_cls = pl.has_cls ? 1 : 0;
     F.has_reg = pl.has_reg ? 1 : 0;
+    F.wide_reg = pl.has_reg && pl.max_n > 32768 ? 1 : 0;  // weights above kRegF64Weight
     F.hist_words = pl.hist_words;
     F.item_words = pl.hist_words + 2;
     F.small_ncap = 256u;  // the wave path packs class counters in 8-bit fields

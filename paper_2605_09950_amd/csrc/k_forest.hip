@@ -95,8 +95,12 @@ __global__ __launch_bounds__(1024) void k_boot_compact(ForestDev F0) {
         if (inb) {
             uint32_t left = wi;
             for (uint32_t k = 0; k < nr; ++k) {
-                recs[pin + wpre + k] = rec_pack(i, min(left, kRecWeight), yi);
-                left -= min(left, kRecWeight);
+                const uint32_t w = min(left, kRecWeight);
+                recs[pin + wpre + k] = rec_pack(i, w, yi);
+                if (reg)
+                    J.wy[0][(size_t)tr.tau * J.rstride + pin + wpre + k] =
+                        (int64_t)w * ldg(J.yfix + i);
+                left -= w;
             }
             atomicAdd(&s_cls[yi], wi);
         }
@@ -528,6 +532,7 @@ __device__ __forceinline__ void small_node_reg(const ForestDev& F, uint32_t id, 
     const int seg = lane / W, i = lane & (W - 1);
     const bool valid = i < len;
     const uint32_t rec = valid ? ldg(rin + i) : 0u;
+    const int64_t wy = valid ? ldg(J.wy[F.parity] + tbase + i) : 0;
     const uint32_t row = rec_row(rec), wt = rec_w(rec);
     const int64_t Ti = node_tsum(F.cls, F.kmax, id);
     const uint32_t Wi = nd.n;
@@ -542,8 +547,7 @@ __device__ __forceinline__ void small_node_reg(const ForestDev& F, uint32_t id, 
     }
     {
         const bool mine = seg == 0 && valid;
-        const int64_t yw = mine ? (int64_t)wt * ldg(J.yfix + row) : 0;
-        rows[lane] = double2{mine ? (double)wt : 0.0, (double)yw};
+        rows[lane] = double2{mine ? (double)wt : 0.0, mine ? (double)wy : 0.0};
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     bool has = false;
@@ -680,6 +684,7 @@ __device__ __forceinline__ void small_node_reg(const ForestDev& F, uint32_t id, 
         const uint32_t pos = left ? (uint32_t)__popcll(lm & below)
                                   : nl_rows + (uint32_t)__popcll(vm & ~lm & below);
         rout[pos] = rec;
+        J.wy[F.parity ^ 1][tbase + pos] = wy;
     }
     if (lane == 0)
         split_node_reg(F, J, tr, id, nd, best, nl_rows, reg_gain_fix(best, J.s_gain), out.child,
@@ -1313,87 +1318,134 @@ __device__ __forceinline__ Cand cand_of(const uint32_t* l, uint32_t fb, int b,
 // W[256] (32-bit) and the weighted fixed-point target sums T[256] (64-bit LDS
 // atomics, two's complement) over the node's rows, then the threshold scan.
 // Lane l owns bins 4l .. 4l+3; prefix sums over the lanes give each
-// threshold's left (W_L, T_L).  Thresholds are ranked by the FP64 score
+// threshold's left (W_L, T_L).  Thresholds are ranked by an FP64 score
 // g^2 / (W_L W_R) (g = T_L W_R - T_R W_L) and every threshold within the
-// ranking margin of the maximum is compared exactly (reg_better); with exact
+// ranking margin of the maximum is compared exactly (reg_cmp); with exact
 // ranking every valid threshold is.
-__device__ __forceinline__ long long wave_excl_sum64(long long x) {
-    long long incl = x;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const long long o = __shfl_up(incl, d);
-        if ((int)(threadIdx.x & 63) >= d) incl += o;
+// In nodes of weight up to 2^15 every target sum is below 2^53: the prefix
+// sums and scores stay in FP64 (reg_score); wider nodes (WIDE plans hold them)
+// keep 64-bit integers and take the score from the 128-bit gap.
+constexpr uint32_t kRegF64Weight = 1u << 15;
+
+template <class T>
+__device__ __forceinline__ T dpp_zero_shift(T v, int s) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
+    switch (s) {  // a constant where this is unrolled
+#define BORUTA_DPP(S, CTRL, ROWS)                                         \
+    case S:                                                               \
+        lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, ROWS, 0xf, false);  \
+        hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, ROWS, 0xf, false);  \
+        break;
+        BORUTA_DPP(0, 0x111, 0xf)
+        BORUTA_DPP(1, 0x112, 0xf)
+        BORUTA_DPP(2, 0x114, 0xf)
+        BORUTA_DPP(3, 0x118, 0xf)
+        BORUTA_DPP(4, 0x142, 0xa)
+        BORUTA_DPP(5, 0x143, 0xc)
+#undef BORUTA_DPP
     }
-    return incl - x;
+    return __builtin_bit_cast(T, (uint64_t)(uint32_t)lo | (uint64_t)(uint32_t)hi << 32);
+}
+template <class T>
+__device__ __forceinline__ T wave_incl_sum64(T v) {
+#pragma unroll
+    for (int s = 0; s < 6; ++s) v += dpp_zero_shift(v, s);
+    return v;
 }
 
+// V: the type of the target sums (double or int64_t).
+template <class V>
 __device__ __forceinline__ Cand reg_feature_best(const uint32_t* hw, const long long* ht, int B,
                                                  int q, int f, uint32_t W, int64_t T,
                                                  int split_rank) {
     const int lane = threadIdx.x & 63;
     const uint4 wv = reinterpret_cast<const uint4*>(hw)[lane];
+    const longlong2 ta = reinterpret_cast<const longlong2*>(ht)[2 * lane],
+                    tb = reinterpret_cast<const longlong2*>(ht)[2 * lane + 1];
     const uint32_t w4[4] = {wv.x, wv.y, wv.z, wv.w};
-    long long t4[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) t4[u] = ht[lane * 4 + u];
-    const uint32_t wsum = w4[0] + w4[1] + w4[2] + w4[3];
-    const long long tsum = t4[0] + t4[1] + t4[2] + t4[3];
-    uint32_t wl = wave_incl_sum(wsum) - wsum;
-    long long tl = wave_excl_sum64(tsum);
-    Cand c[4];
-    double qc[4];
-    double q1 = -1.0;
+    uint32_t wl[4];
+    V tl[4];
+    wl[0] = wv.x;
+    tl[0] = (V)ta.x;
+    wl[1] = wl[0] + wv.y;
+    tl[1] = tl[0] + (V)ta.y;
+    wl[2] = wl[1] + wv.z;
+    tl[2] = tl[1] + (V)tb.x;
+    wl[3] = wl[2] + wv.w;
+    tl[3] = tl[2] + (V)tb.y;
+    const uint32_t wex = wave_incl_sum(wl[3]) - wl[3];
+    const V tex = wave_incl_sum64(tl[3]) - tl[3];
+    Cand c;
+    c.q = q;
+    c.f = f;
+    c.pad = 0;
+    double qs[4], q1 = -1.0;
+    bool ok[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        wl += w4[u];
-        tl += t4[u];
-        const int b = lane * 4 + u;
-        c[u].q = q;
-        c[u].f = f;
-        c[u].b = b;
-        c[u].pad = 0;
-        const bool ok = b <= B - 2 && w4[u] != 0 && wl != 0 && wl != W;
-        c[u].nl = ok ? wl : 0u;
-        c[u].nr = W - wl;
-        c[u].sl = (uint64_t)tl;
-        c[u].sr = (uint64_t)(T - (int64_t)tl);
-        qc[u] = ok ? reg_q64(c[u]) : -1.0;
-        q1 = qc[u] > q1 ? qc[u] : q1;
+        wl[u] += wex;
+        tl[u] += tex;
+        ok[u] = lane * 4 + u <= B - 2 && w4[u] != 0 && wl[u] != W;
+        double s;
+        if constexpr (std::is_same<V, double>::value) {
+            s = reg_score(tl[u], (double)wl[u], (double)T, (double)W);
+        } else {
+            c.nl = ok[u] ? wl[u] : 1u;
+            c.nr = W - c.nl;
+            c.sl = (uint64_t)tl[u];
+            c.sr = (uint64_t)(T - tl[u]);
+            s = reg_q64(c);
+        }
+        qs[u] = ok[u] ? s : -1.0;
+        q1 = fmax(q1, qs[u]);
     }
-    double qmax = q1;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const double o = __shfl_xor(qmax, m);
-        qmax = o > qmax ? o : qmax;
-    }
-    Cand lb;
-    lb.nl = 0;
-    lb.b = 0x7FFFFFFF;
-    lb.q = q;
-    lb.f = f;
-    lb.nr = 0;
-    lb.pad = 0;
-    lb.sl = lb.sr = 0;
-    if (qmax < 0.0) return lb;
+    const double qmax = wave_max_f64_dpp(q1);
+    c.nl = 0;
+    c.nr = 0;
+    c.b = 0x7FFFFFFF;
+    c.sl = c.sr = 0;
+    if (qmax < 0.0) return c;
     const double floor64 = split_rank ? fp64_floor(qmax) : 0.0;
-    // the lane's finalists in ascending threshold order: a strictly better
-    // one replaces, so ties keep the smaller threshold
+    uint32_t fin = 0;  // the lane's finalists
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (c[u].nl != 0 && qc[u] >= floor64 && (lb.nl == 0 || reg_better(c[u], lb))) lb = c[u];
-    const unsigned long long finm = __ballot(lb.nl != 0);
-    if (__popcll(finm) == 1) return shfl_cand(lb, (int)__ffsll(finm) - 1);
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const Cand o = shfl_xor_cand(lb, m);
-        if (reg_wins_same_feature(o, lb)) lb = o;
+    for (int u = 0; u < 4; ++u) fin |= (uint32_t)(ok[u] && qs[u] >= floor64) << u;
+    // candidate of the lane's threshold u
+    auto cand = [&](int u, Cand& o) {
+        const V t = u == 0 ? tl[0] : (u == 1 ? tl[1] : (u == 2 ? tl[2] : tl[3]));
+        const uint32_t w = u == 0 ? wl[0] : (u == 1 ? wl[1] : (u == 2 ? wl[2] : wl[3]));
+        o.b = lane * 4 + u;
+        o.nl = w;
+        o.nr = W - w;
+        o.sl = (uint64_t)(int64_t)t;
+        o.sr = (uint64_t)(T - (int64_t)t);
+    };
+    const unsigned long long fm = __ballot(fin != 0);
+    Cand best = c;
+    if (fin) {  // in ascending threshold order: a strictly better one replaces
+        cand(__builtin_ctz(fin), best);
+#pragma unroll 1
+        for (uint32_t m = fin & (fin - 1u); m; m &= m - 1u) {
+            Cand o = c;
+            cand(__builtin_ctz(m), o);
+            if (reg_cmp(o, best) > 0) best = o;
+        }
     }
-    return lb;
+    if (__popcll(fm) == 1) return shfl_cand(best, (int)__ffsll(fm) - 1);
+#pragma unroll 1
+    for (int m = 1; m < 64; m <<= 1) {
+        const Cand o = shfl_xor_cand(best, m);
+        if (o.nl == 0) continue;
+        const int s = best.nl == 0 ? 1 : reg_cmp(o, best);
+        if (s > 0 || (s == 0 && o.b < best.b)) best = o;
+    }
+    return best;
 }
 
 // One regression item: draws q0 .. q0 + nf - 1 of the node, one after the
-// other in the wave's LDS region (256 words of W, then 256 64-bit sums).
-template <int RB>
+// other in the wave's LDS region (256 words of W, then 256 64-bit sums).  The
+// rows' weighted targets stream beside their records.
+template <int RB, bool WIDE>
 __device__ __forceinline__ Cand reg_item(const ForestDev& F, const SlotRec& sr, int q0, int nf,
                                          const int* fq, const uint8_t* const* col,
                                          uint32_t* hist) {
@@ -1402,38 +1454,49 @@ __device__ __forceinline__ Cand reg_item(const ForestDev& F, const SlotRec& sr, 
     long long* ht = reinterpret_cast<long long*>(hist + 256);
     const int64_t T = (int64_t)((uint64_t)sr.cnode[0] | ((uint64_t)sr.cnode[1] << 32));
     const uint32_t W = sr.n, len = sr.len;
-    const int64_t* yfix = sr.yfix;
+    const int64_t* wy = sr.wy;
     const uint32_t* recs = sr.recs;
     Cand best;
     best.nl = 0;
     for (int v = 0; v < nf; ++v) {
         reinterpret_cast<uint4*>(hw)[lane] = make_uint4(0u, 0u, 0u, 0u);
-        reinterpret_cast<uint4*>(ht)[2 * lane] = make_uint4(0u, 0u, 0u, 0u);
-        reinterpret_cast<uint4*>(ht)[2 * lane + 1] = make_uint4(0u, 0u, 0u, 0u);
+        reinterpret_cast<uint4*>(ht)[lane] = make_uint4(0u, 0u, 0u, 0u);
+        reinterpret_cast<uint4*>(ht)[64 + lane] = make_uint4(0u, 0u, 0u, 0u);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        for (uint32_t i0 = 0; i0 < len; i0 += 64 * RB) {
-            uint32_t r[RB];
+        auto batch = [&](uint32_t i0, auto nb) {
+            constexpr int NB = decltype(nb)::value;
+            uint32_t r[NB];
+            int64_t t[NB];
 #pragma unroll
-            for (int u = 0; u < RB; ++u) r[u] = rec_raw(recs, i0 + u * 64 + lane, len);
-            uint32_t b[RB];
-            long long yv[RB];
-#pragma unroll
-            for (int u = 0; u < RB; ++u) {
-                b[u] = ldg(col[v] + rec_row(r[u]));
-                yv[u] = ldg(yfix + rec_row(r[u]));
+            for (int u = 0; u < NB; ++u) {
+                const uint32_t i = min(i0 + u * 64 + lane, len - 1u);
+                r[u] = rec_raw(recs, i, len);
+                t[u] = ldg(reinterpret_cast<const int64_t*>(
+                    reinterpret_cast<const char*>(wy) + i * 8u));
             }
+            uint32_t b[NB];
 #pragma unroll
-            for (int u = 0; u < RB; ++u) {
-                const uint32_t w = rec_w(r[u]);
+            for (int u = 0; u < NB; ++u) b[u] = ldg(col[v] + rec_row(r[u]));
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
                 if (i0 + u * 64 + lane < len) {
-                    atomicAdd(&hw[b[u]], w);
+                    atomicAdd(&hw[b[u]], rec_w(r[u]));
                     atomicAdd(reinterpret_cast<unsigned long long*>(&ht[b[u]]),
-                              (unsigned long long)((long long)w * yv[u]));
+                              (unsigned long long)t[u]);
                 }
             }
-        }
+        };
+        if (len <= 128u)
+            batch(0u, std::integral_constant<int, 2>{});
+        else
+            for (uint32_t i0 = 0; i0 < len; i0 += 64 * RB)
+                batch(i0, std::integral_constant<int, RB>{});
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        const Cand fb = reg_feature_best(hw, ht, (int)sr.B, q0 + v, fq[v], W, T, F.split_rank);
+        Cand fb;
+        if (WIDE && W > kRegF64Weight)
+            fb = reg_feature_best<int64_t>(hw, ht, (int)sr.B, q0 + v, fq[v], W, T, F.split_rank);
+        else
+            fb = reg_feature_best<double>(hw, ht, (int)sr.B, q0 + v, fq[v], W, T, F.split_rank);
         // draws in order: a strictly better score replaces
         if (fb.nl != 0 && (best.nl == 0 || reg_better(fb, best))) best = fb;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the next draw rewrites
@@ -1502,7 +1565,7 @@ __global__ __launch_bounds__(256) void k_draws(ForestDev F, int level) {
         }
         if (ql == 0) {
             sr->recs = J.rec[F.parity] + (size_t)tr.tau * J.rstride + nd.seg;
-            sr->yfix = J.reg ? J.yfix : nullptr;
+            sr->wy = J.reg ? J.wy[F.parity] + (size_t)tr.tau * J.rstride + nd.seg : nullptr;
             sr->id = id;
             sr->len = nd.len;
             sr->n = nd.n;
@@ -1560,7 +1623,7 @@ struct ItemWalk {
 // classification nodes are left to k_hist_tile, which in turn skips these:
 // the regression item's registers and code stay out of the classification
 // kernel.
-template <int RB>
+template <int RB, bool WIDE>
 __global__ __launch_bounds__(256) void k_hist_reg(ForestDev F, int level, uint32_t first,
                                                   uint32_t count) {
     extern __shared__ uint4 lds_raw[];
@@ -1588,7 +1651,7 @@ __global__ __launch_bounds__(256) void k_hist_reg(ForestDev F, int level, uint32
             fq[u] = (int)drawn[u < nf ? u : 0];
             col[u] = dcol[u < nf ? u : 0];
         }
-        const Cand best = reg_item<RB>(F, sr, q0, nf, fq, col, hist);
+        const Cand best = reg_item<RB, WIDE>(F, sr, q0, nf, fq, col, hist);
         if (lane == 0) F.cand[item] = best;
         alg += (unsigned long long)sr.len * (unsigned long long)(nf + (j == 0 ? 6 : 0));
     }
@@ -1971,70 +2034,57 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level, uint3
 // (bin <= b) from the front in row order, right rows from the back in reverse
 // row order (no result depends on a node's row order, and each child segment
 // stays monotone in row index for the next level's gathers); returns the
-// left rows.  len = 0 when neither child is searched again.  AHEAD: the next
-// block's records are loaded while a block is placed (classification nodes;
-// the regression finalize, at more registers, measured slower with it).
-template <bool AHEAD>
-__device__ uint32_t partition_rows(const ForestDev& F, const JobDev& J, const TreeDev& tr,
-                                   const NodeDev& nd, const SlotRec& sr, const Cand& best,
-                                   uint32_t len) {
-    const int lane = threadIdx.x & 63;
-    const uint8_t* col = ldg(J.colptr + best.f);
+// left rows.  len = 0 when neither child is searched again.  Lanes take
+// consecutive records (coalesced reads, and writes that a ballot packs), 64 at
+// a time, up to 8 such groups in flight; REG: the weighted targets move along.
+template <bool REG>
+__device__ __forceinline__ uint32_t partition_rows(const ForestDev& F, const JobDev& J,
+                                                   const TreeDev& tr, const NodeDev& nd,
+                                                   const SlotRec& sr, const Cand& best,
+                                                   const uint8_t* col, uint32_t len) {
+    const uint32_t lane = threadIdx.x & 63u;
     const uint32_t* recs = sr.recs;
-    uint32_t* rout = J.rec[F.parity ^ 1] + (size_t)tr.tau * J.rstride + nd.seg;
-    constexpr int kR = 8;  // rows per lane per block: lane l owns rows [l kR, l kR + kR)
+    const size_t seg = (size_t)tr.tau * J.rstride + nd.seg;
+    uint32_t* rout = J.rec[F.parity ^ 1] + seg;
+    const int64_t* wy = REG ? sr.wy : nullptr;
+    int64_t* wout = REG ? J.wy[F.parity ^ 1] + seg : nullptr;
     uint32_t runl = 0, runr = 0;
-    uint32_t rn[kR];  // with AHEAD: the next block's records, loaded one block ahead
-    if constexpr (AHEAD) {
+    auto block = [&](uint32_t blk, auto nb) {
+        constexpr int NB = decltype(nb)::value;
+        uint32_t r[NB];
+        int64_t t[REG ? NB : 1];
 #pragma unroll
-        for (int u = 0; u < kR; ++u) {
-            const uint32_t i = (uint32_t)lane * kR + u;
-            rn[u] = i < len ? ldg(recs + i) : 0u;
+        for (int u = 0; u < NB; ++u) r[u] = rec_raw(recs, blk + u * 64 + lane, len);
+        if constexpr (REG) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                t[u] = ldg(reinterpret_cast<const int64_t*>(
+                    reinterpret_cast<const char*>(wy) + min(blk + u * 64 + lane, len - 1u) * 8u));
         }
-    }
-    for (uint32_t blk = 0; blk < len; blk += 64 * kR) {
-        const uint32_t i0 = blk + (uint32_t)lane * kR;
-        uint32_t r[kR];
+        int bb[NB];
 #pragma unroll
-        for (int u = 0; u < kR; ++u) {
-            if constexpr (AHEAD)
-                r[u] = rn[u];
-            else
-                r[u] = i0 + u < len ? ldg(recs + i0 + u) : 0u;
+        for (int u = 0; u < NB; ++u) bb[u] = (int)ldg(col + rec_row(r[u]));
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const bool in = blk + u * 64 + lane < len, left = in && bb[u] <= best.b;
+            const uint64_t lm = __ballot(left), rm = __ballot(in && !left);
+            const uint64_t m = left ? lm : rm;
+            const uint32_t before = __builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            const uint32_t at = left ? runl + before : len - 1u - runr - before;
+            if (in) {
+                rout[at] = r[u];
+                if constexpr (REG) wout[at] = t[u];
+            }
+            runl += (uint32_t)__popcll(lm);
+            runr += (uint32_t)__popcll(rm);
         }
-        int bb[kR];
-#pragma unroll
-        for (int u = 0; u < kR; ++u) bb[u] = i0 + u < len ? (int)ldg(col + rec_row(r[u])) : 0x7FFF;
-        if constexpr (AHEAD) {
-            // the next block's records are in flight while this block is placed
-            const uint32_t j0 = i0 + 64 * kR;
-#pragma unroll
-            for (int u = 0; u < kR; ++u) rn[u] = j0 + u < len ? ldg(recs + j0 + u) : 0u;
-        }
-        uint32_t nlm = 0, nrm = 0;
-#pragma unroll
-        for (int u = 0; u < kR; ++u) {
-            nlm += bb[u] <= best.b;
-            nrm += i0 + u < len && bb[u] > best.b;
-        }
-        // exclusive prefix of (left, right) over the lanes, both packed in one
-        // word (a block holds 512 rows)
-        const uint32_t mine = nlm | (nrm << 16);
-        const uint32_t incl = wave_incl_sum(mine);
-        const uint32_t pre = incl - mine;
-        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        uint32_t lrow = runl + (pre & 0xFFFFu), rrow = runr + (pre >> 16);
-#pragma unroll
-        for (int u = 0; u < kR; ++u) {
-            if (i0 + u >= len) break;
-            if (bb[u] <= best.b)
-                rout[lrow++] = r[u];
-            else
-                rout[len - 1 - rrow++] = r[u];
-        }
-        runl += tot & 0xFFFFu;
-        runr += tot >> 16;
-    }
+    };
+    if (len != 0 && len <= 128u)
+        block(0u, std::integral_constant<int, 2>{});
+    else
+        for (uint32_t blk = 0; blk < len; blk += 512u)
+            block(blk, std::integral_constant<int, 8>{});
     return runl;
 }
 
@@ -2082,7 +2132,7 @@ __device__ void finalize_reg(const ForestDev& F, JobDev& J, const TreeDev& tr, u
         return;
     }
     const bool part = (int)nd.depth + 1 < J.D;
-    const uint32_t runl = partition_rows<false>(F, J, tr, nd, sr, best, part ? sr.len : 0u);
+    const uint32_t runl = partition_rows<true>(F, J, tr, nd, sr, best, ldg(J.colptr + best.f), part ? sr.len : 0u);
     if (lane == 0) {
         int kinds[2];
         split_node_reg(F, J, tr, sr.id, nd, best, runl, reg_gain_fix(best, J.s_gain), child,
@@ -2215,7 +2265,7 @@ __global__ __launch_bounds__(256) void k_split_finalize(ForestDev F0, int level,
         // the maximum depth with two or more classes (which implies two or
         // more distinct rows); other children are final leaves.
         const bool part = (int)nd.depth + 1 < J.D && (nzl >= 2 || nzr >= 2);
-        const uint32_t runl = partition_rows<true>(F, J, tr, nd, sr, best, part ? sr.len : 0u);
+        const uint32_t runl = partition_rows<false>(F, J, tr, nd, sr, best, ldg(J.colptr + best.f), part ? sr.len : 0u);
         if (lane == 0) {
             int kinds[2];
             split_node(F, J, tr, id, nd, best, runl, cl, cr, cand_gain_fix(best, S, N), child,
@@ -2397,11 +2447,19 @@ void launch_hist_tile(const ForestDev& F, int level, uint32_t first, uint32_t co
     const dim3 grid(grid_wg);
     if (F.has_reg) {
         const size_t rl = std::max(lds, (size_t)4 * 768 * sizeof(uint32_t));
+#define BORUTA_REG(RB)                                                                          \
+    if (F.wide_reg)                                                                             \
+        hipLaunchKernelGGL((k_hist_reg<RB, true>), grid, dim3(256), rl, st, F, level, first,    \
+                           count);                                                              \
+    else                                                                                        \
+        hipLaunchKernelGGL((k_hist_reg<RB, false>), grid, dim3(256), rl, st, F, level, first,   \
+                           count);
         switch (rb) {
-            case 4: hipLaunchKernelGGL((k_hist_reg<4>), grid, dim3(256), rl, st, F, level, first, count); break;
-            case 16: hipLaunchKernelGGL((k_hist_reg<16>), grid, dim3(256), rl, st, F, level, first, count); break;
-            default: hipLaunchKernelGGL((k_hist_reg<8>), grid, dim3(256), rl, st, F, level, first, count); break;
+            case 4: BORUTA_REG(4) break;
+            case 16: BORUTA_REG(16) break;
+            default: BORUTA_REG(8) break;
         }
+#undef BORUTA_REG
     }
     if (!F.has_cls) return;
     switch (F.kmax * 8 + F.fw) {

@@ -111,14 +111,15 @@ __device__ __forceinline__ u128 reg_gap(const Cand& c) {
     return (u128)(g < 0 ? -g : g);
 }
 
-// D_a > D_b exactly for candidates of one node: g_a^2 W_Lb W_Rb > g_b^2 W_La W_Ra
-// (products below 2^221).
-__device__ inline bool reg_better(const Cand& a, const Cand& b) {
+// Sign of D_a - D_b exactly for candidates of one node: g_a^2 W_Lb W_Rb against
+// g_b^2 W_La W_Ra (products below 2^221).
+__device__ __forceinline__ int reg_cmp(const Cand& a, const Cand& b) {
     const u128 ga = reg_gap(a), gb = reg_gap(b);
     const U256 lhs = mul256_64(mul128_full(ga, ga), (uint64_t)b.nl * b.nr);
     const U256 rhs = mul256_64(mul128_full(gb, gb), (uint64_t)a.nl * a.nr);
-    return cmp256(lhs, rhs) > 0;
+    return cmp256(lhs, rhs);
 }
+__device__ inline bool reg_better(const Cand& a, const Cand& b) { return reg_cmp(a, b) > 0; }
 
 // FP64 ranking score g^2 / (W_L W_R): relative error at most 5 units of
 // 2^-53 (two roundings converting g, one squaring, one division; W_L W_R <
@@ -243,16 +244,6 @@ __device__ __forceinline__ bool reg_small_better(int64_t TLa, uint32_t WLa, int6
     const u128 ha = (u128)(uint64_t)(sa >> 64) * db + (la >> 64);
     const u128 hb = (u128)(uint64_t)(sb >> 64) * da + (lb >> 64);
     return ha != hb ? ha > hb : (uint64_t)la > (uint64_t)lb;
-}
-
-// Order of one feature's candidates: larger D, then the smaller threshold;
-// invalid ones (nl == 0) last.
-__device__ __forceinline__ bool reg_wins_same_feature(const Cand& a, const Cand& b) {
-    if (b.nl == 0) return a.nl != 0 || a.b < b.b;
-    if (a.nl == 0) return false;
-    if (reg_better(a, b)) return true;
-    if (reg_better(b, a)) return false;
-    return a.b < b.b;
 }
 
 // Total order over a node's candidates: larger D, then the earlier draw
