@@ -24,6 +24,8 @@
 //   * Algorithm 1's final ranking: confirmed 1, undecided 2, rejected from 3
 //     by descending historical importance (the mean of the feature's finite
 //     history entries, summed in iteration order; equal means share a rank).
+#include <cstddef>
+
 #include "dev_common.hpp"
 #include "reg_dev.hpp"
 
@@ -64,14 +66,6 @@ __global__ __launch_bounds__(256) void k_treeimp(JobDev* jobs, const TreeDev* tr
               (unsigned long long)udiv128((u128)gv << 44, (u128)tot[g]));
 }
 
-// Permut: one thread per (tree, OOB row).  When the job's widened width is
-// at most lds_cols, the drops are summed per column in LDS and each
-// workgroup adds its nonzero sums to the importances: once most columns are
-// decided, few remain and per-row atomics would all meet on them (with many
-// columns the per-row atomics are spread out and cheaper than a flush per
-// workgroup).  For a regression job a row's score is the negated squared
-// error against its leaf's prediction, sq_error_fix below, and the
-// per-column sums in LDS are 64-bit.
 // Prediction of a regression leaf: floor(T / W), T in the node's first two
 // class words and W its weighted count.
 __device__ __forceinline__ long long leaf_pred(const NodeDev* nodes, const uint32_t* cls, int kmax,
@@ -90,15 +84,101 @@ __device__ __forceinline__ long long sq_error_fix(const NodeDev* nodes, const ui
     return (long long)((a * a) >> s_perm);
 }
 
+// What a walk needs of a node: one 16-byte load.
+struct Hop {
+    int32_t feat;       // widened column, negative for a leaf
+    uint32_t left;      // left child; the right one is left + 1
+    uint32_t thr, leaf; // threshold bin, leaf class
+};
+__device__ __forceinline__ Hop load_hop(const NodeDev* nodes, uint32_t node) {
+    static_assert(sizeof(NodeDev) == 32 && offsetof(NodeDev, n) == 16, "node record layout");
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = ldg(reinterpret_cast<const u32x4*>(nodes + node) + 1);
+    return Hop{(int32_t)v[1], v[2], v[3] & 0xFFFFu, v[3] >> 16 & 0xFFu};
+}
+
+// A thread's walk from a root, kept in LDS by position (stride 256): column
+// and direction, the child not taken, the threshold bin.  A permuted column
+// changes the row's prediction only where its new bin turns the other way at
+// one of its positions, and then from the child not taken on: positions that
+// keep the direction need no walk, and a turned one none of the nodes above.
+struct PathLds {
+    uint32_t* pf;  // [depth][256] column | went left << 31
+    uint32_t* ps;  // [depth][256] the child not taken
+    uint8_t* pt;   // [depth][256] threshold bin
+};
+__host__ __device__ constexpr uint32_t path_lds_words(int max_depth) {
+    return (uint32_t)max_depth * 256u * 2u + (uint32_t)max_depth * 64u;
+}
+__device__ __forceinline__ PathLds path_lds(uint32_t* s, int max_depth) {
+    return PathLds{s, s + max_depth * 256, reinterpret_cast<uint8_t*>(s + max_depth * 512)};
+}
+struct Walked {
+    uint32_t leaf, leaf_class;
+    int len;
+    uint32_t dup;  // positions whose column is on the path before (depth <= 30)
+};
+__device__ __forceinline__ Walked walk_path(const JobDev& J, const NodeDev* nodes, uint32_t node,
+                                            uint32_t row, const PathLds& P, int tid) {
+    Walked w{node, 0u, 0, 0u};
+    Hop h = load_hop(nodes, node);
+    while (h.feat >= 0) {
+        const bool left = (uint32_t)ldg(ldg(J.colptr + h.feat) + row) <= h.thr;
+        bool dup = false;
+        for (int q = 0; q < w.len; ++q)
+            dup |= (P.pf[q * 256 + tid] & 0x7FFFFFFFu) == (uint32_t)h.feat;
+        w.dup |= (uint32_t)dup << w.len;
+        P.pf[w.len * 256 + tid] = (uint32_t)h.feat | (uint32_t)left << 31;
+        P.ps[w.len * 256 + tid] = left ? h.left + 1u : h.left;
+        P.pt[w.len * 256 + tid] = (uint8_t)h.thr;
+        ++w.len;
+        w.leaf = left ? h.left : h.left + 1u;
+        h = load_hop(nodes, w.leaf);
+    }
+    w.leaf_class = h.leaf;
+    return w;
+}
+// The child from which the row's walk differs when the column first met at
+// position a takes bin sb; 0xFFFFFFFF when it does not (roots are never a child).
+__device__ __forceinline__ uint32_t turned_at(const PathLds& P, const Walked& w, int a,
+                                              uint32_t sb, int tid) {
+    const uint32_t e = P.pf[a * 256 + tid], f = e & 0x7FFFFFFFu;
+    if ((sb <= P.pt[a * 256 + tid]) != (bool)(e >> 31)) return P.ps[a * 256 + tid];
+    // later positions of the same column
+    for (uint32_t m = a < 31 ? w.dup >> (a + 1) << (a + 1) : 0u; m; m &= m - 1u) {
+        const int q = __builtin_ctz(m);
+        const uint32_t g = P.pf[q * 256 + tid];
+        if ((g & 0x7FFFFFFFu) == f && (sb <= P.pt[q * 256 + tid]) != (bool)(g >> 31))
+            return P.ps[q * 256 + tid];
+    }
+    return 0xFFFFFFFFu;
+}
+
 // (path column, replica) pairs whose OOB sources are walked together
 constexpr int kPermGroup = 8;
 
+// Permut: one thread per (tree, OOB row).  The row's (path column, replica)
+// pairs are taken kPermGroup at a time: their source rows pi(j) by cycle walks
+// interleaved in one loop, then all their source bins, then -- for the pairs
+// that turn at a node -- the walks from there, again interleaved in one loop
+// (a lane starts its next pair's walk as soon as one ends, so the wave waits
+// for the lane with the longest total, not for the longest walk of every
+// pair).  When the job's widened width is at most lds_cols, the drops are
+// summed per column in LDS and each workgroup adds its nonzero sums to the
+// importances: once most columns are decided, few remain and per-row atomics
+// would all meet on them.  For a regression job a row's score is the negated
+// squared error against its leaf's prediction, sq_error_fix above, and the
+// per-column sums in LDS are 64-bit.
+// Bound: the scattered bin loads (a 128-byte line each where the matrix exceeds
+// the last-level cache).  Re-routing every pair from its column's node down
+// took 117 ms an iteration at n = 100,000, 2,000 features, 300 trees of depth
+// 16, five replicas: 6.0e9 lines, 6.5 TB/s.
 __global__ __launch_bounds__(256) void k_permut(JobDev* jobs, const TreeDev* trees,
                                                 const NodeDev* nodes, const uint32_t* cls,
                                                 int kmax, int max_depth, int lds_cols,
                                                 int lds_words, unsigned long long* visits) {
-    // [2][max_depth][256]: node, feature; [lds_words]: the column drops
-    // (lds_cols of them); [kPermGroup][256]: a group's source rows
+    // the paths; [lds_words]: the column drops (lds_cols of them);
+    // [kPermGroup][256]: a group's source rows, then its walks' first nodes
     extern __shared__ uint32_t s_path[];
     const uint32_t g = blockIdx.y;
     const TreeDev tr = trees[g];
@@ -108,8 +188,10 @@ __global__ __launch_bounds__(256) void k_permut(JobDev* jobs, const TreeDev* tre
     const uint32_t m = (uint32_t)J.tstat[tr.tau * 4 + 1];
     const uint32_t j = blockIdx.x * 256u + tid;
     if (blockIdx.x * 256u >= m) return;
-    int* s_drop = reinterpret_cast<int*>(s_path + 2 * max_depth * 256);
+    const PathLds P = path_lds(s_path, max_depth);
+    int* s_drop = reinterpret_cast<int*>(s_path + path_lds_words(max_depth));
     long long* s_drop64 = reinterpret_cast<long long*>(s_drop);  // regression jobs
+    uint32_t* g_src = s_path + path_lds_words(max_depth) + lds_words;  // [kPermGroup][256]
     const bool reg = J.reg != 0;
     const bool lds = J.p_w <= lds_cols;  // uniform: one tree per workgroup
     if (lds) {
@@ -126,110 +208,128 @@ __global__ __launch_bounds__(256) void k_permut(JobDev* jobs, const TreeDev* tre
     const uint32_t row = active ? oob[j] : 0u;
     const uint32_t yv = reg ? 0u : (uint32_t)J.y[row];
     const long long yfv = reg ? (long long)J.yfix[row] : 0ll;
-    uint32_t* pn = s_path;
-    uint32_t* pf = s_path + max_depth * 256;
-    int len = 0;
-    uint32_t node = g;
+    Walked w{g, 0u, 0, 0u};
     bool base_ok = false;
     long long base_err = 0;
     unsigned long long nv = 0;  // node visits (statistics)
     if (active) {
-        NodeDev nd = nodes[node];
-        while (nd.feat >= 0) {
-            pn[len * 256 + tid] = node;
-            pf[len * 256 + tid] = (uint32_t)nd.feat;
-            ++len;
-            node = (int)J.colptr[nd.feat][row] <= (int)nd.thr ? nd.left : nd.left + 1;
-            nd = nodes[node];
-        }
-        nv += (unsigned long long)len + 1u;
+        w = walk_path(J, nodes, g, row, P, tid);
+        nv += (unsigned long long)w.len + 1u;
         if (reg)
-            base_err = sq_error_fix(nodes, cls, kmax, node, yfv, J.s_perm);
+            base_err = sq_error_fix(nodes, cls, kmax, w.leaf, yfv, J.s_perm);
         else
-            base_ok = nd.leaf_class == yv;
+            base_ok = w.leaf_class == yv;
     }
     const unsigned long long okm = __ballot(active && base_ok);
     if ((tid & 63) == 0 && okm) atomicAdd(&J.tstat[tr.tau * 4 + 2], (int)__popcll(okm));
-    // The row's (path column, replica) pairs in order -- path positions in
-    // order, a column already on the path skipped, replicas 0..R-1 -- taken
-    // kPermGroup at a time.  First the group's source rows, pi(j) of each
-    // pair's keyed OOB permutation, by walks interleaved in one loop (a lane
-    // starts its next pair's walk as soon as one ends, so the wave waits for
-    // the lane with the longest total rather than for the longest walk of
-    // every pair), kept in LDS; then each pair's re-routing.
-    uint32_t* g_src = s_path + 2 * max_depth * 256 + lds_words;  // [kPermGroup][256]
     const int R = J.R;
-    // next pair at or after (pi, r): a column already on the path is skipped
+    // next pair after (pi, r), in order of positions (a column already on the
+    // path skipped) and replicas
     auto next_pair = [&](int& pi, int& r) {
         if (++r < R) return;
         r = 0;
-        for (++pi; pi < len; ++pi) {
-            const uint32_t f = pf[pi * 256 + tid];
-            bool dup = false;
-            for (int pj = 0; pj < pi; ++pj) dup |= pf[pj * 256 + tid] == f;
-            if (!dup) return;
-        }
+        ++pi;
+        while (pi < w.len && (w.dup >> pi & 1u)) ++pi;
     };
     auto pair_perm = [&](int pi, int r) {
         return make_perm(J.seed_lo, J.seed_hi, kOobPerm, (uint32_t)J.t, (uint32_t)tr.tau,
-                         pf[pi * 256 + tid], (uint32_t)r << 16, (uint64_t)m);
+                         P.pf[pi * 256 + tid] & 0x7FFFFFFFu, (uint32_t)r << 16, (uint64_t)m);
+    };
+    auto add_drop = [&](uint32_t f, int drop, long long drop_sq) {
+        if (reg) {
+            if (drop_sq) {
+                if (lds)
+                    atomicAdd((unsigned long long*)&s_drop64[f], (unsigned long long)drop_sq);
+                else
+                    atomicAdd((unsigned long long*)&J.imp[f], (unsigned long long)drop_sq);
+            }
+        } else if (drop) {
+            if (lds)
+                atomicAdd(&s_drop[f], drop);
+            else
+                atomicAdd((unsigned long long*)&J.imp[f], (unsigned long long)(int64_t)drop);
+        }
     };
     int cpi = 0, cr = 0;  // the next pair to score (position 0 is never a duplicate)
-    while (active && cpi < len) {
-        // walks of the group's pairs
-        int wpi = cpi, wr = cr, k = 0;
-        KeyedPerm P = pair_perm(wpi, wr);
-        uint32_t x = j;
-        while (k < kPermGroup && wpi < len) {
-            if (m > 1u) x = perm_pass(P, x);
-            if (m <= 1u || x < m) {
-                g_src[k * 256 + tid] = m <= 1u ? 0u : x;
-                ++k;
-                next_pair(wpi, wr);
-                x = j;
-                if (wpi < len) P = pair_perm(wpi, wr);
+    while (active && cpi < w.len) {
+        // source rows of the group's pairs; their positions in bytes of pos
+        uint64_t pos = 0;
+        int k = 0;
+        {
+            KeyedPerm K = pair_perm(cpi, cr);
+            uint32_t x = j;
+            while (k < kPermGroup && cpi < w.len) {
+                if (m > 1u) x = perm_pass(K, x);
+                if (m <= 1u || x < m) {
+                    g_src[k * 256 + tid] = m <= 1u ? 0u : x;
+                    pos |= (uint64_t)cpi << (8 * k);
+                    ++k;
+                    next_pair(cpi, cr);
+                    x = j;
+                    if (cpi < w.len) K = pair_perm(cpi, cr);
+                }
             }
         }
-        // re-routing of the group's pairs; a column's drops are added when
-        // its pairs end or the group does
+        // source bins: the rows' loads, then the bins' loads, all in flight
+        uint32_t srow[kPermGroup];
+        uint64_t sbs = 0;
+#pragma unroll
+        for (int e = 0; e < kPermGroup; ++e)
+            srow[e] = ldg(oob + (e < k ? g_src[e * 256 + tid] : 0u));
+        uint32_t sb[kPermGroup];
+#pragma unroll
+        for (int e = 0; e < kPermGroup; ++e) {
+            const uint32_t f = P.pf[(int)(pos >> (8 * e) & 0xFFu) * 256 + tid] & 0x7FFFFFFFu;
+            sb[e] = ldg(ldg(J.colptr + f) + srow[e]);
+        }
+        // the pairs that turn, and where their walks go on
+        uint32_t turn = 0;
+#pragma unroll
+        for (int e = 0; e < kPermGroup; ++e) {
+            sbs |= (uint64_t)sb[e] << (8 * e);
+            if (e < k) {
+                const uint32_t at = turned_at(P, w, (int)(pos >> (8 * e) & 0xFFu), sb[e], tid);
+                g_src[e * 256 + tid] = at;
+                turn |= (uint32_t)(at != 0xFFFFFFFFu) << e;
+            }
+        }
+        // their walks; a column's drops are added when the column changes
+        uint32_t f = 0xFFFFFFFFu, node = 0, sbin = 0;
         int drop = 0;
         long long drop_sq = 0;  // regression: increase of the squared error
-        for (int g = 0; g < k; ++g) {
-            const uint32_t f = pf[cpi * 256 + tid];
-            const int sb = J.colptr[f][oob[g_src[g * 256 + tid]]];
-            uint32_t nd_i = pn[cpi * 256 + tid];
-            NodeDev nd = nodes[nd_i];
-            ++nv;
-            while (nd.feat >= 0) {
-                const int b = (uint32_t)nd.feat == f ? sb : (int)J.colptr[nd.feat][row];
-                nd_i = b <= (int)nd.thr ? nd.left : nd.left + 1;
-                nd = nodes[nd_i];
-                ++nv;
-            }
-            if (reg)
-                drop_sq += sq_error_fix(nodes, cls, kmax, nd_i, yfv, J.s_perm) - base_err;
-            else
-                drop += (int)base_ok - (int)(nd.leaf_class == yv);
-            const int opi = cpi;
-            next_pair(cpi, cr);
-            if (cpi != opi || g + 1 == k) {
-                if (drop_sq) {
-                    if (lds)
-                        atomicAdd((unsigned long long*)&s_drop64[f], (unsigned long long)drop_sq);
-                    else
-                        atomicAdd((unsigned long long*)&J.imp[f], (unsigned long long)drop_sq);
-                }
-                if (drop) {
-                    if (lds)
-                        atomicAdd(&s_drop[f], drop);
-                    else
-                        atomicAdd((unsigned long long*)&J.imp[f],
-                                  (unsigned long long)(int64_t)drop);
-                }
+        auto begin = [&]() {
+            const int e = __builtin_ctz(turn);
+            turn &= turn - 1u;
+            const uint32_t nf = P.pf[(int)(pos >> (8 * e) & 0xFFu) * 256 + tid] & 0x7FFFFFFFu;
+            if (nf != f) {
+                if (f != 0xFFFFFFFFu) add_drop(f, drop, drop_sq);
                 drop = 0;
                 drop_sq = 0;
+                f = nf;
+            }
+            node = g_src[e * 256 + tid];
+            sbin = (uint32_t)(sbs >> (8 * e)) & 0xFFu;
+        };
+        bool walking = turn != 0;
+        if (walking) begin();
+        while (walking) {
+            const Hop h = load_hop(nodes, node);
+            ++nv;
+            if (h.feat >= 0) {
+                const uint32_t b = (uint32_t)h.feat == f
+                                       ? sbin
+                                       : (uint32_t)ldg(ldg(J.colptr + h.feat) + row);
+                node = b <= h.thr ? h.left : h.left + 1u;
+            } else {
+                if (reg)
+                    drop_sq += sq_error_fix(nodes, cls, kmax, node, yfv, J.s_perm) - base_err;
+                else
+                    drop += (int)base_ok - (int)(h.leaf == yv);
+                walking = turn != 0;
+                if (walking) begin();
             }
         }
+        if (f != 0xFFFFFFFFu) add_drop(f, drop, drop_sq);
     }
     if (lds) {
         __syncthreads();
@@ -239,7 +339,7 @@ __global__ __launch_bounds__(256) void k_permut(JobDev* jobs, const TreeDev* tre
         }
     }
     if (visits) {
-        for (int m = 1; m < 64; m <<= 1) nv += __shfl_xor(nv, m);
+        for (int q = 1; q < 64; q <<= 1) nv += __shfl_xor(nv, q);
         if ((tid & 63) == 0 && nv)
             atomicAdd(visits + ((blockIdx.x * 4u + (uint32_t)(tid >> 6)) & (kAlgWords - 1)), nv);
     }
@@ -374,15 +474,14 @@ __global__ __launch_bounds__(256) void k_kl_base(JobDev* jobs, int j, const Node
 // One thread per (tree, row of the block), rows fastest so that a wave
 // walks one tree for 64 rows (its node and bin loads and its atomics then
 // spread over rows, not over trees meeting at one column): the row's path;
-// for each column on it (first occurrence), the row is re-routed from that
-// node with the column's bin taken from row pi(row), and a different leaf
-// adds its frequency difference to delta[column][row][k] (64-bit two's
-// complement).
+// for each column on it whose bin at row pi(row) turns the other way at one of
+// the column's positions, the row is re-routed from there, and the leaf adds
+// its frequency difference to delta[column][row][k] (64-bit two's complement).
 __global__ __launch_bounds__(256) void k_kl_delta(JobDev* jobs, int j, const NodeDev* nodes,
                                                   const uint32_t* cls, int kmax, uint32_t tree0,
                                                   uint32_t r0, uint32_t rb, const uint32_t* pi,
                                                   unsigned long long* delta, int max_depth) {
-    extern __shared__ uint32_t s_path[];  // [2][max_depth][256]: node, column
+    extern __shared__ uint32_t s_path[];  // the paths; [max_depth][256] source bins
     const JobDev& J = jobs[j];
     if (!J.live) return;
     const int tid = threadIdx.x;
@@ -392,43 +491,50 @@ __global__ __launch_bounds__(256) void k_kl_delta(JobDev* jobs, int j, const Nod
     if (tau >= T || r0 + rr >= (uint32_t)J.n) return;
     const uint32_t row = r0 + rr, src = pi[rr];
     const int K = J.K;
-    uint32_t* pn = s_path;
-    uint32_t* pf = s_path + max_depth * 256;
-    int len = 0;
-    uint32_t node = tree0 + tau;
-    NodeDev nd = nodes[node];
-    while (nd.feat >= 0) {
-        pn[len * 256 + tid] = node;
-        pf[len * 256 + tid] = (uint32_t)nd.feat;
-        ++len;
-        node = (int)J.colptr[nd.feat][row] <= (int)nd.thr ? nd.left : nd.left + 1;
-        nd = nodes[node];
-    }
-    const uint32_t leaf0 = node;
-    const uint32_t N0 = leaf_weight(cls, kmax, leaf0, K);
-    for (int a = 0; a < len; ++a) {
-        const uint32_t f = pf[a * 256 + tid];
-        bool dup = false;
-        for (int b = 0; b < a; ++b) dup |= pf[b * 256 + tid] == f;
-        if (dup) continue;
-        const int sb = J.colptr[f][src];
-        uint32_t ni = pn[a * 256 + tid];
-        NodeDev x = nodes[ni];
-        while (x.feat >= 0) {
-            const int bin = (uint32_t)x.feat == f ? sb : (int)J.colptr[x.feat][row];
-            ni = bin <= (int)x.thr ? x.left : x.left + 1;
-            x = nodes[ni];
+    const PathLds P = path_lds(s_path, max_depth);
+    uint8_t* s_bin = reinterpret_cast<uint8_t*>(s_path + path_lds_words(max_depth));
+    const Walked w = walk_path(J, nodes, tree0 + tau, row, P, tid);
+    const uint32_t N0 = leaf_weight(cls, kmax, w.leaf, K);
+    // the columns' source bins, eight positions' loads in flight
+    for (int a0 = 0; a0 < w.len; a0 += 8) {
+        uint32_t sb[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int a = min(a0 + e, w.len - 1);
+            sb[e] = ldg(ldg(J.colptr + (P.pf[a * 256 + tid] & 0x7FFFFFFFu)) + src);
         }
-        if (ni == leaf0) continue;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (a0 + e < w.len) s_bin[(a0 + e) * 256 + tid] = (uint8_t)sb[e];
+    }
+    // Position by position over the wave's rows (near the root they hold one
+    // column, and the atomics of neighbouring rows share lines; one loop over
+    // each lane's own columns took twice the time).
+    for (int a = 0; a < w.len; ++a) {
+        if (w.dup >> a & 1u) continue;
+        const uint32_t sb = s_bin[a * 256 + tid];
+        uint32_t node = turned_at(P, w, a, sb, tid);
+        if (node == 0xFFFFFFFFu) continue;
+        const uint32_t f = P.pf[a * 256 + tid] & 0x7FFFFFFFu;
+        for (;;) {
+            const Hop h = load_hop(nodes, node);
+            if (h.feat < 0) break;
+            const uint32_t b = (uint32_t)h.feat == f
+                                   ? sb
+                                   : (uint32_t)ldg(ldg(J.colptr + h.feat) + row);
+            node = b <= h.thr ? h.left : h.left + 1u;
+        }
         unsigned long long* d = delta + ((size_t)f * rb + rr) * K;
         if (J.reg) {  // change of the leaf's prediction, in the first slot
-            const long long dv = leaf_pred(nodes, cls, kmax, ni) - leaf_pred(nodes, cls, kmax, leaf0);
+            const long long dv =
+                leaf_pred(nodes, cls, kmax, node) - leaf_pred(nodes, cls, kmax, w.leaf);
             if (dv) atomicAdd(d, (unsigned long long)dv);
             continue;
         }
-        const uint32_t N1 = leaf_weight(cls, kmax, ni, K);
+        const uint32_t N1 = leaf_weight(cls, kmax, node, K);
         for (int k = 0; k < K; ++k) {
-            const uint64_t dv = leaf_freq(cls, kmax, ni, k, N1) - leaf_freq(cls, kmax, leaf0, k, N0);
+            const uint64_t dv =
+                leaf_freq(cls, kmax, node, k, N1) - leaf_freq(cls, kmax, w.leaf, k, N0);
             if (dv) atomicAdd(d + k, (unsigned long long)dv);
         }
     }
@@ -787,7 +893,7 @@ void launch_permut(JobDev* jobs, const TreeDev* trees, const NodeDev* nodes, con
     // (64-bit when the batch has a regression job)
     const int lds_cols = max_pw < 1024 ? max_pw : 1024;
     const int lds_words = lds_cols * (any_reg ? 2 : 1);
-    const size_t lds = ((size_t)2 * max_depth * 256 + lds_words + (size_t)kPermGroup * 256) *
+    const size_t lds = ((size_t)path_lds_words(max_depth) + lds_words + (size_t)kPermGroup * 256) *
                        sizeof(uint32_t);
     hipLaunchKernelGGL(k_permut, dim3((unsigned)((max_n + 255) / 256), (unsigned)n_trees),
                        dim3(256), lds, st, jobs, trees, nodes, cls, kmax, max_depth, lds_cols,
@@ -807,7 +913,8 @@ void launch_kl_block(JobDev* jobs, int j, const NodeDev* nodes, const uint32_t* 
         case 8: hipLaunchKernelGGL(k_kl_base<8>, dim3(g_base), b256, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
         default: hipLaunchKernelGGL(k_kl_base<16>, dim3(g_base), b256, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
     }
-    const size_t lds = (size_t)2 * max_depth * 256 * sizeof(uint32_t);
+    const size_t lds =
+        ((size_t)path_lds_words(max_depth) + (size_t)max_depth * 64) * sizeof(uint32_t);
     const unsigned g_delta = (unsigned)(((uint64_t)rb * T + 255) / 256);
     hipLaunchKernelGGL(k_kl_delta, dim3(g_delta), b256, lds, st, jobs, j, nodes, cls, kmax, tree0,
                        r0, rb, pi, delta, max_depth);
