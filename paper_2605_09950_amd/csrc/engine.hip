@@ -381,6 +381,7 @@ struct Plan {
     // column-major histogram path: levels >= col_level (col_level >= max_D: none)
     int col_level = kColNever, col_waves = 0;
     bool has_cls = false, has_reg = false;
+    int small_rows = 32;  // row limit of the wave path
     int hist_words = 1;        // LDS words per bin of a histogram item
     uint32_t n_gcol = 0, unit_cap = 0, gq_max = 0;
     int64_t max_n = 0;
@@ -515,6 +516,12 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         pl.fw = fw;
     }
     pl.npi = (pl.mtry_cap + pl.fw - 1) / pl.fw;
+    // The wave path's row limit at its default: 32 beside column-major levels
+    // (whose LDS-staged bins are cheaper than the wave path's gathers: 157 ms
+    // at 32, 176 at 64, the 100,000 x 2,000 workload's first iterations), else
+    // 64 (the 64-job batch 158 ms at 32, 137 at 64; 10,000 x 500 82.2 and 79.6;
+    // 7 classes exact 11.5 and 10.7; regression 75.3 and 72.5).
+    pl.small_rows = o.small_rows == 32 && pl.col_level >= pl.max_D ? 64 : o.small_rows;
     if (node_cap >= 0xFFFFFFF0ull || slot_cap * (uint64_t)pl.mtry_cap + n_gcol >= 0xFFFFFFF0ull ||
         small_cap >= 0xFFFFFFF0ull)
         throw Error(BORUTA_E_INVALID_ARG, "problem too large: more than 2^32 tree nodes");
@@ -934,7 +941,7 @@ ForestDev Engine::forest() const {
         F.unit_cap = pl.unit_cap;
         F.col_unit = (uint32_t)O.col_unit;
     }
-    F.small_rows = (uint32_t)O.small_rows;
+    F.small_rows = (uint32_t)pl.small_rows;
     F.mtry_cap = pl.mtry_cap;
     F.draw_seg = 1;
     while (F.draw_seg < (uint32_t)pl.mtry_cap && F.draw_seg < 64u) F.draw_seg <<= 1;
