@@ -323,7 +323,8 @@ struct SlotRec {
 // Per-level counters: the lists of tree level d (small nodes, large-node
 // slots) are counted in ctrs[d]; they are zeroed once per iteration.
 struct LevelCtr {
-    uint32_t unused[2];
+    uint32_t pairs;     // child pairs handed out by k_grow (level 0's record, whole iteration)
+    uint32_t unused;
     uint32_t n_slots;   // large nodes
     uint32_t n_small;   // small nodes
     uint32_t overflow;  // a capacity check failed
@@ -412,6 +413,10 @@ struct ForestDev {
     int32_t item_words;   // words of an item record: 2 + hist_words
     int32_t npi;          // histogram items per large node (draw positions / fw)
     int32_t fw;           // draws per histogram item
+    uint32_t small_head;  // LDS words of a wave-path wave before its counters: the draws'
+                          // round table and the bins by row
+    uint32_t bins_off;    // where the bins by row start there
+    int32_t rowmaj;       // the plan's jobs keep row-major copies of their bins
     uint32_t small_rows;  // a node takes the wave path only up to this many distinct rows
     int32_t mtry_cap;     // row stride of feat
     uint32_t draw_seg;    // lanes per node in k_draws: mtry_cap rounded up to a power

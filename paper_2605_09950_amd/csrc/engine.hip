@@ -48,6 +48,9 @@ void launch_lists(const ForestDev&, int, uint32_t, hipStream_t);
 void launch_col_sort(const ForestDev&, int, uint32_t, hipStream_t);
 size_t hist_col_lds(int, int, uint32_t);
 hipError_t prepare_hist_col(int, int, size_t);
+size_t grow_lds(int, uint32_t, int, uint32_t);
+hipError_t prepare_grow(int, size_t);
+void launch_grow(const ForestDev&, uint32_t, int, uint32_t, hipStream_t);
 void launch_hist_col(const ForestDev&, int, uint32_t, int, uint32_t, hipStream_t);
 // k_importance.hip
 void launch_tree_totals(JobDev*, const TreeDev*, int, uint64_t*, hipStream_t);
@@ -354,7 +357,7 @@ struct Region {
 
 struct JobPlan {
     int64_t n_pad, P;
-    size_t rowmaj = 0;        // row-major widened bins (column-path plans)
+    size_t rowmaj = 0;        // row-major widened bins (rm_stride 0: none)
     uint32_t rm_stride = 0;
     uint32_t gbase;
     uint32_t kl_rb;  // KL importance: rows per block (0: the job does not use it)
@@ -382,9 +385,13 @@ struct Plan {
     int col_level = kColNever, col_waves = 0;
     bool has_cls = false, has_reg = false;
     int small_rows = 32;  // row limit of the wave path
+    bool rowmaj = false;  // the jobs keep row-major copies of their widened bins
+    uint32_t small_head = 0, bins_off = 0;  // LDS head of the wave path (ForestDev)
     int hist_words = 1;        // LDS words per bin of a histogram item
     uint32_t n_gcol = 0, unit_cap = 0, gq_max = 0;
     int64_t max_n = 0;
+    int grow_waves = 0;       // waves per tree of the one-launch growth (0: level kernels)
+    uint32_t grow_cap = 0;    // searched nodes of a tree level it holds
     uint32_t boot_chunk = 0;  // rows per workgroup of the LDS bootstrap counts (0: atomics)
     size_t total = 0;
 };
@@ -573,12 +580,49 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         pl.fitems = r.take(items * 4);
         pl.units = r.take((size_t)pl.unit_cap * sizeof(ColUnit));
         pl.gcolq = r.take(n_gcol * 4);
-        // small nodes gather many drawn columns at few rows: a row-major copy
-        // puts a row's columns in a few cache lines
+    }
+    // Plans with column-major levels (matrices past the last-level cache) keep a
+    // row-major copy of the widened bins for the wave path: a node's draws at one
+    // row lie in a few cache lines there.  (In plans whose columns stay cached it
+    // gained 1-2% at 10,000 x 500 and in the 64-job batch and lost 4% at 7 classes,
+    // 5,003 x 257.)
+    if (pl.col_level < pl.max_D) {
         for (JobPlan& j : pl.jp) {
             j.rm_stride = (uint32_t)((j.pw_cap + 63) / 64 * 64);
             j.rowmaj = r.take((size_t)j.n_pad * j.rm_stride);
         }
+        pl.rowmaj = true;
+    }
+    // with one round of draws per node the bins take the round table's place
+    const uint32_t tab = kDrawTab / 2, bins = pl.rowmaj ? 64 * 68 / 4 : 0;
+    pl.bins_off = pl.mtry_cap <= 64 ? 0 : tab;
+    pl.small_head = std::max(tab, pl.bins_off + bins);
+    // Whole trees in one launch (k_grow), one workgroup per tree: a tree's time
+    // does not depend on the others as long as every tree has a compute unit, and
+    // a level's kernels cost about 35 us however little they hold, so it pays for
+    // few trees of few (row, drawn column) pairs.  Measured per iteration, level
+    // kernels against k_grow, 3 classes, depth 12, at 30, 100, 200, 256, 400 trees:
+    //   1,000 x 20 (6,000 pairs)   589 606 631 646 728 / 349 357 364 366 479 us
+    //   1,000 x 300 (24,000)       582 639 699 739 827 / 522 526 541 551 733
+    //   3,000 x 300 (72,000)       663 774 916 1003 1239 / 871 873 889 909 1419
+    //   10,000 x 300 (240,000)     904 1232 1661 1896 2550 / 1932 2011 2065 2118 3829
+    // (16 waves per tree, 8 past 256 trees: two trees per compute unit).  Chosen
+    // launch shapes are those of the level kernels.
+    const bool shapes = o.small_rows != 32 || o.grid_small || o.grid_hist || o.grid_finalize ||
+                        o.col_level || o.col_unit != 2048 || o.grid_col || o.hist_rb != 8 ||
+                        o.hist_rb_deep != 8 || o.band_level != 6 || o.hist_fw || o.col_waves;
+    if (o.form == BORUTA_FORM_BATCHED && !any_reg && !shapes && pl.col_level >= pl.max_D) {
+        int64_t pairs = 0;
+        for (size_t j = 0; j < specs.size(); ++j)
+            pairs = std::max(pairs, specs[j].n * (int64_t)pl.jp[j].mtry_max);
+        if (pl.T_total <= 256 && (pairs <= 24000 || (pairs <= 72000 && pl.T_total >= 192)))
+            pl.grow_waves = 16;
+        else if (pl.T_total <= 512 && pairs <= 24000)
+            pl.grow_waves = 8;
+        pl.grow_cap = (uint32_t)((pl.max_n + 1) / 2);
+        if (pl.max_n >= 65536 ||
+            grow_lds(pl.kmax, pl.small_head, pl.grow_waves, pl.grow_cap) + 2048 > kLdsPerWorkgroup)
+            pl.grow_waves = 0;
     }
     pl.total = r.total + 256;
     return pl;
@@ -908,6 +952,11 @@ void Engine::setup(std::vector<int>& status) {
             launch_fill_u32(at<uint32_t>(pl.fcnt), pl.n_gcol, 0u, st);
         }
     }
+    if (pl.grow_waves && prepare_grow(pl.kmax, grow_lds(pl.kmax, pl.small_head, pl.grow_waves, pl.grow_cap)) !=
+                             hipSuccess) {
+        (void)hipGetLastError();
+        pl.grow_waves = 0;  // the level kernels
+    }
     h2d(at<JobDev>(pl.jobs), hj.data(), hj.size() * sizeof(JobDev));
     // level counters, and the accumulated capacity flags after them
     launch_fill_u32(at<uint32_t>(pl.ctrs), (size_t)(pl.max_D + 2) * sizeof(LevelCtr) / 4, 0u, st);
@@ -942,6 +991,9 @@ ForestDev Engine::forest() const {
         F.col_unit = (uint32_t)O.col_unit;
     }
     F.small_rows = (uint32_t)pl.small_rows;
+    F.small_head = pl.small_head;
+    F.bins_off = pl.bins_off;
+    F.rowmaj = pl.rowmaj ? 1 : 0;
     F.mtry_cap = pl.mtry_cap;
     F.draw_seg = 1;
     while (F.draw_seg < (uint32_t)pl.mtry_cap && F.draw_seg < 64u) F.draw_seg <<= 1;
@@ -1007,7 +1059,7 @@ void Engine::enqueue_iteration() {
     const size_t h_whole = clock.begin(&iter_stat, st);
     launch_active(djobs, nj, st);
     launch_shadow(djobs, nj, pl.max_n, pl.max_sha, st);
-    if (pl.col_level < pl.max_D) launch_rowmaj(djobs, nj, pl.max_n, pl.max_pw, st);
+    if (pl.rowmaj) launch_rowmaj(djobs, nj, pl.max_n, pl.max_pw, st);
     launch_boot_draw(djobs, dtrees, (int)n_trees, pl.max_n, pl.boot_chunk, st);
 
     ForestDev F = forest();
@@ -1020,8 +1072,14 @@ void Engine::enqueue_iteration() {
     F.small_out = small[0];
     F.slot_node_out = slots[0];
     launch_boot_compact(F, n_trees, st);
+    // kernel statistics time the level kernels
+    const bool grow = pl.grow_waves && !stats;
+    if (grow) {
+        launch_grow(F, n_trees, pl.grow_waves, pl.grow_cap, st);
+        HIPC(hipGetLastError());
+    }
     const uint32_t g_col = O.grid_col ? (uint32_t)O.grid_col : level_grid(pl.unit_cap, 1, 2048);
-    for (int d = 0; d < n_levels; ++d) {
+    for (int d = 0; d < (grow ? 0 : n_levels); ++d) {
         // Level d holds at most n_trees * 2^d nodes: the shallow levels launch
         // no more workgroups than that bound can use (a chosen grid size is
         // an upper limit), the deep ones are held to the plan's capacities.

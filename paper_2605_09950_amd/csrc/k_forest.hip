@@ -138,6 +138,7 @@ __global__ __launch_bounds__(1024) void k_boot_compact(ForestDev F0) {
                                               (int64_t)s_tsum, 0u)
                              : write_node(F, J, g, g, 1u, 0u, s_base_in, tot, 0u, counts);
         enqueue_nodes(F, J, g, &kind, 1);
+        F.kinds[g] = (uint8_t)kind;  // k_grow starts from it
     }
 }
 
@@ -169,23 +170,58 @@ __device__ __forceinline__ uint32_t readlane_w(uint32_t v, int src) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, src);
 }
 
-// Words of LDS per wave of the small-node kernel: the permutation round table
-// (kDrawTab 16-bit entries), the rows' counters, two packed histograms.
-__host__ __device__ constexpr uint32_t small_lds_words(int words) {
-    return kDrawTab / 2 + (uint32_t)words * (64u + 512u);
+// LDS of a wave of the small-node kernels: the head -- the permutation round
+// table and the node's bins by row (which take the table's place where one
+// round of 64 draws serves every node) --, then the rows' counters and two
+// packed histograms, or a regression node's rows.
+constexpr uint32_t kBinStride = 68;  // bytes per row: 17 words, so that a column's bytes of
+                                     // different rows lie in different banks
+__host__ __device__ constexpr uint32_t small_lds_words(uint32_t head, int words) {
+    return head + (uint32_t)words * (64u + 512u);
 }
 
-// lds: the wave's LDS region of small_lds_words(WORDS) words
-template <int WORDS>
+// A node's bins of one round of draws, read row by row from the row-major copy
+// (plans with column-major levels) into LDS: a load covers 64 / F2 rows x F2 draws (F2: the draws rounded up to a
+// power of two), so it touches a row's few cache lines once instead of one line
+// per lane, and the passes then take their bins from LDS.  myf: lane q holds draw
+// q's widened column; row: lane i < len holds the node's row i.
+__device__ __forceinline__ void load_bins(const JobDev& J, uint8_t* bins, int myf, uint32_t row,
+                                          int len, int nq) {
+    const int lane = threadIdx.x & 63;
+    int F2 = 1;
+    while (F2 < nq) F2 <<= 1;
+    const int per = 64 / F2, rr = lane / F2, f = lane & (F2 - 1);
+    const uint32_t c = (uint32_t)__shfl(myf, f < nq ? f : 0);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the table's or earlier bins' reads
+    for (int r0 = 0; r0 < len; r0 += 8 * per) {
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int r = min(r0 + u * per + rr, len - 1);
+            const uint32_t i = (uint32_t)__shfl((int)row, r);
+            v[u] = ldg(J.rowmaj + (size_t)i * J.rm_stride + c);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int r = r0 + u * per + rr;
+            if (r < len) bins[r * (int)kBinStride + f] = (uint8_t)v[u];
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+}
+
+// lds: the wave's LDS region of small_lds_words(F.small_head, WORDS) words
+// RM: the job keeps a row-major copy of its bins
+template <int WORDS, bool RM>
 __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, const NodeDev& nd,
                                            const TreeDev& tr, JobDev& J, SmallOut& out,
                                            uint32_t* lds) {
     uint16_t* tab = reinterpret_cast<uint16_t*>(lds);
-    uint32_t* scnt = lds + kDrawTab / 2;    // [WORDS][64] the rows' counter words
+    uint8_t* bins = reinterpret_cast<uint8_t*>(lds + F.bins_off);  // [64][kBinStride]
+    uint32_t* scnt = lds + F.small_head;    // [WORDS][64] the rows' counter words
     uint32_t* hist = scnt + WORDS * 64;     // [2][WORDS][256] packed histograms
     const int lane = threadIdx.x & 63;
     const int B = J.B, mtry = J.mtry;
-    const bool rowmaj = J.rowmaj != nullptr;
     const size_t tbase = (size_t)tr.tau * J.rstride + nd.seg;
     const uint32_t* rin = J.rec[F.parity] + tbase;
     uint32_t* rout = J.rec[F.parity ^ 1] + tbase;
@@ -247,26 +283,29 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
             scnt[w * 64 + lane] = seg == 0 && valid && yw == (uint32_t)w ? inc : 0u;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
-    const uint8_t* rowbase = rowmaj ? J.rowmaj + (size_t)row * J.rm_stride : J.colbase + row;
+    const uint8_t* rowbase = J.colbase + row;
+    int myf = 0;  // the round's draw of this lane
     for (int q0 = 0; q0 < mtry; q0 += 64) {
         const int nq = min(64, mtry - q0);
-        const int myf =
+        myf =
             lane < nq ? (int)(use_tab ? perm_apply_tab(P, tab, (uint32_t)(q0 + lane))
                                       : perm_apply(P, (uint32_t)(q0 + lane)))
                       : 0;
-        // the drawn feature's bins of a row: byte myoff of the row in the
-        // row-major copy, or 256 * myoff bytes from the row in column 0
-        uint32_t myoff = (uint32_t)myf;
-        if (!rowmaj)
+        // the drawn feature's bins: by row in LDS, or in its column, 256 * myoff
+        // bytes from the start of the region
+        uint32_t myoff = 0;
+        if constexpr (RM)
+            load_bins(J, bins, myf, row, len, nq);
+        else
             myoff = lane < nq ? (uint32_t)((uint64_t)(ldg(J.colptr + myf) - J.colbase) >> 8) : 0u;
         const int passes = (nq + G - 1) / G;
         // The bin load is unconditional (lanes without a row read row 0, lanes
         // past the drawn features read the first one) so that blocks of loads
         // issue back to back; eval() masks what does not count.
         auto gather = [&](int pass) {
-            const int qq = pass * G + seg;
-            const uint32_t off = (uint32_t)__shfl((int)myoff, qq < nq ? qq : 0);
-            return (int)ldg(rowmaj ? rowbase + off : rowbase + (uint64_t)off * 256u);
+            const int qq = pass * G + seg, qc = qq < nq ? qq : 0;
+            if constexpr (RM) return (int)bins[(valid ? i : 0) * (int)kBinStride + qc];
+            else return (int)ldg(rowbase + (uint64_t)(uint32_t)__shfl((int)myoff, qc) * 256u);
         };
         auto eval = [&](int pass, int raw) {
             const int qq = pass * G + seg;
@@ -347,6 +386,10 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
                 for (int w = 0; w < WORDS; ++w) la[w] = acc[w];
             }
         };
+        if constexpr (RM) {
+            for (int pass = 0; pass < passes; ++pass) eval(pass, gather(pass));
+            continue;
+        }
         // bins of kPF passes are in flight while the previous kPF are scored
         constexpr int kPF = 2;
         int bq[kPF];
@@ -427,7 +470,10 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
         best.sl = c.sl;
         best.sr = c.sr;
         const uint32_t q = (uint32_t)best.q;
-        best.f = (int)(use_tab ? perm_apply_tab(P, tab, q) : perm_apply(P, q));
+        if (mtry <= 64)  // one round: the draw is still in its lane
+            best.f = __builtin_amdgcn_readlane(myf, best.q);
+        else
+            best.f = (int)(use_tab ? perm_apply_tab(P, tab, q) : perm_apply(P, q));
     }
     if (best.nl == 0 || !cand_positive(best, S, N)) {  // stays the leaf it was created as
         if (lane == 0) mark_unused_pair(F, out.child);
@@ -435,8 +481,12 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
     }
     // partition with the lanes of segment 0
     const bool mine = seg == 0 && valid;
-    const uint8_t* col = ldg(J.colptr + best.f);
-    const bool left = mine && (int)ldg(col + row) <= best.b;
+    int wb;  // the row's bin in the winning column
+    if (RM && mtry <= 64)
+        wb = bins[(valid ? i : 0) * (int)kBinStride + best.q];
+    else
+        wb = (int)ldg(ldg(J.colptr + best.f) + row);
+    const bool left = mine && wb <= best.b;
     const uint64_t lm = __ballot(left), vm = __ballot(mine);
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const uint32_t nl_rows = (uint32_t)__popcll(lm);
@@ -461,8 +511,21 @@ __device__ __forceinline__ void small_node(const ForestDev& F, uint32_t id, cons
 // The small nodes of tree level `level`: all of them (count from the level's
 // counters, grid-stride) or, with an explicit count, list entries
 // [first, first + count).  WORDS: counter words of the plan's widest job; a
-// job of fewer classes takes the narrower form.
-template <int WORDS>
+// job of fewer classes takes the narrower form.  RM: the plan's jobs keep
+// row-major copies.
+template <int WORDS, bool RM>
+__device__ __forceinline__ void small_node_of(const ForestDev& F, uint32_t id, const NodeDev& nd,
+                                              const TreeDev& tr, JobDev& J, SmallOut& out,
+                                              uint32_t* lds) {
+    if (WORDS == 1 || J.K <= 4)
+        small_node<1, RM>(F, id, nd, tr, J, out, lds);
+    else if (WORDS == 2 || J.K <= 8)
+        small_node<WORDS == 1 ? 1 : 2, RM>(F, id, nd, tr, J, out, lds);
+    else
+        small_node<WORDS, RM>(F, id, nd, tr, J, out, lds);
+}
+
+template <int WORDS, bool RM>
 __global__ __launch_bounds__(256) void k_split_small(ForestDev F0, int level, uint32_t first,
                                                      uint32_t count) {
     const ForestDev F = level_view(F0, level);
@@ -470,9 +533,10 @@ __global__ __launch_bounds__(256) void k_split_small(ForestDev F0, int level, ui
         first = 0;
         count = level_small(F0, level);
     }
-    extern __shared__ uint4 lds_raw[];  // [4][small_lds_words(WORDS)]
+    extern __shared__ uint4 lds_raw[];  // [4][small_lds_words(F.small_head, WORDS)]
     const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
-    uint32_t* lds = reinterpret_cast<uint32_t*>(lds_raw) + wave * small_lds_words(WORDS);
+    uint32_t* lds =
+        reinterpret_cast<uint32_t*>(lds_raw) + wave * small_lds_words(F.small_head, WORDS);
     unsigned long long alg = 0;  // statistics
     for (uint32_t li = blockIdx.x * 4u + (uint32_t)wave; li < count; li += gridDim.x * 4u) {
         SmallOut o;
@@ -484,12 +548,7 @@ __global__ __launch_bounds__(256) void k_split_small(ForestDev F0, int level, ui
         const TreeDev tr = F.trees[nd.tree];
         JobDev& J = F.jobs[tr.job];
         if (F.has_reg && J.reg) continue;  // k_split_small_reg
-        if (WORDS == 1 || J.K <= 4)
-            small_node<1>(F, id, nd, tr, J, o, lds);
-        else if (WORDS == 2 || J.K <= 8)
-            small_node<WORDS == 1 ? 1 : 2>(F, id, nd, tr, J, o, lds);
-        else
-            small_node<WORDS>(F, id, nd, tr, J, o, lds);
+        small_node_of<WORDS, RM>(F, id, nd, tr, J, o, lds);
         // what the children need next; the next level's lists are built from these
         if (lane == 0) F.kinds[first + li] = (uint8_t)(o.kinds[0] | o.kinds[1] << 2);
         alg += o.alg;
@@ -513,13 +572,13 @@ __global__ __launch_bounds__(256) void k_split_small(ForestDev F0, int level, ui
 // the levels whose nodes have a few dozen rows (at the deepest level 662 us of
 // histograms, 165 of partitions and 66 of draws became 221, 15 and 99 beside 182
 // for the nodes that stay).
-constexpr uint32_t kSmallRegLds = kDrawTab / 2 + 64 * 4;  // words per wave
+__host__ __device__ constexpr uint32_t small_reg_words(uint32_t head) { return head + 64u * 4u; }
 
 __device__ __forceinline__ void small_node_reg(const ForestDev& F, uint32_t id, const NodeDev& nd,
                                                const TreeDev& tr, JobDev& J, SmallOut& out,
                                                uint32_t* lds) {
     uint16_t* tab = reinterpret_cast<uint16_t*>(lds);
-    double2* rows = reinterpret_cast<double2*>(lds + kDrawTab / 2);  // [64] (w, w y)
+    double2* rows = reinterpret_cast<double2*>(lds + F.small_head);  // [64] (w, w y)
     const int lane = threadIdx.x & 63;
     const int B = J.B, mtry = J.mtry;
     const size_t tbase = (size_t)tr.tau * J.rstride + nd.seg;
@@ -555,10 +614,10 @@ __device__ __forceinline__ void small_node_reg(const ForestDev& F, uint32_t id, 
     int ld = 0, lb = 0;                    // its draw position and threshold
     const bool rank = F.split_rank != 0;
     const int abase = (lane - i) << 2;
+    int myf = 0;  // the round's draw of this lane
     for (int q0 = 0; q0 < mtry; q0 += 64) {
         const int nq = min(64, mtry - q0);
-        const int myf =
-            lane < nq ? (int)(use_tab ? perm_apply_tab(P, tab, (uint32_t)(q0 + lane))
+        myf = lane < nq ? (int)(use_tab ? perm_apply_tab(P, tab, (uint32_t)(q0 + lane))
                                       : perm_apply(P, (uint32_t)(q0 + lane)))
                       : 0;
         const uint32_t myoff =
@@ -667,8 +726,11 @@ __device__ __forceinline__ void small_node_reg(const ForestDev& F, uint32_t id, 
         best.pad = 0;
         best.sl = (uint64_t)tl;
         best.sr = (uint64_t)(Ti - tl);
-        best.f = (int)(use_tab ? perm_apply_tab(P, tab, (uint32_t)best.q)
-                               : perm_apply(P, (uint32_t)best.q));
+        if (mtry <= 64)  // one round: the draw is still in its lane
+            best.f = __builtin_amdgcn_readlane(myf, best.q);
+        else
+            best.f = (int)(use_tab ? perm_apply_tab(P, tab, (uint32_t)best.q)
+                                   : perm_apply(P, (uint32_t)best.q));
     }
     if (best.nl == 0 || reg_gap(best) == 0) {  // no decrease: stays the leaf it was created as
         if (lane == 0) mark_unused_pair(F, out.child);
@@ -700,9 +762,9 @@ __global__ __launch_bounds__(256) void k_split_small_reg(ForestDev F0, int level
         first = 0;
         count = level_small(F0, level);
     }
-    extern __shared__ uint4 lds_raw[];  // [4][kSmallRegLds]
+    extern __shared__ uint4 lds_raw[];  // [4][small_reg_words(F.small_head)]
     const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
-    uint32_t* lds = reinterpret_cast<uint32_t*>(lds_raw) + wave * kSmallRegLds;
+    uint32_t* lds = reinterpret_cast<uint32_t*>(lds_raw) + wave * small_reg_words(F.small_head);
     unsigned long long alg = 0;
     for (uint32_t li = blockIdx.x * 4u + (uint32_t)wave; li < count; li += gridDim.x * 4u) {
         SmallOut o;
@@ -2040,13 +2102,12 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level, uint3
 template <bool REG>
 __device__ __forceinline__ uint32_t partition_rows(const ForestDev& F, const JobDev& J,
                                                    const TreeDev& tr, const NodeDev& nd,
-                                                   const SlotRec& sr, const Cand& best,
-                                                   const uint8_t* col, uint32_t len) {
+                                                   const uint32_t* recs, const int64_t* wy,
+                                                   const Cand& best, const uint8_t* col,
+                                                   uint32_t len) {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t* recs = sr.recs;
     const size_t seg = (size_t)tr.tau * J.rstride + nd.seg;
     uint32_t* rout = J.rec[F.parity ^ 1] + seg;
-    const int64_t* wy = REG ? sr.wy : nullptr;
     int64_t* wout = REG ? J.wy[F.parity ^ 1] + seg : nullptr;
     uint32_t runl = 0, runr = 0;
     auto block = [&](uint32_t blk, auto nb) {
@@ -2132,7 +2193,7 @@ __device__ void finalize_reg(const ForestDev& F, JobDev& J, const TreeDev& tr, u
         return;
     }
     const bool part = (int)nd.depth + 1 < J.D;
-    const uint32_t runl = partition_rows<true>(F, J, tr, nd, sr, best, ldg(J.colptr + best.f), part ? sr.len : 0u);
+    const uint32_t runl = partition_rows<true>(F, J, tr, nd, sr.recs, sr.wy, best, ldg(J.colptr + best.f), part ? sr.len : 0u);
     if (lane == 0) {
         int kinds[2];
         split_node_reg(F, J, tr, sr.id, nd, best, runl, reg_gain_fix(best, J.s_gain), child,
@@ -2265,13 +2326,295 @@ __global__ __launch_bounds__(256) void k_split_finalize(ForestDev F0, int level,
         // the maximum depth with two or more classes (which implies two or
         // more distinct rows); other children are final leaves.
         const bool part = (int)nd.depth + 1 < J.D && (nzl >= 2 || nzr >= 2);
-        const uint32_t runl = partition_rows<false>(F, J, tr, nd, sr, best, ldg(J.colptr + best.f), part ? sr.len : 0u);
+        const uint32_t runl = partition_rows<false>(F, J, tr, nd, sr.recs, nullptr, best, ldg(J.colptr + best.f), part ? sr.len : 0u);
         if (lane == 0) {
             int kinds[2];
             split_node(F, J, tr, id, nd, best, runl, cl, cr, cand_gain_fix(best, S, N), child,
                        kinds);
             F.kinds[F.n_small_cur + slot] = (uint8_t)(kinds[0] | kinds[1] << 2);
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Whole trees in one launch: one workgroup per tree grows all its levels, with
+// workgroup barriers in place of the level kernels' launches.  For jobs of few
+// rows, whose level kernels are launch and dependent-load latency (a 500 x 20
+// forest of 50 trees of depth 8: 56 launches an iteration, each 3-15 us; 20
+// iterations 7.4 ms, 3.7 with this kernel; the engine's rule says where).  The
+// level's node lists live in LDS; a wave takes a small node as k_split_small
+// does, and a group of g waves a large one: each wave counts and scans its
+// share of the drawn features (draw = lane * g + its place in the group), the
+// group's first wave picks the best and partitions.  g falls from all waves to
+// one as a level's large nodes become as many as the waves.  Trees, child pairs
+// and results are those of the level kernels (child pairs are handed out per
+// tree and level instead of per level).
+struct GrowLds {
+    uint32_t cnt[2][2];      // [level parity] small, large nodes of the level
+    uint32_t base;           // first child pair of the level
+    uint32_t best[16][12];   // a wave's best: score, bin, draw, left counts
+};
+
+// Children of a searched node into the next level's lists (one lane).
+__device__ __forceinline__ void grow_push(GrowLds& G, uint32_t* next, uint32_t cap, int parity,
+                                          const int* kinds, uint32_t child) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        if (kinds[c] == kSmall) next[atomicAdd(&G.cnt[parity][0], 1u)] = child + c;
+        if (kinds[c] == kLarge) next[cap - 1u - atomicAdd(&G.cnt[parity][1], 1u)] = child + c;
+    }
+}
+
+template <int KMAX>
+__device__ __forceinline__ void grow_large(const ForestDev& F, JobDev& J, const TreeDev& tr,
+                                           GrowLds& G, const uint32_t* list, uint32_t cap,
+                                           uint32_t ns, uint32_t nl, uint32_t* next, int nparity,
+                                           uint32_t* lds, uint32_t* hist, uint32_t wave,
+                                           uint32_t nw) {
+    constexpr int C = item_counts<KMAX, false>(), PW = pk_words(KMAX);
+    const int lane = threadIdx.x & 63;
+    uint16_t* tab = reinterpret_cast<uint16_t*>(lds);
+    const int B = J.B, mtry = J.mtry;
+    const uint32_t K = (uint32_t)J.K;
+    uint32_t g = nw;
+    while (g > 1u && (nl * g > nw || g > (uint32_t)mtry)) g >>= 1;
+    const uint32_t npr = nw / g, sub = wave % g;
+    for (uint32_t i0 = 0; i0 < nl; i0 += npr) {
+        const uint32_t i = i0 + wave / g;
+        const bool on = i < nl;  // uniform over the wave
+        const uint32_t id = uniform(on ? list[cap - 1u - i] : 0u);
+        const NodeDev nd = F.nodes[on ? id : 0u];
+        const uint32_t N = nd.n, len = uniform(nd.len);
+        const uint32_t* recs = J.rec[F.parity] + (size_t)tr.tau * J.rstride + nd.seg;
+        const CountForm cf = count_form<KMAX>(N, K);
+        uint32_t cnode[KMAX], pk[PW];
+        ItemBest best;
+        best.q = -1.0f;
+        best.b = 0;
+        uint32_t draw = 0, bl[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) bl[c] = 0;
+        if (on) {
+#pragma unroll
+            for (int c = 0; c < KMAX; ++c)
+                cnode[c] = (uint32_t)c < K ? F.cls[(size_t)id * F.kmax + c] : 0u;
+#pragma unroll
+            for (int w = 0; w < PW; ++w) {
+                uint32_t v8 = 0, v16 = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (4 * w + k < KMAX) v8 |= cnode[4 * w + k < KMAX ? 4 * w + k : 0] << (8 * k);
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    if (2 * w + k < KMAX) v16 |= cnode[2 * w + k < KMAX ? 2 * w + k : 0] << (16 * k);
+                pk[w] = cf.fb == 8u ? v8 : v16;
+            }
+            const KeyedPerm P = make_perm(J.seed_lo, J.seed_hi, kMtry, (uint32_t)J.t,
+                                          (uint32_t)tr.tau, nd.heap, 0u, (uint64_t)J.p_w);
+            const bool use_tab = (P.rounds << P.half) <= kDrawTab;
+            if (use_tab) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // earlier lookups
+                for (uint32_t e = (uint32_t)lane; e < (P.rounds << P.half); e += 64u)
+                    tab[e] = (uint16_t)perm_round(P, e >> P.half, e & P.mask);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            }
+            for (uint32_t q0 = sub; q0 < (uint32_t)mtry; q0 += 64u * g) {
+                const uint32_t q = q0 + (uint32_t)lane * g;
+                const bool mine = q < (uint32_t)mtry;
+                const uint32_t f = use_tab ? perm_apply_tab(P, tab, mine ? q : 0u)
+                                           : perm_apply(P, mine ? q : 0u);
+                const uint32_t off =
+                    (uint32_t)((uint64_t)(ldg(J.colptr + f) - J.colbase) >> 8);
+                const uint32_t n_here = min(64u, ((uint32_t)mtry - q0 + g - 1u) / g);
+                for (uint32_t t = 0; t < n_here; ++t) {
+                    const uint8_t* col =
+                        J.colbase + (uint64_t)readlane_w(off, (int)t) * 256u;
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // earlier reads
+#pragma unroll
+                    for (int w = 0; w < C; ++w)
+                        if ((uint32_t)w < cf.words)
+                            reinterpret_cast<uint4*>(hist)[w * 64 + lane] =
+                                make_uint4(0u, 0u, 0u, 0u);
+                    int b0 = 0, b1 = 0;
+                    auto batch = [&](uint32_t r0, auto nb) {
+                        constexpr int NB = decltype(nb)::value;
+                        uint32_t r[NB], b[NB];
+#pragma unroll
+                        for (int u = 0; u < NB; ++u) r[u] = rec_raw(recs, r0 + u * 64 + lane, len);
+#pragma unroll
+                        for (int u = 0; u < NB; ++u) b[u] = ldg(col + rec_row(r[u]));
+#pragma unroll
+                        for (int u = 0; u < NB; ++u)
+                            if (r0 + u * 64 + lane < len) count_row<KMAX>(hist, cf, r[u], b[u]);
+                        b0 = (int)b[0];
+                        b1 = (int)b[1];
+                    };
+                    if (len <= 128u)
+                        batch(0u, std::integral_constant<int, 2>{});
+                    else
+                        for (uint32_t r0 = 0; r0 < len; r0 += 512u)
+                            batch(r0, std::integral_constant<int, 8>{});
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    uint32_t l[C];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) l[c] = 0;
+                    const ItemBest r = scan_item<KMAX, false>(hist, cf, K, len, b0, b1, B, pk,
+                                                              cnode, N, F.split_rank, l);
+                    // draws in order: a strictly better score replaces
+                    bool better = r.q >= 0.0f;
+                    if (better && best.q >= 0.0f) {
+                        if (F.split_rank &&
+                            (r.q < fp32_floor(best.q) || best.q < fp32_floor(r.q)))
+                            better = r.q > best.q;
+                        else
+                            better = cand_better(cand_of<KMAX, false>(l, cf.fb, r.b, cnode, N),
+                                                 cand_of<KMAX, false>(bl, cf.fb, best.b, cnode, N));
+                    }
+                    if (better) {
+                        best = r;
+                        draw = q0 + t * g;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) bl[c] = l[c];
+                    }
+                }
+            }
+        }
+        if (g > 1u) {  // the same for every wave of the workgroup
+            if (lane == 0) {
+                G.best[wave][0] = __float_as_uint(best.q);
+                G.best[wave][1] = (uint32_t)best.b;
+                G.best[wave][2] = draw;
+#pragma unroll
+                for (int c = 0; c < C; ++c) G.best[wave][3 + c] = bl[c];
+            }
+            __syncthreads();
+            if (on && sub == 0u) {
+                for (uint32_t o = 1; o < g; ++o) {
+                    const uint32_t* e = G.best[wave + o];
+                    ItemBest r;
+                    r.q = __uint_as_float(uniform(e[0]));
+                    r.b = (int)uniform(e[1]);
+                    const uint32_t rd = uniform(e[2]);
+                    if (r.q < 0.0f) continue;
+                    uint32_t l[C];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) l[c] = uniform(e[3 + c]);
+                    bool better = best.q < 0.0f;
+                    if (!better) {
+                        if (F.split_rank &&
+                            (r.q < fp32_floor(best.q) || best.q < fp32_floor(r.q))) {
+                            better = r.q > best.q;
+                        } else {  // exact; ties to the earlier draw
+                            const Cand x = cand_of<KMAX, false>(l, cf.fb, r.b, cnode, N);
+                            const Cand y = cand_of<KMAX, false>(bl, cf.fb, best.b, cnode, N);
+                            better = cand_better(x, y) || (rd < draw && !cand_better(y, x));
+                        }
+                    }
+                    if (better) {
+                        best = r;
+                        draw = rd;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) bl[c] = l[c];
+                    }
+                }
+            }
+        }
+        if (on && sub == 0u) {
+            const uint32_t child = F.next_base + 2u * (ns + i);
+            Cand c;
+            c.nl = 0;
+            uint64_t S = 0;
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k) S += (uint64_t)cnode[k] * cnode[k];
+            if (best.q >= 0.0f) c = cand_of<KMAX, false>(bl, cf.fb, best.b, cnode, N);
+            if (c.nl == 0 || !cand_positive(c, S, N)) {  // stays the leaf it was created as
+                if (lane == 0) mark_unused_pair(F, child);
+            } else {
+                const KeyedPerm P = make_perm(J.seed_lo, J.seed_hi, kMtry, (uint32_t)J.t,
+                                              (uint32_t)tr.tau, nd.heap, 0u, (uint64_t)J.p_w);
+                c.q = (int)draw;
+                c.f = (int)((P.rounds << P.half) <= kDrawTab ? perm_apply_tab(P, tab, draw)
+                                                             : perm_apply(P, draw));
+                uint32_t cl[16], cr[16];
+                int nzl = 0, nzr = 0;
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    cl[k] = k < KMAX ? left_count<KMAX, false>(bl, cf.fb, k % KMAX) : 0u;
+                    cr[k] = (k < KMAX ? cnode[k % KMAX] : 0u) - cl[k];
+                    nzl += cl[k] != 0;
+                    nzr += cr[k] != 0;
+                }
+                const bool part = (int)nd.depth + 1 < J.D && (nzl >= 2 || nzr >= 2);
+                const uint32_t runl = partition_rows<false>(F, J, tr, nd, recs, nullptr, c,
+                                                            ldg(J.colptr + c.f), part ? len : 0u);
+                if (lane == 0) {
+                    int kinds[2];
+                    split_node(F, J, tr, id, nd, c, runl, cl, cr, cand_gain_fix(c, S, N), child,
+                               kinds);
+                    grow_push(G, next, cap, nparity, kinds, child);
+                }
+            }
+        }
+        if (g > 1u) __syncthreads();  // the waves' bests are rewritten
+    }
+}
+
+template <int KMAX>
+__global__ __launch_bounds__(1024) void k_grow(ForestDev F0, uint32_t cap) {
+    constexpr int WORDS = KMAX <= 4 ? 1 : (KMAX <= 8 ? 2 : 4);
+    // [waves][small_lds_words(F.small_head, WORDS)], then [2][cap] node lists: small nodes
+    // from the front, large ones from the back
+    extern __shared__ uint4 lds_raw[];
+    __shared__ GrowLds G;
+    const uint32_t g = blockIdx.x;
+    const TreeDev tr = F0.trees[g];
+    JobDev& J = F0.jobs[tr.job];
+    if (!J.live) return;  // the whole workgroup
+    const int lane = threadIdx.x & 63;
+    const uint32_t wave = uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    const uint32_t region = small_lds_words(F0.small_head, WORDS);
+    uint32_t* lds = reinterpret_cast<uint32_t*>(lds_raw) + wave * region;
+    uint32_t* hist = lds + F0.small_head + WORDS * 64;
+    uint32_t* lists = reinterpret_cast<uint32_t*>(lds_raw) + nw * region;
+    if (threadIdx.x == 0) {
+        const int kind = F0.kinds[g];
+        G.cnt[0][0] = kind == kSmall;
+        G.cnt[0][1] = kind == kLarge;
+        lists[kind == kLarge ? cap - 1u : 0u] = g;
+    }
+    __syncthreads();
+    ForestDev F = F0;
+    for (int d = 0; d < J.D; ++d) {
+        const int p = d & 1;
+        const uint32_t ns = G.cnt[p][0], nl = G.cnt[p][1];
+        if (ns + nl == 0u) break;
+        if (threadIdx.x == 0) {
+            G.base = F.n_roots + 2u * atomicAdd(&F.ctrs[0].pairs, ns + nl);
+            G.cnt[p ^ 1][0] = G.cnt[p ^ 1][1] = 0;
+            if (d > 0) {  // the roots were counted when they were made
+                if (ns) atomicAdd(&F.ctrs[d].n_small, ns);
+                if (nl) atomicAdd(&F.ctrs[d].n_slots, nl);
+            }
+        }
+        __syncthreads();
+        const uint32_t* cur = lists + (size_t)p * cap;
+        uint32_t* next = lists + (size_t)(p ^ 1) * cap;
+        F.parity = p;
+        F.ctr = F.ctrs + d + 1;
+        F.next_base = G.base;
+        if (nl)
+            grow_large<KMAX>(F, J, tr, G, cur, cap, ns, nl, next, p ^ 1, lds, hist, wave, nw);
+        for (uint32_t i = wave; i < ns; i += nw) {
+            SmallOut o;
+            o.kinds[0] = o.kinds[1] = kLeaf;
+            o.child = F.next_base + 2u * i;
+            o.alg = 0;
+            const uint32_t id = uniform(cur[i]);
+            const NodeDev nd = F.nodes[id];
+            small_node_of<WORDS, false>(F, id, nd, tr, J, o, lds);
+            if (lane == 0) grow_push(G, next, cap, p ^ 1, o.kinds, o.child);
+        }
+        __syncthreads();
     }
 }
 
@@ -2393,16 +2736,24 @@ void launch_split_small(const ForestDev& F, int level, uint32_t first, uint32_t 
     const dim3 grid(grid_wg);
     if (F.has_reg)
         hipLaunchKernelGGL(k_split_small_reg, grid, dim3(256),
-                           (size_t)4 * kSmallRegLds * sizeof(uint32_t), st, F, level, first,
+                           (size_t)4 * small_reg_words(F.small_head) * sizeof(uint32_t), st, F, level, first,
                            count);
     if (!F.has_cls) return;
     const int words = F.kmax <= 4 ? 1 : (F.kmax <= 8 ? 2 : 4);
-    const size_t lds = (size_t)4 * small_lds_words(words) * sizeof(uint32_t);
+    const size_t lds = (size_t)4 * small_lds_words(F.small_head, words) * sizeof(uint32_t);
+#define BORUTA_SMALL(W)                                                                         \
+    if (F.rowmaj)                                                                               \
+        hipLaunchKernelGGL((k_split_small<W, true>), grid, dim3(256), lds, st, F, level, first, \
+                           count);                                                              \
+    else                                                                                        \
+        hipLaunchKernelGGL((k_split_small<W, false>), grid, dim3(256), lds, st, F, level,       \
+                           first, count);
     switch (words) {
-        case 1: hipLaunchKernelGGL(k_split_small<1>, grid, dim3(256), lds, st, F, level, first, count); break;
-        case 2: hipLaunchKernelGGL(k_split_small<2>, grid, dim3(256), lds, st, F, level, first, count); break;
-        default: hipLaunchKernelGGL(k_split_small<4>, grid, dim3(256), lds, st, F, level, first, count); break;
+        case 1: BORUTA_SMALL(1) break;
+        case 2: BORUTA_SMALL(2) break;
+        default: BORUTA_SMALL(4) break;
     }
+#undef BORUTA_SMALL
 }
 
 void launch_lists(const ForestDev& F, int level, uint32_t grid_wg, hipStream_t st) {
@@ -2486,6 +2837,36 @@ void launch_col_sort(const ForestDev& F, int level, uint32_t grid_wg, hipStream_
                            (size_t)F.n_gcol * sizeof(uint32_t), st, F, level);
     hipLaunchKernelGGL(k_col_scan, dim3(1), dim3(256), 0, st, F, level);
     hipLaunchKernelGGL(k_col_scatter, dim3(grid_wg), dim3(256), 0, st, F, level);
+}
+
+// k_grow: dynamic LDS of a workgroup of `waves`, and its launch (after
+// prepare_grow allowed that LDS).
+size_t grow_lds(int kmax, uint32_t head, int waves, uint32_t cap) {
+    const int words = kmax <= 4 ? 1 : (kmax <= 8 ? 2 : 4);
+    return ((size_t)waves * small_lds_words(head, words) + 2 * (size_t)cap) * sizeof(uint32_t);
+}
+
+static const void* grow_fn(int kmax) {
+    switch (kmax) {
+        case 2: return reinterpret_cast<const void*>(&k_grow<2>);
+        case 3: return reinterpret_cast<const void*>(&k_grow<3>);
+        case 4: return reinterpret_cast<const void*>(&k_grow<4>);
+        case 8: return reinterpret_cast<const void*>(&k_grow<8>);
+        default: return reinterpret_cast<const void*>(&k_grow<16>);
+    }
+}
+
+hipError_t prepare_grow(int kmax, size_t lds) {
+    return hipFuncSetAttribute(grow_fn(kmax), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)lds);
+}
+
+void launch_grow(const ForestDev& F, uint32_t n_trees, int waves, uint32_t cap, hipStream_t st) {
+    ForestDev f = F;
+    void* args[] = {&f, &cap};
+    // a refused launch is reported by the caller's hipGetLastError
+    (void)hipLaunchKernel(grow_fn(F.kmax), dim3(n_trees), dim3(64 * waves), args,
+                          grow_lds(F.kmax, F.small_head, waves, cap), st);
 }
 
 // Allows the column path's dynamic LDS (above the default per-launch limit)
