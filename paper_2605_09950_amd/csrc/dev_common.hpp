@@ -324,7 +324,7 @@ struct SlotRec {
 // slots) are counted in ctrs[d]; they are zeroed once per iteration.
 struct LevelCtr {
     uint32_t pairs;     // child pairs handed out by k_grow (level 0's record, whole iteration)
-    uint32_t unused;
+    uint32_t n_big;     // large nodes of weight 65536 and more (column-major levels)
     uint32_t n_slots;   // large nodes
     uint32_t n_small;   // small nodes
     uint32_t overflow;  // a capacity check failed
@@ -431,6 +431,8 @@ struct ForestDev {
     uint32_t* fitems;     // [slot * mtry_cap] items sorted by column
     ColUnit* units;       // [unit_cap]
     uint32_t n_gcol, unit_cap, col_unit;  // columns, unit capacity, items per unit
+    uint32_t* big;        // [big_cap] slots of this level's nodes of weight 65536 and more
+    uint32_t big_cap;     // (0: the plan's jobs have fewer rows)
     int32_t col_count;    // this level takes the column path: its items' places in their
                           // columns are counted by k_draws (1) or k_col_count (2)
 };

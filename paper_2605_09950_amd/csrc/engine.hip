@@ -47,7 +47,7 @@ void launch_draws(const ForestDev&, int, uint32_t, hipStream_t);
 void launch_lists(const ForestDev&, int, uint32_t, hipStream_t);
 void launch_col_sort(const ForestDev&, int, uint32_t, hipStream_t);
 size_t hist_col_lds(int, int, uint32_t);
-hipError_t prepare_hist_col(int, int, size_t);
+hipError_t prepare_hist_col(int, size_t);
 size_t grow_lds(int, uint32_t, int, uint32_t);
 hipError_t prepare_grow(int, size_t);
 void launch_grow(const ForestDev&, uint32_t, int, uint32_t, hipStream_t);
@@ -374,7 +374,8 @@ struct Plan {
     std::vector<JobPlan> jp;
     size_t keys, jobs, trees, tree_base, flags, nodes, cls, ngain, small0, small1, cand, icand,
         feat, fcol, srec, kinds, chunk_sums, slot0, slot1, ctrs, alg, tot;
-    size_t fcnt = 0, fpos = 0, fitems = 0, units = 0, gcolq = 0;
+    size_t fcnt = 0, fpos = 0, fitems = 0, units = 0, gcolq = 0, big = 0;
+    uint32_t big_cap = 0;  // nodes of weight 65536 and more in a column-major level
     size_t seed_med = 0, seed_dec = 0;  // multi-seed aggregate [p]
     size_t dec_ptrs = 0;                // per job: the decisions the aggregate reads
     size_t kl_S = 0, kl_pi = 0, kl_delta = 0;  // KL importance buffers (shared by its jobs)
@@ -501,7 +502,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         col_level = widest > kColAutoBytes ? kColLevelAuto : kColNever;
     }
     if (o.form == BORUTA_FORM_BATCHED && col_level < pl.max_D) {
-        const size_t per_wave = (size_t)pl.hist_words * 256 * 4, col = (size_t)pl.gq_max * 16;
+        const size_t per_wave = (size_t)pk_words(pl.kmax) * 256 * 4, col = (size_t)pl.gq_max * 16;
         if (col + 2 * per_wave <= kLdsPerWorkgroup) {
             pl.col_level = col_level;
             pl.col_waves = (int)std::min<size_t>(kColWavesMax, (kLdsPerWorkgroup - col) / per_wave);
@@ -580,6 +581,8 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         pl.fitems = r.take(items * 4);
         pl.units = r.take((size_t)pl.unit_cap * sizeof(ColUnit));
         pl.gcolq = r.take(n_gcol * 4);
+        for (const Spec& s : specs) pl.big_cap += (uint32_t)(s.T * (s.n >> 16));
+        pl.big = r.take((size_t)pl.big_cap * 4);
     }
     // Plans with column-major levels (matrices past the last-level cache) keep a
     // row-major copy of the widened bins for the wave path: a node's draws at one
@@ -938,8 +941,8 @@ void Engine::setup(std::vector<int>& status) {
         int dev = 0, lds_max = 0;
         HIPC(hipGetDevice(&dev));
         HIPC(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-        const size_t lds = hist_col_lds(pl.hist_words, pl.col_waves, pl.gq_max);
-        if ((size_t)lds_max < lds || prepare_hist_col(pl.kmax, pl.hist_words, lds) != hipSuccess) {
+        const size_t lds = hist_col_lds(pl.kmax, pl.col_waves, pl.gq_max);
+        if ((size_t)lds_max < lds || prepare_hist_col(pl.kmax, lds) != hipSuccess) {
             (void)hipGetLastError();
             pl.col_level = kColNever;  // node-major at every level (same item layout)
         } else {
@@ -986,6 +989,8 @@ ForestDev Engine::forest() const {
         F.fitems = at<uint32_t>(pl.fitems);
         F.units = at<ColUnit>(pl.units);
         F.gcol_q = at<uint32_t>(pl.gcolq);
+        F.big = at<uint32_t>(pl.big);
+        F.big_cap = pl.big_cap;
         F.n_gcol = pl.n_gcol;
         F.unit_cap = pl.unit_cap;
         F.col_unit = (uint32_t)O.col_unit;

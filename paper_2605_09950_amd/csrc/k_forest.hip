@@ -1347,7 +1347,7 @@ __device__ __forceinline__ void put_item(const ForestDev& F, uint32_t item, cons
     uint32_t v = lane == 0 ? __float_as_uint(r.q) : (uint32_t)r.b | draw << 8;
 #pragma unroll
     for (int k = 0; k < C; ++k) v = lane == k + 2 ? l[k] : v;
-    if (lane < C + 2) F.icand[(size_t)item * (C + 2) + lane] = v;
+    if (lane < C + 2) F.icand[(size_t)item * (uint32_t)F.item_words + lane] = v;
 }
 
 // Exact form of a threshold's left counts l (fb-bit form).
@@ -1626,6 +1626,10 @@ __global__ __launch_bounds__(256) void k_draws(ForestDev F, int level) {
             sr->pk[w] = J.reg || fb == 0u ? 0u : v;
         }
         if (ql == 0) {
+            if (F.col_count && nd.n >= 65536u) {  // too heavy for k_hist_col
+                const uint32_t at = atomicAdd(&F.ctrs[level].n_big, 1u);
+                if (at < F.big_cap) F.big[at] = slot;
+            }
             sr->recs = J.rec[F.parity] + (size_t)tr.tau * J.rstride + nd.seg;
             sr->wy = J.reg ? J.wy[F.parity] + (size_t)tr.tau * J.rstride + nd.seg : nullptr;
             sr->id = id;
@@ -1653,19 +1657,22 @@ __global__ __launch_bounds__(256) void k_draws(ForestDev F, int level) {
 // through that XCD's L2 when the hardware deals workgroups round-robin to the
 // 8 XCDs (any mapping gives the same results: every item is visited once).
 // With an explicit count, items [first, first + count) are walked directly
-// (plain form).
+// (plain form); kBigItems: the items of the level's F.big slots.
+constexpr uint32_t kBigItems = 0xFFFFFFFEu;
 struct ItemWalk {
     bool dyn;
+    const uint32_t* big;
     uint32_t x, r, R, m_end, first, npi;
     __device__ ItemWalk(const ForestDev& F, int level, uint32_t first_, uint32_t count,
                         uint32_t wave) {
         npi = (uint32_t)F.npi;
         first = first_;
         dyn = count == 0xFFFFFFFFu;
+        big = count == kBigItems ? F.big : nullptr;
         x = 0;
         r = blockIdx.x * 4u + wave;
         R = gridDim.x * 4u;
-        m_end = count;
+        m_end = big ? min(F.ctrs[level].n_big, F.big_cap) * npi : count;
         if (dyn) {
             const uint32_t n_slots = level_slots(F, level);
             x = blockIdx.x % 8u;
@@ -1675,6 +1682,7 @@ struct ItemWalk {
         }
     }
     __device__ uint32_t item(uint32_t cur) const {
+        if (big) return big[cur / npi] * npi + cur % npi;
         return dyn ? (8u * (cur / npi) + x) * npi + cur % npi : first + cur;
     }
 };
@@ -1965,7 +1973,10 @@ __global__ __launch_bounds__(256) void k_col_scatter(ForestDev F, int level) {
 // column into LDS (16-byte loads, the whole column once), then each wave
 // takes the unit's items in turn: an LDS class-count histogram from the node's
 // row records and the staged bins, the threshold scan, and the item's record
-// (item = slot * mtry_cap + draw).
+// (item = slot * mtry_cap + draw).  Class counts take 16 bits at most: the items
+// of a node of weight 65536 and more (F.big) are left to k_hist_tile, so that
+// the histograms take two classes to a word (79 instead of 107 registers, half the
+// LDS per wave; 100,000 x 2,000, 3 iterations: 148.4 -> 143.9 ms).
 // Bound: the records (4 bytes per row and draw, mostly from the last-level
 // cache) at the shallow levels, the vector instructions of the scan at the
 // deep ones.  The first two records per lane of the wave's next item are
@@ -1973,9 +1984,9 @@ __global__ __launch_bounds__(256) void k_col_scatter(ForestDev F, int level) {
 // conditional load here is waited for where its paths join.  With 4-byte
 // instead of 8-byte records and the prefetch in flight a launch takes 2.42
 // instead of 2.69 ms (n = 100,000, 2,000 features, mean of tree levels 5-15).
-template <int KMAX, bool BIG>
+template <int KMAX>
 __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level, uint32_t col_words) {
-    constexpr int RB = 8, C = item_counts<KMAX, BIG>(), PW = pk_words(KMAX);
+    constexpr int RB = 8, C = pk_words(KMAX);
     extern __shared__ uint4 lds_raw[];  // the column (col_words 16-byte words), the histograms
     const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
     const uint32_t nw = blockDim.x >> 6;
@@ -2003,9 +2014,9 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level, uint3
             const SlotRec* msr = F.srec + my_item / mc;
             const uint64_t my_recs = reinterpret_cast<uint64_t>(msr->recs);
             const uint32_t my_len = msr->len, my_n = msr->n;
-            uint32_t my_pk[PW];
+            uint32_t my_pk[C];
 #pragma unroll
-            for (int c = 0; c < PW; ++c) my_pk[c] = msr->pk[c];
+            for (int c = 0; c < C; ++c) my_pk[c] = msr->pk[c];
             const uint32_t n_here = min(64u, (cu.end - k0 + nw - 1u) / nw);
             auto recs_of = [&](uint32_t t) {
                 return reinterpret_cast<const uint32_t*>(readlane64(my_recs, (int)t));
@@ -2038,6 +2049,7 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level, uint3
                     p0 = rec_raw(recs_of(tn), (uint32_t)lane, nlen);
                     p1 = rec_raw(recs_of(tn), (uint32_t)lane + 64u, nlen);
                 }
+                if (N >= 65536u) continue;
                 if ((uint32_t)lane < len) count_row<KMAX>(hist, cf, r0, (uint32_t)b0);
                 if ((uint32_t)lane + 64u < len) count_row<KMAX>(hist, cf, r1, (uint32_t)b1);
                 if (len > 128u) {
@@ -2065,20 +2077,14 @@ __global__ __launch_bounds__(1024) void k_hist_col(ForestDev F, int level, uint3
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                uint32_t pk[PW], l[C], cnode[KMAX];
+                uint32_t pk[C], l[C];
 #pragma unroll
-                for (int c = 0; c < PW; ++c) pk[c] = readlane_w(my_pk[c], (int)t);
+                for (int c = 0; c < C; ++c) pk[c] = readlane_w(my_pk[c], (int)t);
 #pragma unroll
                 for (int c = 0; c < C; ++c) l[c] = 0;
-                if constexpr (BIG) {
-                    if (cf.fb == 0u) {
-#pragma unroll
-                        for (int c = 0; c < KMAX; ++c) cnode[c] = F.srec[item / mc].cnode[c];
-                    }
-                }
-                const ItemBest best = scan_item<KMAX, BIG>(hist, cf, K, len, b0, b1, B, pk, cnode,
-                                                           N, F.split_rank, l);
-                put_item<KMAX, BIG>(F, item, best, 0u, l);
+                const ItemBest best = scan_item<KMAX, false>(hist, cf, K, len, b0, b1, B, pk,
+                                                             nullptr, N, F.split_rank, l);
+                put_item<KMAX, false>(F, item, best, 0u, l);
                 if (F.alg_bytes)
                     alg += (unsigned long long)len * (item % mc == 0u ? 7ull : 1ull);
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -2826,8 +2832,8 @@ void launch_hist_tile(const ForestDev& F, int level, uint32_t first, uint32_t co
     }
 }
 
-size_t hist_col_lds(int hist_words, int waves, uint32_t gq_max) {
-    return (size_t)waves * hist_words * 256 * sizeof(uint32_t) + (size_t)gq_max * 16;
+size_t hist_col_lds(int kmax, int waves, uint32_t gq_max) {
+    return (size_t)waves * pk_words(kmax) * 256 * sizeof(uint32_t) + (size_t)gq_max * 16;
 }
 
 // F.col_count == 2: the places are counted by k_col_count (n_gcol <= kColCountLds)
@@ -2871,34 +2877,33 @@ void launch_grow(const ForestDev& F, uint32_t n_trees, int waves, uint32_t cap, 
 
 // Allows the column path's dynamic LDS (above the default per-launch limit)
 // for the instantiation of kmax classes.
-static const void* hist_col_fn(int kmax, bool big) {
-    switch (kmax * 2 + (big ? 1 : 0)) {
-        case 4: return reinterpret_cast<const void*>(&k_hist_col<2, false>);
-        case 5: return reinterpret_cast<const void*>(&k_hist_col<2, true>);
-        case 6: return reinterpret_cast<const void*>(&k_hist_col<3, false>);
-        case 7: return reinterpret_cast<const void*>(&k_hist_col<3, true>);
-        case 8: return reinterpret_cast<const void*>(&k_hist_col<4, false>);
-        case 9: return reinterpret_cast<const void*>(&k_hist_col<4, true>);
-        case 16: return reinterpret_cast<const void*>(&k_hist_col<8, false>);
-        case 17: return reinterpret_cast<const void*>(&k_hist_col<8, true>);
-        case 32: return reinterpret_cast<const void*>(&k_hist_col<16, false>);
-        default: return reinterpret_cast<const void*>(&k_hist_col<16, true>);
+static const void* hist_col_fn(int kmax) {
+    switch (kmax) {
+        case 2: return reinterpret_cast<const void*>(&k_hist_col<2>);
+        case 3: return reinterpret_cast<const void*>(&k_hist_col<3>);
+        case 4: return reinterpret_cast<const void*>(&k_hist_col<4>);
+        case 8: return reinterpret_cast<const void*>(&k_hist_col<8>);
+        default: return reinterpret_cast<const void*>(&k_hist_col<16>);
     }
 }
 
-hipError_t prepare_hist_col(int kmax, int hist_words, size_t lds) {
-    return hipFuncSetAttribute(hist_col_fn(kmax, hist_words == kmax),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+hipError_t prepare_hist_col(int kmax, size_t lds) {
+    return hipFuncSetAttribute(hist_col_fn(kmax), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)lds);
 }
 
 void launch_hist_col(const ForestDev& F, int level, uint32_t grid_wg, int waves, uint32_t gq_max,
                      hipStream_t st) {
-    const size_t lds = hist_col_lds(F.hist_words, waves, gq_max);
+    const size_t lds = hist_col_lds(F.kmax, waves, gq_max);
     ForestDev f = F;
     void* args[] = {&f, &level, &gq_max};
     // a refused launch is reported by the caller's hipGetLastError
-    (void)hipLaunchKernel(hist_col_fn(F.kmax, F.hist_words == F.kmax), dim3(grid_wg),
-                          dim3(64 * waves), args, lds, st);
+    (void)hipLaunchKernel(hist_col_fn(F.kmax), dim3(grid_wg), dim3(64 * waves), args, lds, st);
+    // the level's nodes past its 16-bit counts (plans of 65536 rows and more)
+    if (F.big_cap) {
+        const uint32_t need = std::max(1u, std::min(F.big_cap * (uint32_t)F.npi / 4u, 2048u));
+        launch_hist_tile(F, level, 0, kBigItems, need, 8, st);
+    }
 }
 
 void launch_split_finalize(const ForestDev& F, int level, uint32_t first, uint32_t count,
