@@ -128,8 +128,8 @@ typedef struct {
      * 0 = the library's default).                                                 */
     int32_t small_rows;   /* nodes with at most this many distinct rows (and a
                              weighted count below the packed-counter limit) take
-                             the wavefront path, [2, 64]; default 32, which plans
-                             without column-major levels take as 64             */
+                             the wavefront path, [2, 64]; default 32, which is
+                             taken as 64                                        */
     /* "needed" below: for the nodes tree level d can hold, at most the
      * plan's capacity and n_trees * 2^d; a chosen grid size is an upper
      * limit, lowered to what a level needs.                                */
@@ -144,7 +144,7 @@ typedef struct {
                              column-major histogram path (items bucketed by bin
                              column, each column staged once per unit in LDS);
                              [1, 64], 64 = never; 0 (default) = automatic: level
-                             5 when some job's widened bin matrix (2p columns of
+                             3 when some job's widened bin matrix (2p columns of
                              n rounded up to 256 bytes) exceeds 128 MiB, else
                              never.  The path needs a whole bin column plus two
                              histograms in one workgroup's LDS; where it does

@@ -80,7 +80,10 @@ constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 // (such a matrix no longer stays in the 256 MB last-level cache beside the
 // row records, so node-major gathers pull whole lines from HBM), and the
 // value that disables it.
-constexpr int kColLevelAuto = 5;
+// The level: 100,000 x 2,000, 4 classes, 3 iterations, take 140.9 ms from level 3,
+// 141.2 from 4, 143.9 from 5, 141.5 from 2 and 143.1 from 1 (above it a node's rows
+// are most of a column, which its histogram reads whole anyway).
+constexpr int kColLevelAuto = 3;
 constexpr size_t kColAutoBytes = size_t(128) << 20;
 constexpr int kColNever = 64;
 // KL importance: bound of its per-block difference buffer.
@@ -524,12 +527,11 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         pl.fw = fw;
     }
     pl.npi = (pl.mtry_cap + pl.fw - 1) / pl.fw;
-    // The wave path's row limit at its default: 32 beside column-major levels
-    // (whose LDS-staged bins are cheaper than the wave path's gathers: 157 ms
-    // at 32, 176 at 64, the 100,000 x 2,000 workload's first iterations), else
-    // 64 (the 64-job batch 158 ms at 32, 137 at 64; 10,000 x 500 82.2 and 79.6;
-    // 7 classes exact 11.5 and 10.7; regression 75.3 and 72.5).
-    pl.small_rows = o.small_rows == 32 && pl.col_level >= pl.max_D ? 64 : o.small_rows;
+    // The wave path's row limit at its default: 64, one row per lane (the 64-job
+    // batch 158 ms at 32, 137 at 64; 10,000 x 500 82.2 and 79.6; 7 classes exact
+    // 11.5 and 10.7; regression 75.3 and 72.5; 100,000 x 2,000, whose bins the wave
+    // path reads by row, 144.0 and 140.1).
+    pl.small_rows = o.small_rows == 32 ? 64 : o.small_rows;
     if (node_cap >= 0xFFFFFFF0ull || slot_cap * (uint64_t)pl.mtry_cap + n_gcol >= 0xFFFFFFF0ull ||
         small_cap >= 0xFFFFFFF0ull)
         throw Error(BORUTA_E_INVALID_ARG, "problem too large: more than 2^32 tree nodes");
