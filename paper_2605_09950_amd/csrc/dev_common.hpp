@@ -437,4 +437,11 @@ struct ForestDev {
                           // columns are counted by k_draws (1) or k_col_count (2)
 };
 
+// Launch shape of the Permut kernel (permut_shape).
+struct PermutShape {
+    int threads, chunks, slices, lds_cols, lds_words;
+    bool wide;  // columns past 65,536
+    size_t lds;
+};
+
 }  // namespace boruta

@@ -55,8 +55,9 @@ void launch_hist_col(const ForestDev&, int, uint32_t, int, uint32_t, hipStream_t
 // k_importance.hip
 void launch_tree_totals(JobDev*, const TreeDev*, int, uint64_t*, hipStream_t);
 void launch_treeimp(JobDev*, const TreeDev*, int, const uint64_t*, int, hipStream_t);
-void launch_permut(JobDev*, const TreeDev*, const NodeDev*, const uint32_t*, int, int, int64_t,
-                   int, int, bool, unsigned long long*, hipStream_t);
+PermutShape permut_shape(int, int64_t, int, int, bool);
+void launch_permut(JobDev*, const TreeDev*, const NodeDev*, const uint32_t*, int, int, int,
+                   const PermutShape&, unsigned long long*, hipStream_t);
 void launch_hits_decide(JobDev*, int, int, hipStream_t);
 void launch_rough_fix(const int8_t*, const double*, const double*, int64_t, int, int, int8_t*,
                       hipStream_t);
@@ -396,6 +397,7 @@ struct Plan {
     int64_t max_n = 0;
     int grow_waves = 0;       // waves per tree of the one-launch growth (0: level kernels)
     uint32_t grow_cap = 0;    // searched nodes of a tree level it holds
+    PermutShape permut;       // launch shape of the Permut kernel
     uint32_t boot_chunk = 0;  // rows per workgroup of the LDS bootstrap counts (0: atomics)
     size_t total = 0;
 };
@@ -602,6 +604,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     const uint32_t tab = kDrawTab / 2, bins = pl.rowmaj ? 64 * 68 / 4 : 0;
     pl.bins_off = pl.mtry_cap <= 64 ? 0 : tab;
     pl.small_head = std::max(tab, pl.bins_off + bins);
+    pl.permut = permut_shape(pl.T_total, pl.max_n, pl.max_D, pl.max_pw, any_reg);
     // Whole trees in one launch (k_grow), one workgroup per tree: a tree's time
     // does not depend on the others as long as every tree has a compute unit, and
     // a level's kernels cost about 35 us however little they hold, so it pays for
@@ -1164,10 +1167,7 @@ void Engine::enqueue_iteration() {
     }
     if (any_permut) {
         const size_t h = clock.begin(stats ? &stats->permut : nullptr, st);
-        bool any_reg = false;
-        for (const Spec& sp : S) any_reg |= sp.yr != nullptr;
-        launch_permut(djobs, dtrees, F.nodes, F.cls, pl.kmax, (int)n_trees, pl.max_n, pl.max_D,
-                      pl.max_pw, any_reg,
+        launch_permut(djobs, dtrees, F.nodes, F.cls, pl.kmax, (int)n_trees, pl.max_D, pl.permut,
                       stats ? (unsigned long long*)at<uint64_t>(pl.alg) + 3 * kAlgWords : nullptr,
                       st);
         clock.end(h, st);

@@ -156,84 +156,142 @@ __device__ __forceinline__ uint32_t turned_at(const PathLds& P, const Walked& w,
 
 // (path column, replica) pairs whose OOB sources are walked together
 constexpr int kPermGroup = 8;
+// walks a lane advances at a time
+constexpr int kPermWalks = 4;
 
-// Permut: one thread per (tree, OOB row).  The row's (path column, replica)
-// pairs are taken kPermGroup at a time: their source rows pi(j) by cycle walks
-// interleaved in one loop, then all their source bins, then -- for the pairs
-// that turn at a node -- the walks from there, again interleaved in one loop
-// (a lane starts its next pair's walk as soon as one ends, so the wave waits
-// for the lane with the longest total, not for the longest walk of every
-// pair).  When the job's widened width is at most lds_cols, the drops are
-// summed per column in LDS and each workgroup adds its nonzero sums to the
-// importances: once most columns are decided, few remain and per-row atomics
-// would all meet on them.  For a regression job a row's score is the negated
-// squared error against its leaf's prediction, sq_error_fix above, and the
-// per-column sums in LDS are 64-bit.
-// Bound: the scattered bin loads (a 128-byte line each where the matrix exceeds
-// the last-level cache).  Re-routing every pair from its column's node down
-// took 117 ms an iteration at n = 100,000, 2,000 features, 300 trees of depth
-// 16, five replicas: 6.0e9 lines, 6.5 TB/s.
-__global__ __launch_bounds__(256) void k_permut(JobDev* jobs, const TreeDev* trees,
+// A k_permut workgroup's paths by position (stride: the workgroup's threads);
+// directions are kept in a register.
+template <class Col>
+struct PermPath {
+    uint32_t* ps;  // the child not taken
+    Col* pf;       // column
+    uint8_t* pt;   // threshold bin
+    uint32_t stride;
+};
+template <class Col>
+__host__ __device__ constexpr uint32_t perm_path_bytes(int max_depth, uint32_t threads) {
+    return (uint32_t)max_depth * threads * (4u + (uint32_t)sizeof(Col) + 1u);
+}
+
+// Permut: one thread per (tree, OOB row).  The row's path is walked once and
+// kept in LDS: a permuted column changes the prediction only where its new bin
+// turns the other way at one of its positions, and then from the child not
+// taken on.  The row's (path column, replica) pairs are taken kPermGroup at a
+// time: their source rows pi(j) by cycle walks interleaved in one loop, then
+// all their source bins, then -- for the pairs that turn at a node -- the walks
+// from there, kPermWalks at a time, a lane starting its next pair's walk as
+// soon as one ends.  When the job's widened width is at most lds_cols, the
+// drops are summed per column in LDS and each workgroup adds its nonzero sums
+// to the importances: once most columns are decided, few remain and per-row
+// atomics would all meet on them.  For a regression job a row's score is the
+// negated squared error against its leaf's prediction, sq_error_fix above, and
+// the per-column sums in LDS are 64-bit.
+// Bound: the chains of dependent loads (node, column address, bin) of the walks
+// beside the permutations' multiplies, and for a matrix past the last-level
+// cache the 128-byte lines of its scattered bins.  So: one tree per XCD at a
+// time (consecutive workgroups go to the 8 XCDs in turn), whose nodes and bins
+// then stay in that XCD's L2 (100,000 x 2,000, 300 trees of depth 16, five
+// replicas: 2.6e9 -> 1.7e9 lines); four walks per lane; 128 rows per workgroup
+// and 7 bytes per path position, for 20 waves per compute unit; the positions
+// of a row dealt to up to 8 workgroups where the rows alone leave the chip idle
+// (each walks the path again).  An iteration's time with one walk per lane, any
+// XCD, 256 rows and 9 bytes, and now: 100,000 x 2,000 80.0 -> 54.4 ms; 10,000 x
+// 500, 200 trees 455 -> 305 us; 64 jobs up to 5,000 x 2,000 6.2 -> 3.4 ms; 3,000
+// x 120, 60 trees 199 -> 133 us.  Rounds of the permutations tabulated in LDS
+// for the rows of one node (sorted by path) saved 35% of the multiplies and
+// lost the time again in barriers and occupancy.
+template <class Col>
+__global__ __launch_bounds__(128) void k_permut(JobDev* jobs, const TreeDev* trees, int n_trees,
                                                 const NodeDev* nodes, const uint32_t* cls,
-                                                int kmax, int max_depth, int lds_cols,
-                                                int lds_words, unsigned long long* visits) {
-    // the paths; [lds_words]: the column drops (lds_cols of them);
-    // [kPermGroup][256]: a group's source rows, then its walks' first nodes
-    extern __shared__ uint32_t s_path[];
-    const uint32_t g = blockIdx.y;
+                                                int kmax, int max_depth, int chunks,
+                                                int slices, int lds_cols, int lds_words,
+                                                unsigned long long* visits) {
+    // [kPermGroup][threads]: a group's source rows, then its walks' first nodes;
+    // the column drops (lds_words); the paths
+    extern __shared__ uint32_t s_perm[];
+    const uint32_t S = blockDim.x;
+    const uint32_t idx = blockIdx.x / 8u / (uint32_t)slices;
+    const uint32_t slice = blockIdx.x / 8u % (uint32_t)slices;
+    const uint32_t g = idx / (uint32_t)chunks * 8u + blockIdx.x % 8u;
+    if (g >= (uint32_t)n_trees) return;
+    const uint32_t chunk = idx % (uint32_t)chunks;
     const TreeDev tr = trees[g];
     JobDev& J = jobs[tr.job];
     if (!J.live || J.mode != 1) return;  // finished job, or TreeImp job of a mixed batch
-    const int tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x;
     const uint32_t m = (uint32_t)J.tstat[tr.tau * 4 + 1];
-    const uint32_t j = blockIdx.x * 256u + tid;
-    if (blockIdx.x * 256u >= m) return;
-    const PathLds P = path_lds(s_path, max_depth);
-    int* s_drop = reinterpret_cast<int*>(s_path + path_lds_words(max_depth));
+    if (chunk * S >= m) return;
+    uint32_t* g_src = s_perm;
+    int* s_drop = reinterpret_cast<int*>(g_src + kPermGroup * S);
     long long* s_drop64 = reinterpret_cast<long long*>(s_drop);  // regression jobs
-    uint32_t* g_src = s_path + path_lds_words(max_depth) + lds_words;  // [kPermGroup][256]
+    PermPath<Col> P;
+    P.stride = S;
+    P.ps = reinterpret_cast<uint32_t*>(s_drop) + lds_words;
+    P.pf = reinterpret_cast<Col*>(P.ps + (uint32_t)max_depth * S);
+    P.pt = reinterpret_cast<uint8_t*>(P.pf + (uint32_t)max_depth * S);
     const bool reg = J.reg != 0;
     const bool lds = J.p_w <= lds_cols;  // uniform: one tree per workgroup
     if (lds) {
-        for (int c = tid; c < J.p_w; c += 256) {
+        for (uint32_t c = tid; c < (uint32_t)J.p_w; c += S) {
             if (reg)
                 s_drop64[c] = 0;
             else
                 s_drop[c] = 0;
         }
-        __syncthreads();
     }
+    const uint32_t j = chunk * S + tid;
     const bool active = j < m;
     const uint32_t* oob = J.oob + (size_t)tr.tau * J.n;
     const uint32_t row = active ? oob[j] : 0u;
     const uint32_t yv = reg ? 0u : (uint32_t)J.y[row];
     const long long yfv = reg ? (long long)J.yfix[row] : 0ll;
-    Walked w{g, 0u, 0, 0u};
+    // the path: its length, its directions from the top bit (1: right), and the
+    // positions whose column is on it before (depth <= 30)
+    int len = 0;
+    uint32_t dir = 0u, dup = 0u;
     bool base_ok = false;
     long long base_err = 0;
     unsigned long long nv = 0;  // node visits (statistics)
     if (active) {
-        w = walk_path(J, nodes, g, row, P, tid);
-        nv += (unsigned long long)w.len + 1u;
+        uint32_t leaf = g;
+        Hop h = load_hop(nodes, g);
+        while (h.feat >= 0) {
+            const uint32_t right = (uint32_t)ldg(ldg(J.colptr + h.feat) + row) > h.thr ? 1u : 0u;
+            bool again = false;
+            for (int q = 0; q < len; ++q) again |= P.pf[q * S + tid] == (Col)h.feat;
+            dup |= (uint32_t)again << len;
+            dir |= right << (31 - len);
+            P.pf[len * S + tid] = (Col)h.feat;
+            P.ps[len * S + tid] = h.left + (right ^ 1u);
+            P.pt[len * S + tid] = (uint8_t)h.thr;
+            ++len;
+            leaf = h.left + right;
+            h = load_hop(nodes, leaf);
+        }
+        if (slice == 0u) nv += (unsigned long long)len + 1u;
         if (reg)
-            base_err = sq_error_fix(nodes, cls, kmax, w.leaf, yfv, J.s_perm);
+            base_err = sq_error_fix(nodes, cls, kmax, leaf, yfv, J.s_perm);
         else
-            base_ok = w.leaf_class == yv;
+            base_ok = h.leaf == yv;
     }
-    const unsigned long long okm = __ballot(active && base_ok);
+    const unsigned long long okm = __ballot(active && base_ok && slice == 0u);
     if ((tid & 63) == 0 && okm) atomicAdd(&J.tstat[tr.tau * 4 + 2], (int)__popcll(okm));
-    const int R = J.R;
-    // next pair after (pi, r), in order of positions (a column already on the
-    // path skipped) and replicas
-    auto next_pair = [&](int& pi, int& r) {
-        if (++r < R) return;
-        r = 0;
-        ++pi;
-        while (pi < w.len && (w.dup >> pi & 1u)) ++pi;
-    };
-    auto pair_perm = [&](int pi, int r) {
-        return make_perm(J.seed_lo, J.seed_hi, kOobPerm, (uint32_t)J.t, (uint32_t)tr.tau,
-                         P.pf[pi * 256 + tid] & 0x7FFFFFFFu, (uint32_t)r << 16, (uint64_t)m);
+    if (lds) __syncthreads();
+    const uint32_t R = (uint32_t)J.R;
+    KeyedPerm K = make_perm(J.seed_lo, J.seed_hi, kOobPerm, (uint32_t)J.t, (uint32_t)tr.tau, 0u,
+                            0u, (uint64_t)m);
+    // whether the column of position a with bin sb sends the row another way:
+    // the child from which its walk differs, else 0xFFFFFFFF (roots are never a child)
+    auto turned_to = [&](int a, uint32_t sb) -> uint32_t {
+        const uint32_t f = P.pf[a * S + tid];
+        if ((uint32_t)(sb > P.pt[a * S + tid]) != (dir >> (31 - a) & 1u)) return P.ps[a * S + tid];
+        for (uint32_t q = a < 31 ? dup >> (a + 1) << (a + 1) : 0u; q; q &= q - 1u) {
+            const int b = __builtin_ctz(q);
+            if (P.pf[b * S + tid] == (Col)f &&
+                (uint32_t)(sb > P.pt[b * S + tid]) != (dir >> (31 - b) & 1u))
+                return P.ps[b * S + tid];
+        }
+        return 0xFFFFFFFFu;
     };
     auto add_drop = [&](uint32_t f, int drop, long long drop_sq) {
         if (reg) {
@@ -250,36 +308,18 @@ __global__ __launch_bounds__(256) void k_permut(JobDev* jobs, const TreeDev* tre
                 atomicAdd((unsigned long long*)&J.imp[f], (unsigned long long)(int64_t)drop);
         }
     };
-    int cpi = 0, cr = 0;  // the next pair to score (position 0 is never a duplicate)
-    while (active && cpi < w.len) {
-        // source rows of the group's pairs; their positions in bytes of pos
-        uint64_t pos = 0;
-        int k = 0;
-        {
-            KeyedPerm K = pair_perm(cpi, cr);
-            uint32_t x = j;
-            while (k < kPermGroup && cpi < w.len) {
-                if (m > 1u) x = perm_pass(K, x);
-                if (m <= 1u || x < m) {
-                    g_src[k * 256 + tid] = m <= 1u ? 0u : x;
-                    pos |= (uint64_t)cpi << (8 * k);
-                    ++k;
-                    next_pair(cpi, cr);
-                    x = j;
-                    if (cpi < w.len) K = pair_perm(cpi, cr);
-                }
-            }
-        }
+    // scores a group: k pairs, their source positions in g_src, the path
+    // positions of their columns in bytes of pos
+    auto score = [&](int k, uint64_t pos) {
         // source bins: the rows' loads, then the bins' loads, all in flight
         uint32_t srow[kPermGroup];
         uint64_t sbs = 0;
 #pragma unroll
-        for (int e = 0; e < kPermGroup; ++e)
-            srow[e] = ldg(oob + (e < k ? g_src[e * 256 + tid] : 0u));
+        for (int e = 0; e < kPermGroup; ++e) srow[e] = ldg(oob + (e < k ? g_src[e * S + tid] : 0u));
         uint32_t sb[kPermGroup];
 #pragma unroll
         for (int e = 0; e < kPermGroup; ++e) {
-            const uint32_t f = P.pf[(int)(pos >> (8 * e) & 0xFFu) * 256 + tid] & 0x7FFFFFFFu;
+            const uint32_t f = P.pf[(uint32_t)(pos >> (8 * e) & 0xFFu) * S + tid];
             sb[e] = ldg(ldg(J.colptr + f) + srow[e]);
         }
         // the pairs that turn, and where their walks go on
@@ -288,52 +328,92 @@ __global__ __launch_bounds__(256) void k_permut(JobDev* jobs, const TreeDev* tre
         for (int e = 0; e < kPermGroup; ++e) {
             sbs |= (uint64_t)sb[e] << (8 * e);
             if (e < k) {
-                const uint32_t at = turned_at(P, w, (int)(pos >> (8 * e) & 0xFFu), sb[e], tid);
-                g_src[e * 256 + tid] = at;
+                const uint32_t at = turned_to((int)(pos >> (8 * e) & 0xFFu), sb[e]);
+                g_src[e * S + tid] = at;
                 turn |= (uint32_t)(at != 0xFFFFFFFFu) << e;
             }
         }
-        // their walks; a column's drops are added when the column changes
-        uint32_t f = 0xFFFFFFFFu, node = 0, sbin = 0;
-        int drop = 0;
-        long long drop_sq = 0;  // regression: increase of the squared error
-        auto begin = [&]() {
-            const int e = __builtin_ctz(turn);
+        // their walks, two at a time
+        uint32_t f[kPermWalks], node[kPermWalks], sbin[kPermWalks];
+        bool on[kPermWalks];
+        auto begin = [&](int v) {
+            on[v] = turn != 0u;
+            const int e = on[v] ? __builtin_ctz(turn) : 0;
             turn &= turn - 1u;
-            const uint32_t nf = P.pf[(int)(pos >> (8 * e) & 0xFFu) * 256 + tid] & 0x7FFFFFFFu;
-            if (nf != f) {
-                if (f != 0xFFFFFFFFu) add_drop(f, drop, drop_sq);
-                drop = 0;
-                drop_sq = 0;
-                f = nf;
-            }
-            node = g_src[e * 256 + tid];
-            sbin = (uint32_t)(sbs >> (8 * e)) & 0xFFu;
+            f[v] = P.pf[(uint32_t)(pos >> (8 * e) & 0xFFu) * S + tid];
+            node[v] = on[v] ? g_src[e * S + tid] : g;
+            sbin[v] = (uint32_t)(sbs >> (8 * e)) & 0xFFu;
         };
-        bool walking = turn != 0;
-        if (walking) begin();
-        while (walking) {
-            const Hop h = load_hop(nodes, node);
-            ++nv;
-            if (h.feat >= 0) {
-                const uint32_t b = (uint32_t)h.feat == f
-                                       ? sbin
-                                       : (uint32_t)ldg(ldg(J.colptr + h.feat) + row);
-                node = b <= h.thr ? h.left : h.left + 1u;
-            } else {
-                if (reg)
-                    drop_sq += sq_error_fix(nodes, cls, kmax, node, yfv, J.s_perm) - base_err;
-                else
-                    drop += (int)base_ok - (int)(h.leaf == yv);
-                walking = turn != 0;
-                if (walking) begin();
+        bool any = false;
+#pragma unroll
+        for (int v = 0; v < kPermWalks; ++v) {
+            begin(v);
+            any |= on[v];
+        }
+        while (any) {
+            any = false;
+            Hop h[kPermWalks];
+            uint32_t b[kPermWalks];
+#pragma unroll
+            for (int v = 0; v < kPermWalks; ++v) h[v] = load_hop(nodes, node[v]);
+#pragma unroll
+            for (int v = 0; v < kPermWalks; ++v)
+                b[v] = ldg(ldg(J.colptr + (h[v].feat >= 0 ? h[v].feat : 0)) + row);
+#pragma unroll
+            for (int v = 0; v < kPermWalks; ++v) {
+                nv += on[v];
+                if (h[v].feat >= 0) {
+                    if ((uint32_t)h[v].feat == f[v]) b[v] = sbin[v];
+                    if (on[v]) node[v] = b[v] <= h[v].thr ? h[v].left : h[v].left + 1u;
+                } else if (on[v]) {
+                    if (reg)
+                        add_drop(f[v], 0,
+                                 sq_error_fix(nodes, cls, kmax, node[v], yfv, J.s_perm) -
+                                     base_err);
+                    else
+                        add_drop(f[v], (int)base_ok - (int)(h[v].leaf == yv), 0);
+                    begin(v);
+                }
+                any |= on[v];
             }
         }
-        if (f != 0xFFFFFFFFu) add_drop(f, drop, drop_sq);
+    };
+    uint32_t done = dup;  // positions that need no more pairs here
+    if (slices > 1)
+        for (uint32_t l = 0; l < (uint32_t)len; ++l)
+            if (l % (uint32_t)slices != slice) done |= 1u << l;
+    uint32_t left = active ? ~done & ((1u << len) - 1u) : 0u;
+    uint32_t cr = 0;
+    while (left) {
+        uint64_t pos = 0;
+        int k = 0;
+        uint32_t x = j;
+        int a = __builtin_ctz(left);
+        K.b = P.pf[a * S + tid];
+        K.c_hi = cr << 16;
+        while (k < kPermGroup && left) {
+            if (m > 1u) x = perm_pass(K, x);
+            if (m <= 1u || x < m) {
+                g_src[k * S + tid] = m <= 1u ? 0u : x;
+                pos |= (uint64_t)a << (8 * k);
+                ++k;
+                if (++cr == R) {
+                    cr = 0;
+                    left &= left - 1u;
+                }
+                x = j;
+                if (left) {
+                    a = __builtin_ctz(left);
+                    K.b = P.pf[a * S + tid];
+                    K.c_hi = cr << 16;
+                }
+            }
+        }
+        score(k, pos);
     }
     if (lds) {
         __syncthreads();
-        for (int c = tid; c < J.p_w; c += 256) {
+        for (uint32_t c = tid; c < (uint32_t)J.p_w; c += S) {
             const long long v = reg ? s_drop64[c] : (long long)s_drop[c];
             if (v) atomicAdd((unsigned long long*)&J.imp[c], (unsigned long long)v);
         }
@@ -341,7 +421,7 @@ __global__ __launch_bounds__(256) void k_permut(JobDev* jobs, const TreeDev* tre
     if (visits) {
         for (int q = 1; q < 64; q <<= 1) nv += __shfl_xor(nv, q);
         if ((tid & 63) == 0 && nv)
-            atomicAdd(visits + ((blockIdx.x * 4u + (uint32_t)(tid >> 6)) & (kAlgWords - 1)), nv);
+            atomicAdd(visits + ((blockIdx.x * 8u + (tid >> 6)) & (kAlgWords - 1)), nv);
     }
 }
 
@@ -886,18 +966,40 @@ void launch_treeimp(JobDev* jobs, const TreeDev* trees, int n_trees, const uint6
                        dim3(256), 0, st, jobs, trees, tot);
 }
 
-void launch_permut(JobDev* jobs, const TreeDev* trees, const NodeDev* nodes, const uint32_t* cls,
-                   int kmax, int n_trees, int64_t max_n, int max_depth, int max_pw,
-                   bool any_reg, unsigned long long* visits, hipStream_t st) {
+PermutShape permut_shape(int n_trees, int64_t max_n, int max_depth, int max_pw, bool any_reg) {
+    PermutShape s;
+    // 128 rows per workgroup: 256 take 4.6 instead of 3.5 ms in the 64-job batch
+    // (workgroups that few OOB rows leave half empty), 64 take 374 instead of
+    // 314 us at 10,000 x 500
+    s.threads = 128;
     // per-column drop sums in LDS for jobs of at most 1024 widened columns
     // (64-bit when the batch has a regression job)
-    const int lds_cols = max_pw < 1024 ? max_pw : 1024;
-    const int lds_words = lds_cols * (any_reg ? 2 : 1);
-    const size_t lds = ((size_t)path_lds_words(max_depth) + lds_words + (size_t)kPermGroup * 256) *
-                       sizeof(uint32_t);
-    hipLaunchKernelGGL(k_permut, dim3((unsigned)((max_n + 255) / 256), (unsigned)n_trees),
-                       dim3(256), lds, st, jobs, trees, nodes, cls, kmax, max_depth, lds_cols,
-                       lds_words, visits);
+    s.lds_cols = max_pw < 1024 ? max_pw : 1024;
+    s.lds_words = s.lds_cols * (any_reg ? 2 : 1);
+    s.wide = max_pw > 65536;
+    s.lds = (s.wide ? perm_path_bytes<uint32_t>(max_depth, s.threads)
+                    : perm_path_bytes<uint16_t>(max_depth, s.threads)) +
+            (size_t)s.threads * kPermGroup * 4 + (size_t)s.lds_words * 4;
+    s.chunks = (int)((max_n + s.threads - 1) / s.threads);
+    // workgroups sharing a row's path: doubled while they hold no more threads than
+    // the chip a few times over (about 3/8 of a tree's rows are out of bag;
+    // 3,000 x 120, 60 trees: 146 us with four, 133 with eight)
+    const int64_t oob = max_n * 3 / 8;
+    s.slices = 1;
+    while (s.slices < 8 && (int64_t)n_trees * oob * s.slices * 2 <= 512 * 1024) s.slices *= 2;
+    return s;
+}
+
+void launch_permut(JobDev* jobs, const TreeDev* trees, const NodeDev* nodes, const uint32_t* cls,
+                   int kmax, int n_trees, int max_depth, const PermutShape& s,
+                   unsigned long long* visits, hipStream_t st) {
+    const dim3 grid((unsigned)((n_trees + 7) / 8 * 8) * (unsigned)(s.chunks * s.slices)), wg(s.threads);
+    if (s.wide)
+        hipLaunchKernelGGL(k_permut<uint32_t>, grid, wg, s.lds, st, jobs, trees, n_trees, nodes,
+                           cls, kmax, max_depth, s.chunks, s.slices, s.lds_cols, s.lds_words, visits);
+    else
+        hipLaunchKernelGGL(k_permut<uint16_t>, grid, wg, s.lds, st, jobs, trees, n_trees, nodes,
+                           cls, kmax, max_depth, s.chunks, s.slices, s.lds_cols, s.lds_words, visits);
 }
 
 // The KL importance of job j over rows [r0, r0 + rb): base, deltas, reduce.
