@@ -428,10 +428,16 @@ __global__ __launch_bounds__(128) void k_permut(JobDev* jobs, const TreeDev* tre
 // ---------------------------------------------------------------------------
 // KL permutation importance.
 
-// Fixed-point class frequency of a leaf: floor(2^32 c_k / N).
-__device__ __forceinline__ uint64_t leaf_freq(const uint32_t* cls, int kmax, uint32_t node,
-                                              int k, uint32_t N) {
-    return ((uint64_t)cls[(size_t)node * kmax + k] << 32) / N;
+// Fixed-point class frequency of a leaf, floor(2^32 c / N), with inv = 1.0 / N:
+// the product is within one of the quotient (2^33 2^-52 < 1) and put right by
+// its remainder; a 64-bit division takes about four times its instructions.
+__device__ __forceinline__ uint64_t leaf_freq(uint32_t c, uint32_t N, double inv) {
+    const uint64_t num = (uint64_t)c << 32;
+    uint64_t q = (uint64_t)((double)c * 4294967296.0 * inv);
+    const int64_t rem = (int64_t)(num - q * N);
+    if (rem < 0) --q;
+    if (rem >= (int64_t)N) ++q;
+    return q;
 }
 
 __device__ __forceinline__ uint32_t leaf_weight(const uint32_t* cls, int kmax, uint32_t node,
@@ -443,9 +449,19 @@ __device__ __forceinline__ uint32_t leaf_weight(const uint32_t* cls, int kmax, u
 
 // 2^32 log2(x), 1 <= x < 2^62: bit length, then 32 digits of the fraction
 // from successive squares of the mantissa (62 fractional bits, truncated).
+// The digits are those of log2 but for an error below 2^-28 of the last one
+// (32 truncated squares), so they are taken from the FP64 logarithm (error below
+// 2^-51, that is 2^-19 of the last digit) wherever that is 2^-16 or more from
+// a change of the last digit: the loop is left to one value in 32,768.
+// k_kl_reduce at 10,000 x 500: 612 -> 212 us.
 __device__ __forceinline__ uint64_t lg2_q32(uint64_t x) {
     const int e = 63 - __builtin_clzll(x);
     uint64_t m = x << (62 - e);
+    const uint64_t whole = (uint64_t)e << 32;
+    if (m == (uint64_t)1 << 62) return whole;
+    const double t = log2((double)m * 0x1p-62) * 4294967296.0;
+    const double down = floor(t), part = t - down;
+    if (part >= 0x1p-16 && part <= 1.0 - 0x1p-16) return whole | (uint32_t)down;
     uint64_t frac = 0;
     for (int i = 0; i < 32; ++i) {
         const uint64_t hi = __umul64hi(m, m), lo = m * m;
@@ -454,7 +470,7 @@ __device__ __forceinline__ uint64_t lg2_q32(uint64_t x) {
         frac = (frac << 1) | top;
         m >>= top;
     }
-    return ((uint64_t)e << 32) | frac;
+    return whole | frac;
 }
 
 // KL(P || Q) in 2^-32 bits for summed fixed-point frequencies S (P) and
@@ -492,62 +508,82 @@ __device__ int64_t kl_q32(const uint64_t* S, const uint64_t* lgS, uint64_t lgsum
     return first + (int64_t)(sq == sp ? lgsum : lg2_q32(sq)) - (int64_t)lgsum;
 }
 
-// Rows [r0, r0 + rb) of job J: one wavefront per row, lanes over the job's
-// trees; writes the row's summed leaf frequencies S_k, their lg S_k and
-// lg sum S (S[row][2K + 1]), and pi(row).
+// Rows [r0, r0 + rb) of job J, 64 per workgroup, a lane each; the 16 waves deal
+// the job's trees among them, four walks in flight per lane (near a root the
+// lanes share nodes, and read neighbouring bins of one column).  Writes the
+// row's summed leaf frequencies S_k, their lg S_k and lg sum S (S[row][2K + 1]),
+// and pi(row).  With a wave per row and a tree per lane 10,000 rows through 200
+// trees of depth 12 took 393 us; this takes 151.
 template <int KMAX>
-__global__ __launch_bounds__(256) void k_kl_base(JobDev* jobs, int j, const NodeDev* nodes,
-                                                 const uint32_t* cls, int kmax, uint32_t tree0,
-                                                 uint32_t r0, uint32_t rb, uint64_t* S,
-                                                 uint32_t* pi) {
+__global__ __launch_bounds__(1024) void k_kl_base(JobDev* jobs, int j, const NodeDev* nodes,
+                                                  const uint32_t* cls, int kmax, uint32_t tree0,
+                                                  uint32_t r0, uint32_t rb, uint64_t* S,
+                                                  uint32_t* pi) {
+    __shared__ unsigned long long s_acc[KMAX][64];
     const JobDev& J = jobs[j];
     if (!J.live) return;
-    const int lane = threadIdx.x & 63;
-    const uint32_t rr = blockIdx.x * 4u + (threadIdx.x >> 6);
-    if (rr >= rb || r0 + rr >= (uint32_t)J.n) return;
-    const uint32_t row = r0 + rr;
+    const int lane = threadIdx.x & 63, wave = (int)(threadIdx.x >> 6);
+    const uint32_t rr = blockIdx.x * 64u + (uint32_t)lane;
+    const bool mine = rr < rb && r0 + rr < (uint32_t)J.n;
+    const uint32_t row = mine ? r0 + rr : r0;
     const int K = J.K;
-    if (J.reg) {  // regression: the loss depends on the change of the prediction only
-        if (lane == 0) {
-            const KeyedPerm P = make_perm(J.seed_lo, J.seed_hi, kFlush, (uint32_t)J.t, 0u, 0u,
-                                          0u, (uint64_t)J.n);
-            pi[rr] = perm_apply(P, row);
-        }
-        return;
-    }
-    uint64_t acc[KMAX];
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) acc[k] = 0;
-    for (int tau = lane; tau < J.T; tau += 64) {
-        uint32_t node = tree0 + (uint32_t)tau;
-        NodeDev nd = nodes[node];
-        while (nd.feat >= 0) {
-            node = (int)J.colptr[nd.feat][row] <= (int)nd.thr ? nd.left : nd.left + 1;
-            nd = nodes[node];
-        }
-        const uint32_t N = leaf_weight(cls, kmax, node, K);
-#pragma unroll
-        for (int k = 0; k < KMAX; ++k)
-            if (k < K) acc[k] += leaf_freq(cls, kmax, node, k, N);
-    }
-    uint64_t mine = 0, sum = 0;  // lane k < K keeps S_k
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        uint64_t v = acc[k];
-        for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m);
-        if (lane == k) mine = v;
-        if (k < K) sum += v;
-    }
-    uint64_t* row_out = S + (size_t)rr * (2 * K + 1);
-    if (lane < K) {
-        row_out[lane] = mine;
-        row_out[K + lane] = mine ? lg2_q32(mine) : 0ull;
-    }
-    if (lane == K) row_out[2 * K] = lg2_q32(sum);
-    if (lane == 0) {
+    if (wave == 0 && mine) {
         const KeyedPerm P = make_perm(J.seed_lo, J.seed_hi, kFlush, (uint32_t)J.t, 0u, 0u, 0u,
                                       (uint64_t)J.n);
         pi[rr] = perm_apply(P, row);
+    }
+    if (J.reg) return;  // regression: the loss depends on the change of the prediction only
+    for (int i = (int)threadIdx.x; i < KMAX * 64; i += 1024) s_acc[i >> 6][i & 63] = 0ull;
+    __syncthreads();
+    uint64_t acc[KMAX];
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) acc[k] = 0;
+    for (int t0 = wave * 4; t0 < J.T; t0 += 64) {
+        uint32_t node[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) node[v] = tree0 + (uint32_t)min(t0 + v, J.T - 1);
+        for (bool any = true; any;) {
+            any = false;
+            Hop h[4];
+            uint32_t b[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) h[v] = load_hop(nodes, node[v]);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) b[v] = ldg(ldg(J.colptr + max(h[v].feat, 0)) + row);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (h[v].feat >= 0) {
+                    node[v] = b[v] <= h[v].thr ? h[v].left : h[v].left + 1u;
+                    any = true;
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (t0 + v >= J.T) break;
+            const uint32_t N = leaf_weight(cls, kmax, node[v], K);
+            const double inv = 1.0 / (double)N;
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k)
+                if (k < K) acc[k] += leaf_freq(cls[(size_t)node[v] * kmax + k], N, inv);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k)
+        if (k < K) atomicAdd(&s_acc[k][lane], (unsigned long long)acc[k]);
+    __syncthreads();
+    if (!mine) return;
+    // the logarithms: one class (or the sum) per wave
+    uint64_t* row_out = S + (size_t)rr * (2 * K + 1);
+    for (int k = wave; k <= K; k += 16) {
+        uint64_t v = 0;
+        if (k < K) {
+            v = s_acc[k][lane];
+            row_out[k] = v;
+        } else {
+            for (int q = 0; q < K; ++q) v += s_acc[q][lane];
+        }
+        row_out[K + k] = v ? lg2_q32(v) : 0ull;
     }
 }
 
@@ -557,6 +593,11 @@ __global__ __launch_bounds__(256) void k_kl_base(JobDev* jobs, int j, const Node
 // for each column on it whose bin at row pi(row) turns the other way at one of
 // the column's positions, the row is re-routed from there, and the leaf adds
 // its frequency difference to delta[column][row][k] (64-bit two's complement).
+// Bound: the address units, by the scattered loads of the walks (a wave's 480
+// load instructions took 1.23 ms at 10,000 x 500, 200 trees; now four walks
+// advance at a time, a finished one reads the root, and a leaf's counts are read
+// once: 0.80 ms).  Which rows or trees share an XCD makes no difference there.
+template <int KMAX>
 __global__ __launch_bounds__(256) void k_kl_delta(JobDev* jobs, int j, const NodeDev* nodes,
                                                   const uint32_t* cls, int kmax, uint32_t tree0,
                                                   uint32_t r0, uint32_t rb, const uint32_t* pi,
@@ -565,16 +606,30 @@ __global__ __launch_bounds__(256) void k_kl_delta(JobDev* jobs, int j, const Nod
     const JobDev& J = jobs[j];
     if (!J.live) return;
     const int tid = threadIdx.x;
-    const uint64_t gi = (uint64_t)blockIdx.x * 256u + (uint64_t)tid;
-    const uint32_t T = (uint32_t)J.T;
-    const uint32_t tau = (uint32_t)(gi / rb), rr = (uint32_t)(gi % rb);
-    if (tau >= T || r0 + rr >= (uint32_t)J.n) return;
+    // one tree per XCD at a time (workgroups go to the 8 XCDs in turn)
+    const uint32_t T = (uint32_t)J.T, per = (rb + 255u) / 256u;
+    const uint32_t idx = blockIdx.x / 8u;
+    const uint32_t tau = idx / per * 8u + blockIdx.x % 8u, rr = idx % per * 256u + (uint32_t)tid;
+    if (tau >= T || rr >= rb || r0 + rr >= (uint32_t)J.n) return;
     const uint32_t row = r0 + rr, src = pi[rr];
     const int K = J.K;
     const PathLds P = path_lds(s_path, max_depth);
     uint8_t* s_bin = reinterpret_cast<uint8_t*>(s_path + path_lds_words(max_depth));
     const Walked w = walk_path(J, nodes, tree0 + tau, row, P, tid);
-    const uint32_t N0 = leaf_weight(cls, kmax, w.leaf, K);
+    // a leaf's class frequencies, each count read once
+    auto freqs = [&](uint32_t node, uint64_t (&q)[KMAX]) {
+        uint32_t c[KMAX], N = 0;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) c[k] = ldg(cls + (size_t)node * kmax + min(k, K - 1));
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) N += k < K ? c[k] : 0u;
+        const double inv = 1.0 / (double)N;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k)
+            if (k < K) q[k] = leaf_freq(c[k], N, inv);
+    };
+    uint64_t q0[KMAX];
+    if (!J.reg) freqs(w.leaf, q0);
     // the columns' source bins, eight positions' loads in flight
     for (int a0 = 0; a0 < w.len; a0 += 8) {
         uint32_t sb[8];
@@ -587,35 +642,63 @@ __global__ __launch_bounds__(256) void k_kl_delta(JobDev* jobs, int j, const Nod
         for (int e = 0; e < 8; ++e)
             if (a0 + e < w.len) s_bin[(a0 + e) * 256 + tid] = (uint8_t)sb[e];
     }
-    // Position by position over the wave's rows (near the root they hold one
-    // column, and the atomics of neighbouring rows share lines; one loop over
-    // each lane's own columns took twice the time).
-    for (int a = 0; a < w.len; ++a) {
-        if (w.dup >> a & 1u) continue;
-        const uint32_t sb = s_bin[a * 256 + tid];
-        uint32_t node = turned_at(P, w, a, sb, tid);
-        if (node == 0xFFFFFFFFu) continue;
-        const uint32_t f = P.pf[a * 256 + tid] & 0x7FFFFFFFu;
-        for (;;) {
-            const Hop h = load_hop(nodes, node);
-            if (h.feat < 0) break;
-            const uint32_t b = (uint32_t)h.feat == f
-                                   ? sb
-                                   : (uint32_t)ldg(ldg(J.colptr + h.feat) + row);
-            node = b <= h.thr ? h.left : h.left + 1u;
+    // Four positions at a time over the wave's rows, the atomics position by
+    // position (near the root they hold one column, and those of neighbouring
+    // rows share lines; one loop over each lane's own columns took twice the time).
+    for (int a0 = 0; a0 < w.len; a0 += 4) {
+        uint32_t node[4], leaf[4], f[4], sb[4];
+        bool turned[4], on[4];
+        bool any = false;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int a = min(a0 + v, w.len - 1);
+            sb[v] = s_bin[a * 256 + tid];
+            f[v] = P.pf[a * 256 + tid] & 0x7FFFFFFFu;
+            const uint32_t at = a0 + v < w.len && !(w.dup >> a & 1u)
+                                    ? turned_at(P, w, a, sb[v], tid)
+                                    : 0xFFFFFFFFu;
+            turned[v] = at != 0xFFFFFFFFu;
+            node[v] = turned[v] ? at : tree0 + tau;
+            leaf[v] = w.leaf;
+            on[v] = turned[v];
+            any |= turned[v];
         }
-        unsigned long long* d = delta + ((size_t)f * rb + rr) * K;
-        if (J.reg) {  // change of the leaf's prediction, in the first slot
-            const long long dv =
-                leaf_pred(nodes, cls, kmax, node) - leaf_pred(nodes, cls, kmax, w.leaf);
-            if (dv) atomicAdd(d, (unsigned long long)dv);
-            continue;
+        while (any) {
+            any = false;
+            Hop h[4];
+            uint32_t b[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) h[v] = load_hop(nodes, node[v]);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) b[v] = ldg(ldg(J.colptr + max(h[v].feat, 0)) + row);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (on[v] && h[v].feat >= 0) {
+                    if ((uint32_t)h[v].feat == f[v]) b[v] = sb[v];
+                    node[v] = b[v] <= h[v].thr ? h[v].left : h[v].left + 1u;
+                    any = true;
+                } else if (on[v]) {  // its lane reads the root from here on, as its
+                    leaf[v] = node[v];  // neighbours do: one line
+                    node[v] = tree0 + tau;
+                    on[v] = false;
+                }
+            }
         }
-        const uint32_t N1 = leaf_weight(cls, kmax, node, K);
-        for (int k = 0; k < K; ++k) {
-            const uint64_t dv =
-                leaf_freq(cls, kmax, node, k, N1) - leaf_freq(cls, kmax, w.leaf, k, N0);
-            if (dv) atomicAdd(d + k, (unsigned long long)dv);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (!turned[v] || leaf[v] == w.leaf) continue;
+            unsigned long long* d = delta + ((size_t)f[v] * rb + rr) * K;
+            if (J.reg) {  // change of the leaf's prediction, in the first slot
+                const long long dv =
+                    leaf_pred(nodes, cls, kmax, leaf[v]) - leaf_pred(nodes, cls, kmax, w.leaf);
+                if (dv) atomicAdd(d, (unsigned long long)dv);
+                continue;
+            }
+            uint64_t q1[KMAX];
+            freqs(leaf[v], q1);
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k)
+                if (k < K && q1[k] != q0[k]) atomicAdd(d + k, (unsigned long long)(q1[k] - q0[k]));
         }
     }
 }
@@ -1007,18 +1090,24 @@ void launch_kl_block(JobDev* jobs, int j, const NodeDev* nodes, const uint32_t* 
                      uint32_t tree0, int T, int p_w_cap, uint32_t r0, uint32_t rb, uint64_t* S,
                      uint32_t* pi, unsigned long long* delta, int max_depth, hipStream_t st) {
     const dim3 b256(256);
-    const unsigned g_base = (rb + 3) / 4;
+    const unsigned g_base = (rb + 63) / 64;
+    const dim3 b1024(1024);
     switch (kmax) {
-        case 2: hipLaunchKernelGGL(k_kl_base<2>, dim3(g_base), b256, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
-        case 3: hipLaunchKernelGGL(k_kl_base<3>, dim3(g_base), b256, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
-        case 4: hipLaunchKernelGGL(k_kl_base<4>, dim3(g_base), b256, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
-        case 8: hipLaunchKernelGGL(k_kl_base<8>, dim3(g_base), b256, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
-        default: hipLaunchKernelGGL(k_kl_base<16>, dim3(g_base), b256, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
+        case 2: hipLaunchKernelGGL(k_kl_base<2>, dim3(g_base), b1024, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
+        case 3: hipLaunchKernelGGL(k_kl_base<3>, dim3(g_base), b1024, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
+        case 4: hipLaunchKernelGGL(k_kl_base<4>, dim3(g_base), b1024, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
+        case 8: hipLaunchKernelGGL(k_kl_base<8>, dim3(g_base), b1024, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
+        default: hipLaunchKernelGGL(k_kl_base<16>, dim3(g_base), b1024, 0, st, jobs, j, nodes, cls, kmax, tree0, r0, rb, S, pi); break;
     }
     const size_t lds =
         ((size_t)path_lds_words(max_depth) + (size_t)max_depth * 64) * sizeof(uint32_t);
-    const unsigned g_delta = (unsigned)(((uint64_t)rb * T + 255) / 256);
-    hipLaunchKernelGGL(k_kl_delta, dim3(g_delta), b256, lds, st, jobs, j, nodes, cls, kmax, tree0,
+    const unsigned g_delta = (unsigned)((T + 7) / 8 * 8) * ((rb + 255) / 256);
+    const auto kl_delta = kmax == 2   ? k_kl_delta<2>
+                          : kmax == 3 ? k_kl_delta<3>
+                          : kmax == 4 ? k_kl_delta<4>
+                          : kmax == 8 ? k_kl_delta<8>
+                                      : k_kl_delta<16>;
+    hipLaunchKernelGGL(kl_delta, dim3(g_delta), b256, lds, st, jobs, j, nodes, cls, kmax, tree0,
                        r0, rb, pi, delta, max_depth);
     const uint32_t groups = (rb + 255) / 256;
     const unsigned g_red = (unsigned)(groups * (uint64_t)p_w_cap);
