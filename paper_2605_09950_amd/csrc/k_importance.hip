@@ -203,18 +203,18 @@ __host__ __device__ constexpr uint32_t perm_path_bytes(int max_depth, uint32_t t
 template <class Col>
 __global__ __launch_bounds__(128) void k_permut(JobDev* jobs, const TreeDev* trees, int n_trees,
                                                 const NodeDev* nodes, const uint32_t* cls,
-                                                int kmax, int max_depth, int chunks,
-                                                int slices, int lds_cols, int lds_words,
+                                                int kmax, int max_depth, int slices,
+                                                int lds_cols, int lds_words,
                                                 unsigned long long* visits) {
     // [kPermGroup][threads]: a group's source rows, then its walks' first nodes;
     // the column drops (lds_words); the paths
     extern __shared__ uint32_t s_perm[];
     const uint32_t S = blockDim.x;
-    const uint32_t idx = blockIdx.x / 8u / (uint32_t)slices;
-    const uint32_t slice = blockIdx.x / 8u % (uint32_t)slices;
-    const uint32_t g = idx / (uint32_t)chunks * 8u + blockIdx.x % 8u;
+    // grid: x = (chunk, slice) times the 8 XCDs, y = eighths of the trees
+    const uint32_t g = blockIdx.y * 8u + blockIdx.x % 8u;
     if (g >= (uint32_t)n_trees) return;
-    const uint32_t chunk = idx % (uint32_t)chunks;
+    const uint32_t slice = blockIdx.x / 8u % (uint32_t)slices;
+    const uint32_t chunk = blockIdx.x / 8u / (uint32_t)slices;
     const TreeDev tr = trees[g];
     JobDev& J = jobs[tr.job];
     if (!J.live || J.mode != 1) return;  // finished job, or TreeImp job of a mixed batch
@@ -1076,13 +1076,14 @@ PermutShape permut_shape(int n_trees, int64_t max_n, int max_depth, int max_pw, 
 void launch_permut(JobDev* jobs, const TreeDev* trees, const NodeDev* nodes, const uint32_t* cls,
                    int kmax, int n_trees, int max_depth, const PermutShape& s,
                    unsigned long long* visits, hipStream_t st) {
-    const dim3 grid((unsigned)((n_trees + 7) / 8 * 8) * (unsigned)(s.chunks * s.slices)), wg(s.threads);
+    const dim3 grid(8u * (unsigned)(s.chunks * s.slices), (unsigned)((n_trees + 7) / 8));
+    const dim3 wg(s.threads);
     if (s.wide)
         hipLaunchKernelGGL(k_permut<uint32_t>, grid, wg, s.lds, st, jobs, trees, n_trees, nodes,
-                           cls, kmax, max_depth, s.chunks, s.slices, s.lds_cols, s.lds_words, visits);
+                           cls, kmax, max_depth, s.slices, s.lds_cols, s.lds_words, visits);
     else
         hipLaunchKernelGGL(k_permut<uint16_t>, grid, wg, s.lds, st, jobs, trees, n_trees, nodes,
-                           cls, kmax, max_depth, s.chunks, s.slices, s.lds_cols, s.lds_words, visits);
+                           cls, kmax, max_depth, s.slices, s.lds_cols, s.lds_words, visits);
 }
 
 // The KL importance of job j over rows [r0, r0 + rb): base, deltas, reduce.

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(1024) void k_sort_bin(const uint32_t* keys, int64_t
     extern __shared__ uint32_t s[];  // P keys
     __shared__ uint32_t s_cut[256];
     __shared__ int s_m;
-    const uint32_t* col = keys + (size_t)blockIdx.x * P;
+    const uint32_t* col = keys + (size_t)blockIdx.y * P;
     const int tid = threadIdx.x, threads = (int)blockDim.x;
     uint32_t v[kSortTile / 1024];
 #pragma unroll
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(1024) void k_sort_bin(const uint32_t* keys, int64_t
     }
     __syncthreads();
     const int m = s_m;
-    uint8_t* out = bins + (size_t)blockIdx.x * n_pad;
+    uint8_t* out = bins + (size_t)blockIdx.y * n_pad;
 #pragma unroll
     for (int q = 0; q < kSortTile / 1024; ++q) {
         const int i = tid + q * threads;
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(1024) void k_select_bin(const uint32_t* keys, int64
     __shared__ uint32_t s_pre[256], s_cut[256];  // a cut's digits so far; the cuts
     __shared__ int s_m;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t* col = keys + (size_t)blockIdx.x * P;
+    const uint32_t* col = keys + (size_t)blockIdx.y * P;
     // calls f(key) for every key, keys in lanes as they come
     auto each = [&](auto f) {
         const uint4* c4 = reinterpret_cast<const uint4*>(col);
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(1024) void k_select_bin(const uint32_t* keys, int64
     }
     __syncthreads();
     const int m = s_m;
-    uint32_t* out = reinterpret_cast<uint32_t*>(bins + (size_t)blockIdx.x * n_pad);
+    uint32_t* out = reinterpret_cast<uint32_t*>(bins + (size_t)blockIdx.y * n_pad);
     for (int64_t i = tid; i < n_pad / 4; i += 1024) {
         uint32_t w = 0u;
         if (4 * i < n) {
@@ -688,12 +688,12 @@ void launch_binning(const float* X, int64_t n, int64_t p, int B, uint8_t* bins, 
     hipLaunchKernelGGL(k_to_keys, dim3((unsigned)((p + 31) / 32), (unsigned)((P + 31) / 32)),
                        dim3(256), 0, st, X, n, p, P, keys);
     if (P > kSortTile) {
-        hipLaunchKernelGGL(k_select_bin, dim3((unsigned)p), dim3(1024), 0, st, keys, n, P, B, bins,
-                           n_pad);
+        hipLaunchKernelGGL(k_select_bin, dim3(1, (unsigned)p), dim3(1024), 0, st, keys, n, P, B,
+                           bins, n_pad);
     } else {
         const int threads = P < 128 ? 64 : (P < 2048 ? (int)P / 2 : 1024);
-        hipLaunchKernelGGL(k_sort_bin, dim3((unsigned)p), dim3(threads), (size_t)P * 4, st, keys,
-                           n, (int)P, B, bins, n_pad);
+        hipLaunchKernelGGL(k_sort_bin, dim3(1, (unsigned)p), dim3(threads), (size_t)P * 4, st,
+                           keys, n, (int)P, B, bins, n_pad);
     }
 }
 
