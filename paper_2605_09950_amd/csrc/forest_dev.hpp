@@ -333,7 +333,8 @@ struct ItemBest {
 // any order (score q, threshold b, split side; ok: valid).
 // With FP32 ranking the candidates within the margin of the wave's maximum are
 // compared exactly, and not at all when they are one threshold; with exact
-// ranking all are.  Ties keep the smaller threshold.
+// ranking all are.  Ties keep the smaller threshold; without a candidate the
+// score is negative and the bin 0.
 template <int FB, int NS>
 __device__ __forceinline__ ItemBest pick_threshold(const float* q, const int* b, const Side* sd,
                                                    const bool* ok, uint32_t N, int split_rank) {
@@ -391,8 +392,10 @@ __device__ __forceinline__ ItemBest pick_threshold(const float* q, const int* b,
             bb = ob;
         }
     }
-    r.b = (int)uniform((uint32_t)bb);
-    if (!split_rank) r.q = uniform(best.nd) ? 1.0f : -1.0f;
+    // no candidate: bin 0, as callers read the histogram at the bin they get
+    const bool any = uniform(best.nd) != 0u;
+    r.b = any ? (int)uniform((uint32_t)bb) : 0;
+    if (!split_rank) r.q = any ? 1.0f : -1.0f;
     return r;
 }
 
