@@ -135,7 +135,8 @@ void mark_shared_inputs(std::vector<Spec>& specs) {
 
 struct Opts {
     int B = 256, R = 1, split_rank = 1, form = 1, graph = 1;
-    int small_rows = 32, grid_small = 0, grid_hist = 0, grid_finalize = 0;
+    // small_rows 0: the library's choice
+    int small_rows = 0, grid_small = 0, grid_hist = 0, grid_finalize = 0;
     int col_level = 0, col_unit = 2048, grid_col = 0, kl_rows = 0;
     int perc = 100, rough_fix = 0;
     // histogram shapes: rows per lane per batch of the node-major kernel before
@@ -157,7 +158,7 @@ Opts read_opts(const boruta_options* o) {
         r.split_rank = o->split_rank;
         r.form = o->form;
         r.graph = o->graph;
-        if (o->small_rows) r.small_rows = o->small_rows;
+        r.small_rows = o->small_rows;
         r.grid_small = o->grid_small;
         r.grid_hist = o->grid_hist;
         r.grid_finalize = o->grid_finalize;
@@ -182,7 +183,7 @@ Opts read_opts(const boruta_options* o) {
         throw Error(BORUTA_E_INVALID_ARG, "split_rank must be 0 or 1");
     if (r.form != 0 && r.form != 1) throw Error(BORUTA_E_INVALID_ARG, "form must be 0 or 1");
     if (r.graph != 0 && r.graph != 1) throw Error(BORUTA_E_INVALID_ARG, "graph must be 0 or 1");
-    if (r.small_rows < 2 || r.small_rows > kSmallRows)
+    if (r.small_rows != 0 && (r.small_rows < 2 || r.small_rows > kSmallRows))
         throw Error(BORUTA_E_INVALID_ARG, "small_rows outside [2, 64]");
     if (r.grid_small < 0 || r.grid_hist < 0 || r.grid_finalize < 0 || r.grid_small > 65536 ||
         r.grid_hist > 65536 || r.grid_finalize > 65536)
@@ -255,7 +256,10 @@ void apply_tune_cache(Opts& r, const boruta_options* o, const std::vector<Spec>&
         if (o->name == d.name) r.name = v;                              \
         continue;                                                       \
     }
-            BORUTA_TUNE_FIELD(small_rows)
+            if (key == "small_rows") {  // 0, the library's choice, is no choice either
+                if (o->small_rows == 0 || o->small_rows == d.small_rows) r.small_rows = v;
+                continue;
+            }
             BORUTA_TUNE_FIELD(grid_small)
             BORUTA_TUNE_FIELD(grid_hist)
             BORUTA_TUNE_FIELD(grid_finalize)
@@ -415,6 +419,9 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     pl.kmax = maxK <= 4 ? maxK : (maxK <= 8 ? 8 : 16);
     pl.keys = r.take((size_t)keys_words * 4);
     uint64_t node_cap = 0, slot_cap = 0, small_cap = 0, n_gcol = 0;
+    // the large-node lists are sized for the chosen row limit of the wave path, and
+    // for the options' default where the library chooses it (never below that)
+    const int min_rows = o.small_rows ? o.small_rows : 32;
     uint64_t kl_S = 0, kl_pi = 0, kl_delta = 0;
     for (const Spec& s : specs) {
         JobPlan j;
@@ -477,7 +484,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         // pair unused), so the pool holds up to twice the nodes of the trees
         node_cap += T + 2 * T * per_tree_nodes;
         const uint64_t large_per_tree =
-            (uint64_t)(s.n + o.small_rows) / (uint64_t)(o.small_rows + 1);
+            (uint64_t)(s.n + min_rows) / (uint64_t)(min_rows + 1);
         slot_cap += T * large_per_tree;
         small_cap += T * (uint64_t)((s.n + 1) / 2);
         pl.max_sha = std::max(pl.max_sha, j.max_sha);
@@ -529,11 +536,11 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         pl.fw = fw;
     }
     pl.npi = (pl.mtry_cap + pl.fw - 1) / pl.fw;
-    // The wave path's row limit at its default: 64, one row per lane (the 64-job
+    // The wave path's row limit where none is chosen: 64, one row per lane (the 64-job
     // batch 158 ms at 32, 137 at 64; 10,000 x 500 82.2 and 79.6; 7 classes exact
     // 11.5 and 10.7; regression 75.3 and 72.5; 100,000 x 2,000, whose bins the wave
     // path reads by row, 144.0 and 140.1).
-    pl.small_rows = o.small_rows == 32 ? 64 : o.small_rows;
+    pl.small_rows = o.small_rows ? o.small_rows : 64;
     if (node_cap >= 0xFFFFFFF0ull || slot_cap * (uint64_t)pl.mtry_cap + n_gcol >= 0xFFFFFFF0ull ||
         small_cap >= 0xFFFFFFF0ull)
         throw Error(BORUTA_E_INVALID_ARG, "problem too large: more than 2^32 tree nodes");
@@ -615,9 +622,10 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     //   3,000 x 300 (72,000)       663 774 916 1003 1239 / 871 873 889 909 1419
     //   10,000 x 300 (240,000)     904 1232 1661 1896 2550 / 1932 2011 2065 2118 3829
     // (16 waves per tree, 8 past 256 trees: two trees per compute unit).  Chosen
-    // launch shapes are those of the level kernels.
-    const bool shapes = o.small_rows != 32 || o.grid_small || o.grid_hist || o.grid_finalize ||
-                        o.col_level || o.col_unit != 2048 || o.grid_col || o.hist_rb != 8 ||
+    // launch shapes are those of the level kernels (the options' default row limit,
+    // which k_grow keeps to, is no such choice).
+    const bool shapes = (o.small_rows && o.small_rows != 32) || o.grid_small || o.grid_hist ||
+                        o.grid_finalize || o.col_level || o.col_unit != 2048 || o.grid_col || o.hist_rb != 8 ||
                         o.hist_rb_deep != 8 || o.band_level != 6 || o.hist_fw || o.col_waves;
     if (o.form == BORUTA_FORM_BATCHED && !any_reg && !shapes && pl.col_level >= pl.max_D) {
         int64_t pairs = 0;
