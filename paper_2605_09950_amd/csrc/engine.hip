@@ -539,8 +539,12 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     // The wave path's row limit where none is chosen: 64, one row per lane (the 64-job
     // batch 158 ms at 32, 137 at 64; 10,000 x 500 82.2 and 79.6; 7 classes exact
     // 11.5 and 10.7; regression 75.3 and 72.5; 100,000 x 2,000, whose bins the wave
-    // path reads by row, 144.0 and 140.1).
-    pl.small_rows = o.small_rows ? o.small_rows : 64;
+    // path reads by row, 144.0 and 140.1).  The plain form, whose nodes run one
+    // after the other, takes 32: above it the histogram items of one node spread
+    // over the chip (one iteration at 32 and 64: 2,000 x 20,000, 2 classes, 4 trees
+    // 25.0 and 38.4 ms; 10,000 x 500, 3 classes 30.5 and 35.1; 5,000 x 200, 4 classes
+    // 19.9 and 21.4; regression 3,000 x 600 17.7 and 21.1).
+    pl.small_rows = o.small_rows ? o.small_rows : (o.form == BORUTA_FORM_PLAIN ? 32 : 64);
     if (node_cap >= 0xFFFFFFF0ull || slot_cap * (uint64_t)pl.mtry_cap + n_gcol >= 0xFFFFFFF0ull ||
         small_cap >= 0xFFFFFFF0ull)
         throw Error(BORUTA_E_INVALID_ARG, "problem too large: more than 2^32 tree nodes");

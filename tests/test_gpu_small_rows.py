@@ -1,5 +1,6 @@
 """The wave path's row limit: each chosen value is the one that acts, 32 among
-them, from the caller and from a tuning cache; the library's choice is 64."""
+them, from the caller and from a tuning cache; the library's choice is 64, and
+32 in the plain form."""
 import numpy as np
 import pytest
 
@@ -32,3 +33,9 @@ def test_every_chosen_limit_acts(tmp_path):
     for _, r in runs.values():
         for k in ("decision", "hits", "shadow_max", "imp_history"):
             assert np.array_equal(r[k], base[k], equal_nan=True)
+
+
+def test_the_plain_form_keeps_to_32():
+    n = {rows: wave_nodes(dict(small_rows=rows) if rows else None, form=B.FORM_PLAIN)[0]
+         for rows in (0, 32, 64)}
+    assert n[0] == n[32] < n[64]
