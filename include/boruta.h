@@ -129,8 +129,10 @@ typedef struct {
     int32_t small_rows;   /* nodes with at most this many distinct rows (and a
                              weighted count below the packed-counter limit) take
                              the wavefront path, [2, 64]; 0 = the library's choice
-                             (64, in the plain form 32), which calls without
-                             options take; default 32                           */
+                             (64; 32 in the plain form and for forests of many
+                             draws and few rows and trees; small regression
+                             forests take none), which calls without options
+                             take; default 32                                    */
     /* "needed" below: for the nodes tree level d can hold, at most the
      * plan's capacity and n_trees * 2^d; a chosen grid size is an upper
      * limit, lowered to what a level needs.                                */

@@ -26,7 +26,7 @@ from paper_2605_09950_amd import binding as B
 
 # candidate values per parameter, in search order (0 = library default).
 # small_rows moves nodes between the two split-search kernels; it is left at
-# the library's choice (64) unless the caller asks for it, so that per-kernel
+# the library's choice unless the caller asks for it, so that per-kernel
 # measurements stay comparable between tuned runs.
 CANDIDATES = (
     ("col_level", (64, 5, 3, 7)),
@@ -42,7 +42,7 @@ CANDIDATES = (
     ("grid_finalize", (0, 1024, 2048, 8192)),
 )
 # what the library takes for a parameter that is not chosen
-DEFAULTS = {"small_rows": 64, "col_unit": 2048, "hist_rb": 8, "hist_rb_deep": 8,
+DEFAULTS = {"col_unit": 2048, "hist_rb": 8, "hist_rb_deep": 8,
             "band_level": 6}
 
 

@@ -406,6 +406,59 @@ struct Plan {
     size_t total = 0;
 };
 
+int max_shadows(const Spec& s) { return (int)std::max<int64_t>(s.p, 8); }
+// Most columns that a node of the job draws.
+int mtry_cap(const Spec& s) {
+    const int64_t pw = s.p + max_shadows(s);
+    return s.mtry > 0 ? (int)std::min<int64_t>(s.mtry, pw) : isqrt_i(pw);
+}
+
+// Row limit of the wave path: the chosen one, or the library's (1: no node takes it).
+// A wave searches all of a node's draws one after the other, the histogram path
+// gives each draw a wave of its own: where a level's nodes alone do not fill the
+// chip, the wave path pays only while the draws are few.  Limits 32 / 64, six
+// iterations of depth 10 in ms:
+//   classification, 24 draws: 64 wins by 2-11% at all sizes; 34: by up to 7% either way
+//     63   2,000 x 2,000, 10 trees 3.62 / 4.29, 50 4.15 / 4.40, 200 5.84 / 5.56
+//     200  600 x 20,000, 50 trees 8.5 / 11.0, 500 12.2 / 12.6; 2,000 rows, 200 14.1 / 14.3
+//     (the 64-job batch 158 / 137, 10,000 x 500 82.2 / 79.6 for whole runs)
+//   regression, up to 10 draws: 64 wins or ties
+//     34   2,000 x 600, 10 trees 4.06 / 5.48, 200 6.7 / 7.3, 500 11.3 / 11.4
+//     100  600 x 5,000, 50 trees 5.7 / 12.3, 500 12.7 / 17.5
+// Regression forests of few histogram items a level do without the wave path: its
+// launch and the second stream cost 10-14 us a level.  None / the better limit:
+//     7    5,000 x 30, depth 12, 30 trees 4.50 / 4.98, 60 5.67 / 5.31, 100 7.13 / 5.90
+//     34   1,000 x 600, depth 8, 30 trees 2.82 / 3.18, 60 3.33 / 3.38, 100 4.03 / 3.64
+//     100  600 x 5,000, depth 10, 10 trees 4.11 / 5.47, 50 7.23 / 5.73
+// but where a wave's few draws are done before the histogram kernels' chain, in
+// trees of few rows (4 draws, 300 x 10, depth 16, 30 trees 5.57 / 4.53).
+// The plain form, whose nodes run one after the other, takes 32 (one iteration
+// at 32 and 64: 2,000 x 20,000, 2 classes, 4 trees 25.0 and 38.4 ms; 10,000 x 500, 3
+// classes 30.5 and 35.1; regression 3,000 x 600 17.7 and 21.1).
+int wave_rows(const std::vector<Spec>& specs, const Opts& o) {
+    if (o.small_rows) return o.small_rows;
+    if (o.form == BORUTA_FORM_PLAIN) return 32;
+    bool cls = false, reg = false;
+    double rows = 0.0, items = 0.0;  // of all trees; histogram items of an iteration
+    int draws = 1, depth = 1;
+    int64_t longest = 0;
+    for (const Spec& s : specs) {
+        (s.yr ? reg : cls) = true;
+        const int m = mtry_cap(s);
+        rows += (double)s.n * s.T;
+        for (int d = 0; d < s.D; ++d)
+            items += (double)s.T * m * std::min(std::ldexp(1.0, d), 0.25 * (double)s.n);
+        draws = std::max(draws, m);
+        depth = std::max(depth, s.D);
+        longest = std::max(longest, s.n);
+    }
+    const double few = draws <= 4 ? 25000.0 : draws <= 64 ? 50000.0 : 125000.0;  // a level
+    if (!cls && items <= few * depth && (draws > 4 || longest > 400)) return 1;
+    if (reg && draws > 10 && rows < 30000.0 * draws) return 32;
+    if (cls && draws > 40 && rows < 2000.0 * draws) return 32;
+    return 64;
+}
+
 Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_device) {
     Plan pl;
     Region r;
@@ -419,21 +472,21 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     pl.kmax = maxK <= 4 ? maxK : (maxK <= 8 ? 8 : 16);
     pl.keys = r.take((size_t)keys_words * 4);
     uint64_t node_cap = 0, slot_cap = 0, small_cap = 0, n_gcol = 0;
-    // the large-node lists are sized for the chosen row limit of the wave path, and
-    // for the options' default where the library chooses it (never below that)
-    const int min_rows = o.small_rows ? o.small_rows : 32;
+    // the large-node lists are sized for the chosen row limit of the wave path; where
+    // the library chooses it, for the options' default or less
+    const int min_rows = o.small_rows ? o.small_rows : std::min(wave_rows(specs, o), 32);
     uint64_t kl_S = 0, kl_pi = 0, kl_delta = 0;
     for (const Spec& s : specs) {
         JobPlan j;
         const JobPlan* sh = s.share >= 0 ? &pl.jp[(size_t)s.share] : nullptr;
         j.n_pad = round_up(s.n, 256);
         j.P = pow2_at_least(s.n);
-        j.max_sha = (int)std::max<int64_t>(s.p, 8);
-        j.pw_cap = (int)(s.p + j.max_sha);
+        j.max_sha = max_shadows(s);
+        j.pw_cap = (int)s.p + j.max_sha;
         j.gbase = (uint32_t)n_gcol;
         n_gcol += (uint64_t)j.pw_cap;
         pl.gq_max = std::max<uint32_t>(pl.gq_max, (uint32_t)(j.n_pad / 16));
-        j.mtry_max = s.mtry > 0 ? std::min(s.mtry, j.pw_cap) : isqrt_i(j.pw_cap);
+        j.mtry_max = mtry_cap(s);
         const size_t n = (size_t)s.n, p = (size_t)s.p, T = (size_t)s.T;
         j.X = inputs_on_device || sh ? 0 : r.take(n * p * 4);
         j.y32 = inputs_on_device || sh ? 0 : r.take(n * 4);
@@ -536,15 +589,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         pl.fw = fw;
     }
     pl.npi = (pl.mtry_cap + pl.fw - 1) / pl.fw;
-    // The wave path's row limit where none is chosen: 64, one row per lane (the 64-job
-    // batch 158 ms at 32, 137 at 64; 10,000 x 500 82.2 and 79.6; 7 classes exact
-    // 11.5 and 10.7; regression 75.3 and 72.5; 100,000 x 2,000, whose bins the wave
-    // path reads by row, 144.0 and 140.1).  The plain form, whose nodes run one
-    // after the other, takes 32: above it the histogram items of one node spread
-    // over the chip (one iteration at 32 and 64: 2,000 x 20,000, 2 classes, 4 trees
-    // 25.0 and 38.4 ms; 10,000 x 500, 3 classes 30.5 and 35.1; 5,000 x 200, 4 classes
-    // 19.9 and 21.4; regression 3,000 x 600 17.7 and 21.1).
-    pl.small_rows = o.small_rows ? o.small_rows : (o.form == BORUTA_FORM_PLAIN ? 32 : 64);
+    pl.small_rows = wave_rows(specs, o);
     if (node_cap >= 0xFFFFFFF0ull || slot_cap * (uint64_t)pl.mtry_cap + n_gcol >= 0xFFFFFFF0ull ||
         small_cap >= 0xFFFFFFF0ull)
         throw Error(BORUTA_E_INVALID_ARG, "problem too large: more than 2^32 tree nodes");
@@ -1135,16 +1180,20 @@ void Engine::enqueue_iteration() {
         // nodes, child pairs, row segments and kinds entries: without kernel
         // statistics the small-node launch runs on a second stream, beside
         // the large-node kernels, and rejoins before the lists are built.
-        const bool fork = !stats && side != nullptr;
+        const bool wave = pl.has_cls || pl.small_rows > 1;
+        const bool fork = wave && !stats && side != nullptr;
         hipStream_t ss = st;
         if (fork) {
             HIPC(hipEventRecord(ev_fork, st));
             HIPC(hipStreamWaitEvent(side, ev_fork, 0));
             ss = side;
         }
-        size_t h = clock.begin(stats ? &stats->hist_small : nullptr, ss);
-        launch_split_small(F, d, 0, kAll, g_small, ss);
-        clock.end(h, ss);
+        size_t h = 0;
+        if (wave) {
+            h = clock.begin(stats ? &stats->hist_small : nullptr, ss);
+            launch_split_small(F, d, 0, kAll, g_small, ss);
+            clock.end(h, ss);
+        }
         if (fork) HIPC(hipEventRecord(ev_join, side));
         const bool col = d >= pl.col_level;
         if (col) {

@@ -1,11 +1,13 @@
 """The wave path's row limit: each chosen value is the one that acts, 32 among
-them, from the caller and from a tuning cache; the library's choice is 64, and
-32 in the plain form."""
+them, from the caller and from a tuning cache; the library's choice is 64, less
+in the plain form and for forests of many draws or few nodes."""
 import numpy as np
 import pytest
 
+from oracle import oracle as O
 from paper_2605_09950_amd import autotune as A
 from paper_2605_09950_amd import binding as B
+from tests.parity_helpers import assert_same_run
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +41,34 @@ def test_the_plain_form_keeps_to_32():
     n = {rows: wave_nodes(dict(small_rows=rows) if rows else None, form=B.FORM_PLAIN)[0]
          for rows in (0, 32, 64)}
     assert n[0] == n[32] < n[64]
+
+
+@pytest.mark.parametrize("n,p,K,trees,depth,limit", [
+    (300, 20, 0, 10, 8, 0), (600, 8, 0, 10, 8, 0), (200, 2200, 0, 20, 8, 0),  # no wave path
+    (200, 600, 0, 60, 10, 32), (300, 8, 0, 10, 8, 64), (300, 20, 0, 400, 8, 64),
+    (150, 2000, 2, 10, 6, 32), (150, 300, 3, 10, 6, 64)])
+def test_the_limit_follows_the_forest(n, p, K, trees, depth, limit):
+    # both sides of the rule's lines, regression (K = 0) and classification
+    rng = np.random.default_rng(n + p)
+    X = rng.standard_normal((n, p)).astype(np.float32)
+    s = X[:, :3] + 0.5 * rng.standard_normal((n, 3))
+    kw = dict(max_iter=2, seed=3, trace=True)
+    print(f"library's limit n={n} p={p} K={K} T={trees} D={depth}: {limit}", flush=True)
+    if K:
+        y = np.argmax(s[:, :K], axis=1).astype(np.int32)
+        o = O.boruta_fit(X, y, K, trees, depth, **kw)
+        run = lambda **o: B.boruta_fit_ex(X, y, K, trees, depth, **kw, **o)  # noqa: E731
+    else:
+        y = s.sum(axis=1).astype(np.float32)
+        o = O.boruta_fit_reg(X, y, trees, depth, **kw)
+        run = lambda **o: B.boruta_fit_regression(X, y, trees, depth, **kw, **o)  # noqa: E731
+    assert_same_run(run(), o)
+    own = run(stats=True)
+    assert_same_run(own, o)
+    if limit:
+        want = run(stats=True, tune=dict(small_rows=limit))
+        other = run(stats=True, tune=dict(small_rows=96 - limit))
+        assert list(own["stats"].level_small) == list(want["stats"].level_small)
+        assert sum(own["stats"].level_small) != sum(other["stats"].level_small)
+    else:
+        assert sum(own["stats"].level_small) == 0
