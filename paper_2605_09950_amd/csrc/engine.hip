@@ -670,19 +670,33 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     //   1,000 x 300 (24,000)       582 639 699 739 827 / 522 526 541 551 733
     //   3,000 x 300 (72,000)       663 774 916 1003 1239 / 871 873 889 909 1419
     //   10,000 x 300 (240,000)     904 1232 1661 1896 2550 / 1932 2011 2065 2118 3829
-    // (16 waves per tree, 8 past 256 trees: two trees per compute unit).  Chosen
-    // launch shapes are those of the level kernels (the options' default row limit,
-    // which k_grow keeps to, is no such choice).
+    // (16 waves per tree, 8 past 256 trees: two trees per compute unit).  With 5 to 8
+    // classes long trees of many rows lose (rows times classes: level kernels /
+    // k_grow, five iterations of depth 11, 8 columns, ms):
+    //   16 waves, 30 trees         3,000 x 8 classes equal; 4,500 x 8 2.9 / 3.4 and x 5 2.7 /
+    //                              2.5; 6,000 x 5 3.2 / 3.4; 4,500 x 6 wins at 150
+    //   8 waves, 260 trees         2,000 x 8 equal; 3,000 x 5 3.7 / 3.9; 6,000 x 5 4.6 / 8.0
+    // For 9 to 16 classes 16 waves do not fit the LDS, and 8 pay for tiny jobs alone
+    // (16 classes, eight iterations of depth 10 at 260, 400, 512 trees):
+    //   300 x 10 (1,200 pairs)     5.85 6.35 6.78 / 5.68 6.19 6.50 ms
+    //   400 x 20 (2,400)           5.54 6.18 6.68 / 6.19 6.80 7.09
+    //   3,000 x 8 (12,000)         8.6 11.0 12.7 / 15.5 16.8 17.4
+    // Chosen launch shapes are those of the level kernels (the options' default row
+    // limit, which k_grow keeps to, is no such choice).
     const bool shapes = (o.small_rows && o.small_rows != 32) || o.grid_small || o.grid_hist ||
-                        o.grid_finalize || o.col_level || o.col_unit != 2048 || o.grid_col || o.hist_rb != 8 ||
-                        o.hist_rb_deep != 8 || o.band_level != 6 || o.hist_fw || o.col_waves;
+                        o.grid_finalize || o.col_level || o.col_unit != 2048 || o.grid_col ||
+                        o.hist_rb != 8 || o.hist_rb_deep != 8 || o.band_level != 6 || o.hist_fw ||
+                        o.col_waves;
     if (o.form == BORUTA_FORM_BATCHED && !any_reg && !shapes && pl.col_level >= pl.max_D) {
         int64_t pairs = 0;
         for (size_t j = 0; j < specs.size(); ++j)
             pairs = std::max(pairs, specs[j].n * (int64_t)pl.jp[j].mtry_max);
-        if (pl.T_total <= 256 && (pairs <= 24000 || (pairs <= 72000 && pl.T_total >= 192)))
+        const int64_t tall = pl.kmax == 8 && pl.max_D > 6 ? pl.max_n * maxK : 0;
+        if (pl.T_total <= 256 && ((pairs <= 24000 && (tall <= 24000 || pl.T_total >= 128)) ||
+                                  (pairs <= 72000 && pl.T_total >= 192)))
             pl.grow_waves = 16;
-        else if (pl.T_total <= 512 && pairs <= 24000)
+        else if (pl.T_total > 256 && pl.T_total <= 512 && tall <= 16000 &&
+                 pairs <= (pl.kmax <= 8 ? 24000 : 1800))
             pl.grow_waves = 8;
         pl.grow_cap = (uint32_t)((pl.max_n + 1) / 2);
         if (pl.max_n >= 65536 ||
