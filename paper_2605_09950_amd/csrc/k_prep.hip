@@ -191,6 +191,62 @@ __global__ __launch_bounds__(1024) void k_sort_bin(const uint32_t* keys, int64_t
     for (int64_t i = n + tid; i < n_pad; i += threads) out[i] = 0;
 }
 
+// Few columns of very many rows leave k_select_bin, a workgroup per column, on a few
+// compute units: these are sorted by all of them, in LDS tiles with global steps
+// between, and the bins are read off the rows again.
+// Sorts each tile of kSortTile keys in LDS (all merge sizes up to it), or, with
+// kmin > 0, runs only the steps below a tile of merge size kmin.
+__global__ __launch_bounds__(1024) void k_sort_tile(uint32_t* keys, int64_t P, int64_t kmin) {
+    __shared__ uint32_t s[kSortTile];
+    uint32_t* col = keys + (size_t)blockIdx.y * P + (size_t)blockIdx.x * kSortTile;
+    const uint32_t gbase = (uint32_t)blockIdx.x * kSortTile;
+    for (int i = threadIdx.x; i < kSortTile; i += 1024) s[i] = col[i];
+    __syncthreads();
+    const uint32_t k_lo = kmin > 0 ? (uint32_t)kmin : 2u;
+    const uint32_t k_hi = kmin > 0 ? (uint32_t)kmin : kSortTile;
+    for (uint32_t k = k_lo; k <= k_hi; k <<= 1) {
+        for (uint32_t j = (kmin > 0 ? kSortTile : k) >> 1; j > 0; j >>= 1) {
+            for (uint32_t t = threadIdx.x; t < kSortTile / 2; t += 1024) {
+                const uint32_t i = ((t & ~(j - 1u)) << 1) | (t & (j - 1u));
+                cmp_swap(s, i, i + j, ((gbase + i) & k) == 0);
+            }
+            __syncthreads();
+        }
+    }
+    for (int i = threadIdx.x; i < kSortTile; i += 1024) col[i] = s[i];
+}
+
+// One global compare-exchange step (merge size k, distance j >= kSortTile).
+__global__ void k_sort_step(uint32_t* keys, int64_t P, uint32_t k, uint32_t j) {
+    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;  // P / 2 <= 2^23 of them
+    if (t >= P / 2) return;
+    const uint32_t i = ((t & ~(j - 1u)) << 1) | (t & (j - 1u));
+    cmp_swap(keys + (size_t)blockIdx.y * P, i, i + j, (i & k) == 0);
+}
+
+// Cuts from the sorted keys, then the bins of one chunk of rows.
+__global__ __launch_bounds__(256) void k_bin(const float* X, int64_t n, int64_t p, int64_t P,
+                                             const uint32_t* keys, int B, uint8_t* bins,
+                                             int64_t n_pad, int64_t chunk) {
+    __shared__ uint32_t s_cut[256];
+    __shared__ int s_m;
+    const int64_t c = blockIdx.y;
+    const uint32_t* sk = keys + c * P;
+    const int tid = threadIdx.x;
+    if (tid < 64) {
+        const int m = cut_table(
+            B, [&](int t) { return sk[((int64_t)t * n + B - 1) / B - 1]; }, s_cut);
+        if (tid == 0) s_m = m;
+    }
+    __syncthreads();
+    const int m = s_m;
+    const int64_t r0 = (int64_t)blockIdx.x * chunk;
+    const int64_t r1 = min(r0 + chunk, n_pad);
+    uint8_t* out = bins + c * n_pad;
+    for (int64_t r = r0 + tid; r < r1; r += 256)
+        out[r] = r < n ? (uint8_t)bin_of(f2key(X[r * p + c]), s_cut, m) : 0;
+}
+
 // Bins of a longer column: the order statistics that its cuts take by selection --
 // a histogram of the keys' top 14 bits, then three of the next 6 bits of the keys
 // that share a wanted one's digits so far (at most 255 groups, numbered in rank
@@ -681,13 +737,34 @@ void launch_labels(const int32_t* y, size_t n, uint8_t* out, hipStream_t st) {
                        out);
 }
 
+// Few columns of very many rows are sorted.  Selection / sorting: 500,000 x 1 756 /
+// 275 us, x 8 755 / 419; 2^20 x 1 1,570 / 335, x 8 1,580 / 671, x 16 1,685 / 1,269
+// (which 2^19 + 1 rows, padded to as many keys, would take too, for 814); 2^22 x 8
+// 6.7 / 3.1 ms, 2^23 x 1 13.2 / 0.95.
+bool sort_columns(int64_t n, int64_t p) {
+    return n > (int64_t(1) << 18) && (p <= 8 || (p <= 16 && n > 3 * (int64_t(1) << 18)));
+}
+
 // Bins of all p columns of X (device, row-major) into bins[p][n_pad];
 // keys is scratch of p * P words.
 void launch_binning(const float* X, int64_t n, int64_t p, int B, uint8_t* bins, int64_t n_pad,
                     uint32_t* keys, int64_t P, hipStream_t st) {
     hipLaunchKernelGGL(k_to_keys, dim3((unsigned)((p + 31) / 32), (unsigned)((P + 31) / 32)),
                        dim3(256), 0, st, X, n, p, P, keys);
-    if (P > kSortTile) {
+    if (sort_columns(n, p)) {
+        hipLaunchKernelGGL(k_sort_tile, dim3((unsigned)(P / kSortTile), (unsigned)p), dim3(1024),
+                           0, st, keys, P, (int64_t)0);
+        for (int64_t k = 2 * kSortTile; k <= P; k <<= 1) {
+            for (int64_t j = k >> 1; j >= kSortTile; j >>= 1)
+                hipLaunchKernelGGL(k_sort_step, dim3((unsigned)(P / 2 / 256), (unsigned)p),
+                                   dim3(256), 0, st, keys, P, (uint32_t)k, (uint32_t)j);
+            hipLaunchKernelGGL(k_sort_tile, dim3((unsigned)(P / kSortTile), (unsigned)p),
+                               dim3(1024), 0, st, keys, P, k);
+        }
+        const int64_t chunk = 16384;
+        hipLaunchKernelGGL(k_bin, dim3((unsigned)((n_pad + chunk - 1) / chunk), (unsigned)p),
+                           dim3(256), 0, st, X, n, p, P, keys, B, bins, n_pad, chunk);
+    } else if (P > kSortTile) {
         hipLaunchKernelGGL(k_select_bin, dim3(1, (unsigned)p), dim3(1024), 0, st, keys, n, P, B,
                            bins, n_pad);
     } else {
