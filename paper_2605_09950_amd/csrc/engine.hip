@@ -363,6 +363,26 @@ struct Region {
     }
 };
 
+// The buffers of boruta_bin: the inputs, the columns' keys (read 16 bytes at a
+// time), the bins, the validation flag.
+struct BinPlan {
+    int64_t n_pad, P;
+    size_t X, keys, bins, flags, total;
+};
+
+BinPlan bin_plan(int64_t n, int64_t p) {
+    BinPlan b;
+    Region r;
+    b.n_pad = round_up(n, 256);
+    b.P = pow2_at_least(n);
+    b.X = r.take((size_t)n * p * 4);
+    b.keys = r.take((size_t)p * b.P * 4);
+    b.bins = r.take((size_t)p * b.n_pad);
+    b.flags = r.take(4);
+    b.total = r.total;
+    return b;
+}
+
 struct JobPlan {
     int64_t n_pad, P;
     size_t rowmaj = 0;        // row-major widened bins (rm_stride 0: none)
@@ -1996,30 +2016,29 @@ int boruta_bin(const float* X, int64_t n, int64_t p, int32_t n_bins, uint8_t* bi
     }
     try {
         require_device();
-        const int64_t n_pad = round_up(n, 256), P = pow2_at_least(n);
-        const size_t bx = (size_t)n * p * 4, bk = (size_t)p * P * 4, bb = (size_t)p * n_pad;
+        const BinPlan pl = bin_plan(n, p);
         DeviceRegion reg;
         const char* fail = std::getenv("BORUTA_FAIL_ALLOC");
         if ((fail && std::strcmp(fail, "1") == 0) ||
-            hipMalloc(&reg.p, bx + bk + bb + 256) != hipSuccess) {
+            hipMalloc(&reg.p, pl.total) != hipSuccess) {
             (void)hipGetLastError();
             reg.p = nullptr;
             throw Error(BORUTA_E_OOM, "hipMalloc for the binning failed");
         }
-        float* dX = reinterpret_cast<float*>(reg.p);
-        uint32_t* keys = reinterpret_cast<uint32_t*>(reg.p + bx);
-        uint8_t* bins = reinterpret_cast<uint8_t*>(reg.p + bx + bk);
-        uint32_t* flags = reinterpret_cast<uint32_t*>(reg.p + ((bx + bk + bb + 3) & ~size_t(3)));
+        float* dX = reinterpret_cast<float*>(reg.p + pl.X);
+        uint32_t* keys = reinterpret_cast<uint32_t*>(reg.p + pl.keys);
+        uint8_t* bins = reinterpret_cast<uint8_t*>(reg.p + pl.bins);
+        uint32_t* flags = reinterpret_cast<uint32_t*>(reg.p + pl.flags);
         hipStream_t st = nullptr;
-        HIPC(hipMemcpyAsync(dX, X, bx, hipMemcpyHostToDevice, st));
+        HIPC(hipMemcpyAsync(dX, X, (size_t)n * p * 4, hipMemcpyHostToDevice, st));
         launch_fill_u32(flags, 1, 0u, st);
         launch_validate_reg(dX, (size_t)n * p, dX, 0, flags, st);  // X finite
         uint32_t f = 0;
         HIPC(hipMemcpyAsync(&f, flags, 4, hipMemcpyDeviceToHost, st));
         HIPC(hipStreamSynchronize(st));
         if (f) throw Error(BORUTA_E_NONFINITE, "X holds NaN or Inf");
-        launch_binning(dX, n, p, n_bins, bins, n_pad, keys, P, st);
-        HIPC(hipMemcpy2DAsync(bins_out, (size_t)n, bins, (size_t)n_pad, (size_t)n, (size_t)p,
+        launch_binning(dX, n, p, n_bins, bins, pl.n_pad, keys, pl.P, st);
+        HIPC(hipMemcpy2DAsync(bins_out, (size_t)n, bins, (size_t)pl.n_pad, (size_t)n, (size_t)p,
                               hipMemcpyDeviceToHost, st));
         HIPC(hipStreamSynchronize(st));
         return BORUTA_OK;
