@@ -352,6 +352,12 @@ __host__ __device__ __forceinline__ uint32_t count_bits(int kmax, uint32_t N) {
 // Words of a node's packed class counts: two classes to a word.
 __host__ __device__ constexpr int pk_words(int kmax) { return (kmax + 1) / 2; }
 
+// LDS a gfx950 workgroup may allocate (checked against the device at set-up).  The
+// kernels that take more than the default 64 KB are allowed all of it, once and for
+// every plan: a kernel's limit is the process's, and one set to a plan's own size
+// would be lowered under the sessions of larger ones.
+constexpr size_t kLdsPerWorkgroup = 160 * 1024;
+constexpr size_t kGrowStaticLds = 2048;  // k_grow's own shared variables, at most
 // k_col_count: columns counted in LDS (64 KB) and its workgroups
 constexpr uint32_t kColCountLds = 16384;
 constexpr uint32_t kColCountGrid = 512;

@@ -47,9 +47,9 @@ void launch_draws(const ForestDev&, int, uint32_t, hipStream_t);
 void launch_lists(const ForestDev&, int, uint32_t, hipStream_t);
 void launch_col_sort(const ForestDev&, int, uint32_t, hipStream_t);
 size_t hist_col_lds(int, int, uint32_t);
-hipError_t prepare_hist_col(int, size_t);
+hipError_t prepare_hist_col(int);
 size_t grow_lds(int, uint32_t, int, uint32_t);
-hipError_t prepare_grow(int, size_t);
+hipError_t prepare_grow(int);
 void launch_grow(const ForestDev&, uint32_t, int, uint32_t, hipStream_t);
 void launch_hist_col(const ForestDev&, int, uint32_t, int, uint32_t, hipStream_t);
 // k_importance.hip
@@ -74,8 +74,6 @@ namespace {
 
 thread_local std::string g_err;
 
-// LDS a gfx950 workgroup may allocate (checked against the device at set-up).
-constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 // Column-major histogram path: the first tree level it serves when chosen
 // automatically, the widened bin matrix of one job above which it is chosen
 // (such a matrix no longer stays in the 256 MB last-level cache beside the
@@ -720,7 +718,8 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
             pl.grow_waves = 8;
         pl.grow_cap = (uint32_t)((pl.max_n + 1) / 2);
         if (pl.max_n >= 65536 ||
-            grow_lds(pl.kmax, pl.small_head, pl.grow_waves, pl.grow_cap) + 2048 > kLdsPerWorkgroup)
+            grow_lds(pl.kmax, pl.small_head, pl.grow_waves, pl.grow_cap) + kGrowStaticLds >
+                kLdsPerWorkgroup)
             pl.grow_waves = 0;
     }
     pl.total = r.total + 256;
@@ -1038,7 +1037,7 @@ void Engine::setup(std::vector<int>& status) {
         HIPC(hipGetDevice(&dev));
         HIPC(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
         const size_t lds = hist_col_lds(pl.kmax, pl.col_waves, pl.gq_max);
-        if ((size_t)lds_max < lds || prepare_hist_col(pl.kmax, lds) != hipSuccess) {
+        if ((size_t)lds_max < lds || prepare_hist_col(pl.kmax) != hipSuccess) {
             (void)hipGetLastError();
             pl.col_level = kColNever;  // node-major at every level (same item layout)
         } else {
@@ -1051,8 +1050,7 @@ void Engine::setup(std::vector<int>& status) {
             launch_fill_u32(at<uint32_t>(pl.fcnt), pl.n_gcol, 0u, st);
         }
     }
-    if (pl.grow_waves && prepare_grow(pl.kmax, grow_lds(pl.kmax, pl.small_head, pl.grow_waves, pl.grow_cap)) !=
-                             hipSuccess) {
+    if (pl.grow_waves && prepare_grow(pl.kmax) != hipSuccess) {
         (void)hipGetLastError();
         pl.grow_waves = 0;  // the level kernels
     }

@@ -2573,6 +2573,7 @@ __global__ __launch_bounds__(1024) void k_grow(ForestDev F0, uint32_t cap) {
     // from the front, large ones from the back
     extern __shared__ uint4 lds_raw[];
     __shared__ GrowLds G;
+    static_assert(sizeof(GrowLds) <= kGrowStaticLds, "k_grow's share of the LDS");
     const uint32_t g = blockIdx.x;
     const TreeDev tr = F0.trees[g];
     JobDev& J = F0.jobs[tr.job];
@@ -2863,9 +2864,9 @@ static const void* grow_fn(int kmax) {
     }
 }
 
-hipError_t prepare_grow(int kmax, size_t lds) {
+hipError_t prepare_grow(int kmax) {
     return hipFuncSetAttribute(grow_fn(kmax), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds);
+                               (int)(kLdsPerWorkgroup - kGrowStaticLds));
 }
 
 void launch_grow(const ForestDev& F, uint32_t n_trees, int waves, uint32_t cap, hipStream_t st) {
@@ -2888,9 +2889,9 @@ static const void* hist_col_fn(int kmax) {
     }
 }
 
-hipError_t prepare_hist_col(int kmax, size_t lds) {
+hipError_t prepare_hist_col(int kmax) {
     return hipFuncSetAttribute(hist_col_fn(kmax), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds);
+                               (int)kLdsPerWorkgroup);
 }
 
 void launch_hist_col(const ForestDev& F, int level, uint32_t grid_wg, int waves, uint32_t gq_max,

@@ -821,7 +821,7 @@ uint32_t prepare_boot_draw(int64_t max_n) {
         (size_t)lds_max < chunk * sizeof(uint32_t) ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(&k_boot_draw_lds),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(chunk * sizeof(uint32_t))) != hipSuccess) {
+                            (int)(kBootLdsRows * sizeof(uint32_t))) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
