@@ -396,34 +396,6 @@ struct JobPlan {
     size_t wy0 = 0, wy1 = 0;      // regression: the records' weighted targets
 };
 
-struct Plan {
-    std::vector<JobPlan> jp;
-    size_t keys, jobs, trees, tree_base, flags, nodes, cls, ngain, small0, small1, cand, icand,
-        feat, fcol, srec, kinds, chunk_sums, slot0, slot1, ctrs, alg, tot;
-    size_t fcnt = 0, fpos = 0, fitems = 0, units = 0, gcolq = 0, big = 0;
-    uint32_t big_cap = 0;  // nodes of weight 65536 and more in a column-major level
-    size_t seed_med = 0, seed_dec = 0;  // multi-seed aggregate [p]
-    size_t dec_ptrs = 0;                // per job: the decisions the aggregate reads
-    size_t kl_S = 0, kl_pi = 0, kl_delta = 0;  // KL importance buffers (shared by its jobs)
-    uint32_t node_cap = 0, slot_cap = 0, small_cap = 0;
-    int kmax = 4, max_sha = 1, max_pw = 1, max_D = 1, T_total = 0, mtry_cap = 1,
-        npi = 1, fw = 1;
-    // column-major histogram path: levels >= col_level (col_level >= max_D: none)
-    int col_level = kColNever, col_waves = 0;
-    bool has_cls = false, has_reg = false;
-    int small_rows = 32;  // row limit of the wave path
-    bool rowmaj = false;  // the jobs keep row-major copies of their widened bins
-    uint32_t small_head = 0, bins_off = 0;  // LDS head of the wave path (ForestDev)
-    int hist_words = 1;        // LDS words per bin of a histogram item
-    uint32_t n_gcol = 0, unit_cap = 0, gq_max = 0;
-    int64_t max_n = 0;
-    int grow_waves = 0;       // waves per tree of the one-launch growth (0: level kernels)
-    uint32_t grow_cap = 0;    // searched nodes of a tree level it holds
-    PermutShape permut;       // launch shape of the Permut kernel
-    uint32_t boot_chunk = 0;  // rows per workgroup of the LDS bootstrap counts (0: atomics)
-    size_t total = 0;
-};
-
 int max_shadows(const Spec& s) { return (int)std::max<int64_t>(s.p, 8); }
 // Most columns that a node of the job draws.
 int mtry_cap(const Spec& s) {
@@ -443,19 +415,25 @@ int mtry_cap(const Spec& s) {
 //   regression, up to 10 draws: 64 wins or ties
 //     34   2,000 x 600, 10 trees 4.06 / 5.48, 200 6.7 / 7.3, 500 11.3 / 11.4
 //     100  600 x 5,000, 50 trees 5.7 / 12.3, 500 12.7 / 17.5
+//     beside classification jobs up to 20 (20 such jobs of up to 1,500 x 200: 12.5 / 11.9)
 // Regression forests of few histogram items a level do without the wave path: its
 // launch and the second stream cost 10-14 us a level.  None / the better limit:
 //     7    5,000 x 30, depth 12, 30 trees 4.50 / 4.98, 60 5.67 / 5.31, 100 7.13 / 5.90
 //     34   1,000 x 600, depth 8, 30 trees 2.82 / 3.18, 60 3.33 / 3.38, 100 4.03 / 3.64
 //     100  600 x 5,000, depth 10, 10 trees 4.11 / 5.47, 50 7.23 / 5.73
 // but where a wave's few draws are done before the histogram kernels' chain, in
-// trees of few rows (4 draws, 300 x 10, depth 16, 30 trees 5.57 / 4.53).
+// trees of few rows (4 draws, 300 x 10, depth 16, 30 trees 5.57 / 4.53); there too
+// the second stream costs more than it hides (200 x 10, depth 10, 10 trees 2.93 ms
+// with it, 2.76 without).
 // The plain form, whose nodes run one after the other, takes 32 (one iteration
 // at 32 and 64: 2,000 x 20,000, 2 classes, 4 trees 25.0 and 38.4 ms; 10,000 x 500, 3
 // classes 30.5 and 35.1; regression 3,000 x 600 17.7 and 21.1).
-int wave_rows(const std::vector<Spec>& specs, const Opts& o) {
-    if (o.small_rows) return o.small_rows;
-    if (o.form == BORUTA_FORM_PLAIN) return 32;
+struct WaveShape {
+    int rows;
+    bool beside;  // launched on the second stream, beside the histogram kernels
+};
+
+WaveShape wave_shape(const std::vector<Spec>& specs, const Opts& o) {
     bool cls = false, reg = false;
     double rows = 0.0, items = 0.0;  // of all trees; histogram items of an iteration
     int draws = 1, depth = 1;
@@ -471,11 +449,42 @@ int wave_rows(const std::vector<Spec>& specs, const Opts& o) {
         longest = std::max(longest, s.n);
     }
     const double few = draws <= 4 ? 25000.0 : draws <= 64 ? 50000.0 : 125000.0;  // a level
-    if (!cls && items <= few * depth && (draws > 4 || longest > 400)) return 1;
-    if (reg && draws > 10 && rows < 30000.0 * draws) return 32;
-    if (cls && draws > 40 && rows < 2000.0 * draws) return 32;
-    return 64;
+    const bool small_reg = !cls && items <= few * depth;
+    if (o.small_rows) return {o.small_rows, !small_reg};
+    if (o.form == BORUTA_FORM_PLAIN) return {32, false};
+    if (small_reg) return {draws <= 4 && longest <= 400 ? 64 : 1, false};
+    if (reg && draws > (cls ? 20 : 10) && rows < 30000.0 * draws) return {32, true};
+    if (cls && draws > 40 && rows < 2000.0 * draws) return {32, true};
+    return {64, true};
 }
+
+struct Plan {
+    std::vector<JobPlan> jp;
+    size_t keys, jobs, trees, tree_base, flags, nodes, cls, ngain, small0, small1, cand, icand,
+        feat, fcol, srec, kinds, chunk_sums, slot0, slot1, ctrs, alg, tot;
+    size_t fcnt = 0, fpos = 0, fitems = 0, units = 0, gcolq = 0, big = 0;
+    uint32_t big_cap = 0;  // nodes of weight 65536 and more in a column-major level
+    size_t seed_med = 0, seed_dec = 0;  // multi-seed aggregate [p]
+    size_t dec_ptrs = 0;                // per job: the decisions the aggregate reads
+    size_t kl_S = 0, kl_pi = 0, kl_delta = 0;  // KL importance buffers (shared by its jobs)
+    uint32_t node_cap = 0, slot_cap = 0, small_cap = 0;
+    int kmax = 4, max_sha = 1, max_pw = 1, max_D = 1, T_total = 0, mtry_cap = 1,
+        npi = 1, fw = 1;
+    // column-major histogram path: levels >= col_level (col_level >= max_D: none)
+    int col_level = kColNever, col_waves = 0;
+    bool has_cls = false, has_reg = false;
+    WaveShape wave{64, true};
+    bool rowmaj = false;  // the jobs keep row-major copies of their widened bins
+    uint32_t small_head = 0, bins_off = 0;  // LDS head of the wave path (ForestDev)
+    int hist_words = 1;        // LDS words per bin of a histogram item
+    uint32_t n_gcol = 0, unit_cap = 0, gq_max = 0;
+    int64_t max_n = 0;
+    int grow_waves = 0;       // waves per tree of the one-launch growth (0: level kernels)
+    uint32_t grow_cap = 0;    // searched nodes of a tree level it holds
+    PermutShape permut;       // launch shape of the Permut kernel
+    uint32_t boot_chunk = 0;  // rows per workgroup of the LDS bootstrap counts (0: atomics)
+    size_t total = 0;
+};
 
 Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_device) {
     Plan pl;
@@ -492,7 +501,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     uint64_t node_cap = 0, slot_cap = 0, small_cap = 0, n_gcol = 0;
     // the large-node lists are sized for the chosen row limit of the wave path; where
     // the library chooses it, for the options' default or less
-    const int min_rows = o.small_rows ? o.small_rows : std::min(wave_rows(specs, o), 32);
+    const int min_rows = o.small_rows ? o.small_rows : std::min(wave_shape(specs, o).rows, 32);
     uint64_t kl_S = 0, kl_pi = 0, kl_delta = 0;
     for (const Spec& s : specs) {
         JobPlan j;
@@ -607,7 +616,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         pl.fw = fw;
     }
     pl.npi = (pl.mtry_cap + pl.fw - 1) / pl.fw;
-    pl.small_rows = wave_rows(specs, o);
+    pl.wave = wave_shape(specs, o);
     if (node_cap >= 0xFFFFFFF0ull || slot_cap * (uint64_t)pl.mtry_cap + n_gcol >= 0xFFFFFFF0ull ||
         small_cap >= 0xFFFFFFF0ull)
         throw Error(BORUTA_E_INVALID_ARG, "problem too large: more than 2^32 tree nodes");
@@ -1089,7 +1098,7 @@ ForestDev Engine::forest() const {
         F.unit_cap = pl.unit_cap;
         F.col_unit = (uint32_t)O.col_unit;
     }
-    F.small_rows = (uint32_t)pl.small_rows;
+    F.small_rows = (uint32_t)pl.wave.rows;
     F.small_head = pl.small_head;
     F.bins_off = pl.bins_off;
     F.rowmaj = pl.rowmaj ? 1 : 0;
@@ -1212,8 +1221,8 @@ void Engine::enqueue_iteration() {
         // nodes, child pairs, row segments and kinds entries: without kernel
         // statistics the small-node launch runs on a second stream, beside
         // the large-node kernels, and rejoins before the lists are built.
-        const bool wave = pl.has_cls || pl.small_rows > 1;
-        const bool fork = wave && !stats && side != nullptr;
+        const bool wave = pl.has_cls || pl.wave.rows > 1;
+        const bool fork = wave && pl.wave.beside && !stats && side != nullptr;
         hipStream_t ss = st;
         if (fork) {
             HIPC(hipEventRecord(ev_fork, st));
