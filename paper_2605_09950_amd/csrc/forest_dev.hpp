@@ -2,8 +2,6 @@
 // node creation / classification and wave-level candidate reductions.
 #pragma once
 
-#include <climits>
-
 #include "dev_common.hpp"
 #include "reg_dev.hpp"
 
@@ -111,24 +109,6 @@ __device__ __forceinline__ uint32_t wave_min_u_dpp(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-__device__ __forceinline__ float wave_max_f(float v) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) v = fmaxf(v, __shfl_xor(v, m));
-    return v;
-}
-
-__device__ __forceinline__ int wave_min_i(int v) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) v = min(v, __shfl_xor(v, m));
-    return v;
-}
-
-__device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) v = max(v, __shfl_xor(v, m));
-    return v;
-}
-
 // Margin of the FP32 ranking.  An FP32 score is within eps of its exact value
 // Q: eps = 5u (u = 2^-24) for cand_q32 and (K + 4)u <= 20u for hist_q32
 // below.  The exact best then scores at least (1 - 2 eps) * FP32 max, so
@@ -156,93 +136,6 @@ __device__ __forceinline__ float hist_q32(const uint32_t* cl, const uint32_t* cn
     const float nr = (float)N - nl;
     if (nl == 0.0f || nr == 0.0f) return -1.0f;
     return sl * __builtin_amdgcn_rcpf(nl) + sr * __builtin_amdgcn_rcpf(nr);
-}
-
-// Best of one feature's candidates with FP32 ranking and exact recheck of the
-// finalists.  q32 < 0 marks an invalid candidate.
-__device__ __forceinline__ Cand wave_best_fp32(const Cand& c, float q32) {
-    const float qmax = wave_max_f(q32);
-    Cand out;
-    out.nl = 0;
-    out.b = 0x7FFFFFFF;
-    if (qmax < 0.0f) return out;  // no valid candidate in the wave
-    const bool fin = q32 >= fp32_floor(qmax);
-    const int bmin = wave_min_i(fin ? c.b : 0x7FFFFFFF);
-    const int bmax = wave_max_i(fin ? c.b : -1);
-    if (bmin == bmax) {
-        // one threshold among the finalists: the same candidate in every finalist lane
-        const unsigned long long mask = __ballot(fin && c.b == bmin);
-        return shfl_cand(c, (int)__ffsll(mask) - 1);
-    }
-    Cand f = c;
-    if (!fin) {
-        f.nl = 0;
-        f.b = 0x7FFFFFFF;
-    }
-    return wave_best_exact(f);
-}
-
-// Total order over candidates of different features: higher Q, then the
-// earlier draw position q, then the smaller threshold b (equal (q, b) is the
-// same candidate).  The winner over a set is the sequential rule's choice.
-__device__ __forceinline__ bool cand_wins_total(const Cand& a, const Cand& b) {
-    if (b.nl == 0) return a.nl != 0;
-    if (a.nl == 0) return false;
-    if (cand_better(a, b)) return true;
-    if (cand_better(b, a)) return false;
-    return a.q < b.q || (a.q == b.q && a.b < b.b);
-}
-
-__device__ __forceinline__ Cand wave_best_total_exact(Cand c) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const Cand o = shfl_xor_cand(c, m);
-        if (cand_wins_total(o, c)) c = o;
-    }
-    return c;
-}
-
-__device__ __forceinline__ long long wave_min_ll(long long v) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const long long o = __shfl_xor(v, m);
-        v = o < v ? o : v;
-    }
-    return v;
-}
-
-__device__ __forceinline__ long long wave_max_ll(long long v) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const long long o = __shfl_xor(v, m);
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
-// The same with FP32 ranking: exact comparisons only among the finalists,
-// and none when all finalists are one candidate (the common case).
-__device__ __forceinline__ Cand wave_best_total_fp32(const Cand& c, float q32) {
-    const float qmax = wave_max_f(q32);
-    Cand out;
-    out.nl = 0;
-    out.b = 0x7FFFFFFF;
-    out.q = 0x7FFFFFFF;
-    if (qmax < 0.0f) return out;
-    const bool fin = q32 >= fp32_floor(qmax);
-    const long long key = ((long long)c.q << 9) | (long long)(c.b & 511);
-    const long long kmin = wave_min_ll(fin ? key : LLONG_MAX);
-    const long long kmax = wave_max_ll(fin ? key : -1ll);
-    if (kmin == kmax) {
-        const unsigned long long mask = __ballot(fin && key == kmin);
-        return shfl_cand(c, (int)__ffsll(mask) - 1);
-    }
-    Cand f = c;
-    if (!fin) {
-        f.nl = 0;
-        f.b = 0x7FFFFFFF;
-    }
-    return wave_best_total_exact(f);
 }
 
 // Packed class counters: a side's class counts as fields of FB bits -- 8 for
