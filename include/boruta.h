@@ -147,9 +147,9 @@ typedef struct {
                              column-major histogram path (items bucketed by bin
                              column, each column staged once per unit in LDS);
                              [1, 64], 64 = never; 0 (default) = automatic: level
-                             3 when some job's widened bin matrix (2p columns of
-                             n rounded up to 256 bytes) exceeds 128 MiB, else
-                             never.  The path needs a whole bin column plus two
+                             3 (5 for forests of few draws per column) when some
+                             job's widened bin matrix (2p columns of n rounded up
+                             to 256 bytes) exceeds 128 MiB, else never.  The path needs a whole bin column plus two
                              histograms in one workgroup's LDS; where it does
                              not fit, every level stays node-major.              */
     int32_t col_unit;     /* items (node, draw) per unit of that path, [1, 65536];

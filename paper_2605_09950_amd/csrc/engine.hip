@@ -79,10 +79,14 @@ thread_local std::string g_err;
 // (such a matrix no longer stays in the 256 MB last-level cache beside the
 // row records, so node-major gathers pull whole lines from HBM), and the
 // value that disables it.
-// The level: 100,000 x 2,000, 4 classes, 3 iterations, take 140.9 ms from level 3,
-// 141.2 from 4, 143.9 from 5, 141.5 from 2 and 143.1 from 1 (above it a node's rows
-// are most of a column, which its histogram reads whole anyway).
-constexpr int kColLevelAuto = 3;
+// The level: a column is staged for the level's items that drew it, so the path starts
+// at level 3 where a column has kColItems of them there, else at 5.  Three iterations
+// from level 3, 4, 5 (items per column at level 3): 100,000 x 2,000, 300 trees (38)
+// 140.9, 141.2, 143.9 ms; 60,000 x 1,200, 100 trees (16) 24.9, 24.4, 24.2; 100,000 x
+// 1,500, 30 trees (4) 29.0, 28.2, 27.4; 10,000 x 10,000, 30 trees of depth 6 (2) 8.6,
+// 7.7, 6.5.
+constexpr int kColLevelAuto = 3, kColLevelFew = 5;
+constexpr double kColItems = 28.0;
 constexpr size_t kColAutoBytes = size_t(128) << 20;
 constexpr int kColNever = 64;
 // KL importance: bound of its per-block difference buffer.
@@ -411,7 +415,9 @@ int mtry_cap(const Spec& s) {
 //   classification, 24 draws: 64 wins by 2-11% at all sizes; 34: by up to 7% either way
 //     63   2,000 x 2,000, 10 trees 3.62 / 4.29, 50 4.15 / 4.40, 200 5.84 / 5.56
 //     200  600 x 20,000, 50 trees 8.5 / 11.0, 500 12.2 / 12.6; 2,000 rows, 200 14.1 / 14.3
-//     (the 64-job batch 158 / 137, 10,000 x 500 82.2 / 79.6 for whole runs)
+//     (the 64-job batch 158 / 137, 10,000 x 500 82.2 / 79.6 for whole runs); where the
+//     bins are read by row (by_row: plans with column-major levels) 64 wins: 2,000 x
+//     40,000, 30 trees of depth 14 35.1 / 32.5
 //   regression, up to 10 draws: 64 wins or ties
 //     34   2,000 x 600, 10 trees 4.06 / 5.48, 200 6.7 / 7.3, 500 11.3 / 11.4
 //     100  600 x 5,000, 50 trees 5.7 / 12.3, 500 12.7 / 17.5
@@ -433,7 +439,7 @@ struct WaveShape {
     bool beside;  // launched on the second stream, beside the histogram kernels
 };
 
-WaveShape wave_shape(const std::vector<Spec>& specs, const Opts& o) {
+WaveShape wave_shape(const std::vector<Spec>& specs, const Opts& o, bool by_row) {
     bool cls = false, reg = false;
     double rows = 0.0, items = 0.0;  // of all trees; histogram items of an iteration
     int draws = 1, depth = 1;
@@ -454,7 +460,7 @@ WaveShape wave_shape(const std::vector<Spec>& specs, const Opts& o) {
     if (o.form == BORUTA_FORM_PLAIN) return {32, false};
     if (small_reg) return {draws <= 4 && longest <= 400 ? 64 : 1, false};
     if (reg && draws > (cls ? 20 : 10) && rows < 30000.0 * draws) return {32, true};
-    if (cls && draws > 40 && rows < 2000.0 * draws) return {32, true};
+    if (cls && !by_row && draws > 40 && rows < 2000.0 * draws) return {32, true};
     return {64, true};
 }
 
@@ -501,7 +507,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     uint64_t node_cap = 0, slot_cap = 0, small_cap = 0, n_gcol = 0;
     // the large-node lists are sized for the chosen row limit of the wave path; where
     // the library chooses it, for the options' default or less
-    const int min_rows = o.small_rows ? o.small_rows : std::min(wave_shape(specs, o).rows, 32);
+    const int min_rows = o.small_rows ? o.small_rows : std::min(wave_shape(specs, o, false).rows, 32);
     uint64_t kl_S = 0, kl_pi = 0, kl_delta = 0;
     for (const Spec& s : specs) {
         JobPlan j;
@@ -590,8 +596,16 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     int col_level = any_reg ? kColNever : o.col_level;
     if (col_level == 0) {
         size_t widest = 0;
-        for (const JobPlan& j : pl.jp) widest = std::max(widest, (size_t)j.pw_cap * j.n_pad);
-        col_level = widest > kColAutoBytes ? kColLevelAuto : kColNever;
+        double items = 0.0;  // per column at level kColLevelAuto
+        for (size_t i = 0; i < specs.size(); ++i) {
+            const JobPlan& j = pl.jp[i];
+            widest = std::max(widest, (size_t)j.pw_cap * j.n_pad);
+            items = std::max(items, std::ldexp((double)specs[i].T * j.mtry_max / j.pw_cap,
+                                               kColLevelAuto));
+        }
+        col_level = widest <= kColAutoBytes ? kColNever
+                    : items >= kColItems    ? kColLevelAuto
+                                            : kColLevelFew;
     }
     if (o.form == BORUTA_FORM_BATCHED && col_level < pl.max_D) {
         const size_t per_wave = (size_t)pk_words(pl.kmax) * 256 * 4, col = (size_t)pl.gq_max * 16;
@@ -616,7 +630,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         pl.fw = fw;
     }
     pl.npi = (pl.mtry_cap + pl.fw - 1) / pl.fw;
-    pl.wave = wave_shape(specs, o);
+    pl.wave = wave_shape(specs, o, pl.col_level < pl.max_D);
     if (node_cap >= 0xFFFFFFF0ull || slot_cap * (uint64_t)pl.mtry_cap + n_gcol >= 0xFFFFFFF0ull ||
         small_cap >= 0xFFFFFFF0ull)
         throw Error(BORUTA_E_INVALID_ARG, "problem too large: more than 2^32 tree nodes");
