@@ -94,10 +94,13 @@ typedef struct {
                                rows x (features drawn + 6)                          */
 } boruta_kernel_stat;
 
+/* Kernel statistics are those of the level kernels: with them a small forest,
+ * whose trees otherwise grow in one launch, takes the level kernels too (so
+ * these times are not parts of that forest's time without statistics).          */
 typedef struct {
-    boruta_kernel_stat hist_large; /* node histogram + split scan, > 64 rows      */
-    boruta_kernel_stat hist_small; /* wave-per-node split search, <= 64 rows      */
-    boruta_kernel_stat finalize;   /* split choice + row partition, > 64 rows     */
+    boruta_kernel_stat hist_large; /* node histogram + split scan, > small_rows   */
+    boruta_kernel_stat hist_small; /* wave-per-node split search, <= small_rows   */
+    boruta_kernel_stat finalize;   /* split choice + row partition, > small_rows  */
     boruta_kernel_stat permut;     /* re-routing for the permutation importances  */
     double iter_ms;                /* device time of all iterations               */
     int64_t iterations;            /* job-iterations run                          */
@@ -125,7 +128,11 @@ typedef struct {
                              needs events around every launch.  Results are
                              identical either way.                                 */
     /* Launch tuning (batched form; every choice gives identical results;
-     * 0 = the library's default).                                                 */
+     * 0 = the library's default).  Forests of few trees of few rows grow in one
+     * launch per iteration; a launch parameter chosen below (kl_rows and
+     * small_rows = 32 apart), by the caller or by a tuning cache, selects the level
+     * kernels instead, which it shapes.  A cache entry written for such a forest
+     * before these grew in one launch should be written anew.                     */
     int32_t small_rows;   /* nodes with at most this many distinct rows (and a
                              weighted count below the packed-counter limit) take
                              the wavefront path, [2, 64]; 0 = the library's choice
@@ -185,8 +192,8 @@ typedef struct {
     int32_t band_level;   /* first tree level of the deep band, [1, 64]; default 6 */
     int32_t hist_fw;      /* drawn features per node-major histogram item: 0
                              (default: 2 for two classes, else 1), 1, 2 or 4;
-                             reduced to at most 8 class rows of LDS per wavefront,
-                             raised to 768 LDS words per wavefront for a batch
+                             reduced to at most 8 draws times classes (2, 3, 4, 8
+                             or 16), raised to 2 for a two-class batch
                              with a regression job, and 1 whenever the plan has
                              column-major levels                                  */
     int32_t col_waves;    /* wavefronts per workgroup of the column-major kernel,

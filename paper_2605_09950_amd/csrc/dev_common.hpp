@@ -364,12 +364,11 @@ constexpr uint32_t kColCountGrid = 512;
 // Keyed-permutation round tables in LDS: 16-bit entries per table, rounds
 // << half for halves of at most 8 bits (6 rounds of 256 entries at most)
 constexpr uint32_t kDrawTab = 1536;
-constexpr int kSmallRows = 64;  // nodes with at most this many distinct rows take the wave path
+constexpr int kSmallRows = 64;  // most row records of a node on the wave path
 constexpr int kWave = 64;
 constexpr uint32_t kAlgWords = 1024;  // statistics words per kernel
 
-// Draws per histogram work item (one wavefront, LDS histogram of
-// hist_fw * kmax rows of 256 bins): 4 KB per wave up to 4 classes.
+// Draws per histogram work item (one wavefront, an LDS histogram per draw).
 __host__ __device__ constexpr int hist_fw(int kmax) { return kmax <= 4 ? 4 / kmax : 1; }
 
 // Column-major histogram path: a unit is a run of items (node, draw) of one
@@ -423,7 +422,7 @@ struct ForestDev {
                           // round table and the bins by row
     uint32_t bins_off;    // where the bins by row start there
     int32_t rowmaj;       // the plan's jobs keep row-major copies of their bins
-    uint32_t small_rows;  // a node takes the wave path only up to this many distinct rows
+    uint32_t small_rows;  // a node takes the wave path only up to this many row records
     int32_t mtry_cap;     // row stride of feat
     uint32_t draw_seg;    // lanes per node in k_draws: mtry_cap rounded up to a power
                           // of two, at most 64

@@ -617,7 +617,7 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
     }
     // histogram items per large node: fw draws each (the column-major path
     // takes one draw per item, and both paths then share that layout).  A
-    // chosen hist_fw is kept within 8 class rows of LDS per wave, and a plan
+    // chosen hist_fw is kept to 8 / kmax (the kernels' instantiations), and a plan
     // with a regression job keeps at least 768 words per wave (its items hold
     // 256 weights and 256 64-bit sums); none of this changes any result.
     if (pl.col_level < pl.max_D) {
@@ -1194,7 +1194,7 @@ void Engine::enqueue_iteration() {
     F.small_out = small[0];
     F.slot_node_out = slots[0];
     launch_boot_compact(F, n_trees, st);
-    // kernel statistics time the level kernels
+    // kernel statistics time the level kernels (small forests take k_grow without)
     const bool grow = pl.grow_waves && !stats;
     if (grow) {
         launch_grow(F, n_trees, pl.grow_waves, pl.grow_cap, st);

@@ -1645,12 +1645,13 @@ __global__ __launch_bounds__(256) void k_draws(ForestDev F, int level) {
 }
 
 // Large nodes, phase 1: one wavefront per (node, FW consecutive draws)
-// item, with its own LDS histogram [FW][KMAX][256] (4 KB up to 4 classes,
-// 8 KB / 16 KB for 5-8 / 9-16 classes).  The wave gathers the bins of its features at the node's rows,
-// accumulates the weighted class counts with LDS atomics (class-major rows
-// spread a wave's atomics over the banks by bin), scans each feature and
-// writes the item's best candidate and its left class counts.  No barriers:
-// the four waves of a workgroup are independent.
+// item, with its own LDS histograms, F.hist_words words per bin and draw: the
+// class counts packed two or four to a word, or one word per class where the
+// plan may hold nodes of weight 65536 and more (2 KB per draw of 3 or 4 classes,
+// 1 KB of 2).  The wave gathers the bins of its features at the node's rows,
+// adds each row's weight to its class's field with an LDS atomic, scans each
+// feature and writes the record of the item's best threshold (put_item).  No
+// barriers: the four waves of a workgroup are independent.
 // Work of a level for the node-major histogram kernels: node slots [0, n)
 // with npi items each.  Workgroup b takes the slots congruent to b mod 8 (the
 // grid is a multiple of 8), and its waves walk those slots' items in order,

@@ -333,7 +333,7 @@ __global__ __launch_bounds__(128) void k_permut(JobDev* jobs, const TreeDev* tre
                 turn |= (uint32_t)(at != 0xFFFFFFFFu) << e;
             }
         }
-        // their walks, two at a time
+        // their walks, kPermWalks at a time
         uint32_t f[kPermWalks], node[kPermWalks], sbin[kPermWalks];
         bool on[kPermWalks];
         auto begin = [&](int v) {
