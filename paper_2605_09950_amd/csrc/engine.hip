@@ -569,8 +569,10 @@ Plan make_plan(const std::vector<Spec>& specs, const Opts& o, bool inputs_on_dev
         // every searched node reserves a pair of child slots (a leaf leaves its
         // pair unused), so the pool holds up to twice the nodes of the trees
         node_cap += T + 2 * T * per_tree_nodes;
-        const uint64_t large_per_tree =
-            (uint64_t)(s.n + min_rows) / (uint64_t)(min_rows + 1);
+        uint64_t large_per_tree = (uint64_t)(s.n + min_rows) / (uint64_t)(min_rows + 1);
+        // without a wave path every searched node is one: no more than a level holds
+        if (min_rows == 1)
+            large_per_tree = std::min<uint64_t>(large_per_tree, uint64_t(1) << (s.D - 1));
         slot_cap += T * large_per_tree;
         small_cap += T * (uint64_t)((s.n + 1) / 2);
         pl.max_sha = std::max(pl.max_sha, j.max_sha);
