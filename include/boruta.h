@@ -138,8 +138,10 @@ typedef struct {
                              the wavefront path, [2, 64]; 0 = the library's choice
                              (64; 32 in the plain form and for forests of many
                              draws and few rows and trees; small regression
-                             forests take none), which calls without options
-                             take; default 32                                    */
+                             forests take none).  32, the value of
+                             boruta_default_options, is that choice too while
+                             every launch parameter has its value from there,
+                             and 32 beside any that has not (col_unit = 0)     */
     /* "needed" below: for the nodes tree level d can hold, at most the
      * plan's capacity and n_trees * 2^d; a chosen grid size is an upper
      * limit, lowered to what a level needs.                                */

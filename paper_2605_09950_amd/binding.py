@@ -234,7 +234,7 @@ def make_options(n_bins=256, n_perm=1, split_rank=RANK_FP32, form=FORM_BATCHED, 
     o.n_bins, o.n_perm, o.split_rank, o.form = n_bins, n_perm, split_rank, form
     o.graph = int(bool(graph))
     o.perc, o.rough_fix = int(perc), int(bool(rough_fix))
-    o.small_rows = 0  # the library's choice, unless tune holds one
+    o.small_rows = o.col_unit = 0  # the library's choices, unless tune holds some
     for k, v in (tune or {}).items():
         if k == "tune_cache":  # a path (see include/boruta.h)
             keep_cache = str(v).encode()

@@ -152,6 +152,18 @@ struct Opts {
     boruta_stats* stats = nullptr;
 };
 
+// Whether every launch parameter has boruta_default_options' value: nothing chosen.
+bool launch_untouched(const boruta_options& o) {
+    boruta_options d;
+    boruta_default_options(&d);
+    return o.small_rows == d.small_rows && o.grid_small == d.grid_small &&
+           o.grid_hist == d.grid_hist && o.grid_finalize == d.grid_finalize &&
+           o.col_level == d.col_level && o.col_unit == d.col_unit && o.grid_col == d.grid_col &&
+           o.kl_rows == d.kl_rows && o.hist_rb == d.hist_rb &&
+           o.hist_rb_deep == d.hist_rb_deep && o.band_level == d.band_level &&
+           o.hist_fw == d.hist_fw && o.col_waves == d.col_waves;
+}
+
 Opts read_opts(const boruta_options* o) {
     Opts r;
     if (o) {
@@ -160,7 +172,7 @@ Opts read_opts(const boruta_options* o) {
         r.split_rank = o->split_rank;
         r.form = o->form;
         r.graph = o->graph;
-        r.small_rows = o->small_rows;
+        r.small_rows = launch_untouched(*o) ? 0 : o->small_rows;
         r.grid_small = o->grid_small;
         r.grid_hist = o->grid_hist;
         r.grid_finalize = o->grid_finalize;
@@ -252,16 +264,13 @@ void apply_tune_cache(Opts& r, const boruta_options* o, const std::vector<Spec>&
             } catch (...) {
                 continue;
             }
-            // a field the caller left at its default takes the cached value
+            // a field the caller left at its default (0 is one too) takes the cached value
 #define BORUTA_TUNE_FIELD(name)                                        \
     if (key == #name) {                                                 \
-        if (o->name == d.name) r.name = v;                              \
+        if (o->name == d.name || o->name == 0) r.name = v;              \
         continue;                                                       \
     }
-            if (key == "small_rows") {  // 0, the library's choice, is no choice either
-                if (o->small_rows == 0 || o->small_rows == d.small_rows) r.small_rows = v;
-                continue;
-            }
+            BORUTA_TUNE_FIELD(small_rows)
             BORUTA_TUNE_FIELD(grid_small)
             BORUTA_TUNE_FIELD(grid_hist)
             BORUTA_TUNE_FIELD(grid_finalize)
@@ -296,8 +305,10 @@ void apply_tune_cache(Opts& r, const boruta_options* o, const std::vector<Spec>&
     c.tune_cache = nullptr;
     const Opts checked = read_opts(&c);
     const bool no_alloc = r.no_alloc;
+    const int small_rows = r.small_rows;  // a cached value is a choice, whatever the others
     r = checked;
     r.no_alloc = no_alloc;
+    r.small_rows = small_rows;
 }
 
 void check_spec(const Spec& s) {

@@ -37,6 +37,26 @@ def test_every_chosen_limit_acts(tmp_path):
             assert np.array_equal(r[k], base[k], equal_nan=True)
 
 
+def test_untouched_default_options_leave_the_choice_to_the_library():
+    # the options of boruta_default_options hold 32: no choice unless another
+    # launch parameter is set
+    import ctypes
+    rng = np.random.default_rng(61)
+    X = rng.standard_normal((3000, 12)).astype(np.float32)
+    y = np.argmax(X[:, :3] + rng.standard_normal((3000, 3)), axis=1).astype(np.int32)
+    n = {}
+    for unit in (2048, 0):
+        o, st = B.boruta_default_options(), B.Stats()
+        o.stats, o.col_unit = ctypes.pointer(st), unit
+        out = [np.zeros(12, np.int8), np.zeros((2, 12)), np.zeros(1, np.int32)]
+        ptr = [a.ctypes.data_as(ctypes.c_void_p) for a in (X, y, *out)]
+        assert B.lib().boruta_fit_ex(ptr[0], ptr[1], 3000, 12, 3, 10, 10, 0, 0, 2, 0.05, 3,
+                                     ctypes.byref(o), ptr[2], ptr[3], None, None, ptr[4]) == 0
+        n[unit] = sum(st.level_small)
+    assert n[2048] == wave_nodes(dict(small_rows=64))[0]
+    assert n[0] == wave_nodes(dict(small_rows=32))[0]
+
+
 def test_the_plain_form_keeps_to_32():
     n = {rows: wave_nodes(dict(small_rows=rows) if rows else None, form=B.FORM_PLAIN)[0]
          for rows in (0, 32, 64)}
